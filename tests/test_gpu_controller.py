@@ -65,6 +65,26 @@ def test_mlp_gradient_and_adam_match_oracle(n_rows):
         th, mo, vo = mlp.adam_step(th, mo, vo, t, lr, g)
 
 
+@pytest.mark.parametrize("n_rows", [15, 16, 17, 129, 4096 + 5, 40000])
+def test_mlp_gradient_at_tile_edges(n_rows):
+    """Rows around the gradient kernel's 16-row tiles, more than one tile per
+    workgroup, and more tiles than wavefronts.  FP32 sums of n terms: errors
+    below (16 + sqrt(n)) * 2^-23 of the largest gradient."""
+    rng = np.random.default_rng(70 + n_rows)
+    theta = rng.normal(scale=0.2, size=mlp.N_PARAM).astype(np.float32).astype(np.float64)
+    X = rng.normal(size=(n_rows, 8)).astype(np.float32).astype(np.float64)
+    Y = rng.normal(size=(n_rows, hub.MLP_OUT)).astype(np.float32).astype(np.float64)
+    P, m, v = _dev(theta), torch.zeros(mlp.N_PARAM, device=DEV), torch.zeros(mlp.N_PARAM, device=DEV)
+    loss = torch.zeros(1, device=DEV)
+    ws = torch.full((hub.hub_mlp_workspace_bytes(n_rows) // 4,), float("nan"), device=DEV)
+    hub.hub_mlp_train_step(P, m, v, 1, 1e-3, _dev(X), _dev(Y), loss, ws)
+    L_ref, g_ref = mlp.loss_and_grad(theta, X, Y)
+    bound = (16 + np.sqrt(n_rows)) * 2.0 ** -23
+    assert abs(loss.item() - L_ref) <= bound * L_ref
+    g_gpu = m.cpu().numpy().astype(np.float64) / 0.1
+    assert np.max(np.abs(g_gpu - g_ref)) <= bound * np.max(np.abs(g_ref))
+
+
 @pytest.fixture(scope="module")
 def ring8():
     w = workloads()["ring8"]
