@@ -17,12 +17,12 @@
 #include <cstddef>
 #include <cstring>
 #include <new>
-#include <random>
 #include <string>
 #include <utility>
 #include <vector>
 
 #include "basis.h"
+#include "ground.h"
 #include "host_eig.h"
 #include "kernels.h"
 #include "members.h"
@@ -100,6 +100,9 @@ struct Work {
   double* partials_e = nullptr;   // partial sums of the elementwise kernels
   size_t partials_e_bytes = 0;
   double* scal = nullptr;         // device scalars [kMMax*2 + 16]
+  double* gs = nullptr;           // ground-state scalars and partial sums (grow only), pinned mirror of its scalars
+  double* h_gs = nullptr;
+  size_t gs_bytes = 0;
   double* rcoef = nullptr;        // device re-orthogonalisation coefficients [kMMax + 1][kMaxNV] complex
   hipStream_t stream = nullptr;   // extra lanes: their own stream (lane 0 runs on the caller's)
   void** h_ptrs = nullptr;        // pinned host mirror of slot_ptrs (uploaded without a wait)
@@ -211,6 +214,8 @@ void work_free(Work& W) {
   if (W.partials_e) (void)hipFree(W.partials_e);
   if (W.scal) (void)hipFree(W.scal);
   if (W.rcoef) (void)hipFree(W.rcoef);
+  if (W.gs) (void)hipFree(W.gs);
+  if (W.h_gs) (void)hipHostFree(W.h_gs);
   if (W.partials) (void)hipFree(W.partials);
   if (W.h_ctl) (void)hipHostFree(W.h_ctl);
   if (W.h_ptrs) (void)hipHostFree(W.h_ptrs);
@@ -2292,109 +2297,116 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
 }
 
 // ---------------------------------------------------------------------------
-// Ground state: restarted Lanczos with full reorthogonalisation (classical
-// Gram-Schmidt applied twice), complex double; Ritz pairs from the
-// tridiagonal by Jacobi rotations on the host.
+// Ground state: restarted Lanczos with full reorthogonalisation, complex
+// double; the lowest Ritz pair of the tridiagonal on the host.
 namespace {
 
+// Iterations enqueued between two looks at the residual (the host waits once
+// per batch; iterations past the one that converges are dropped).
+constexpr int kGsBatch = 8;
+
+// Device scalars and partial sums of a run with kmax Lanczos vectors, in the
+// lane's workspace, and the pinned host mirror of alpha, beta and coefficients.
 struct GSBufs {
-  std::vector<void*> V;  // device vectors
-  void** Vdev = nullptr;
-  double2* coef = nullptr;
-  double2* coef2 = nullptr;
+  char* V = nullptr;  // kmax + 1 vectors, one after another
+  double *alpha = nullptr, *beta = nullptr, *coef = nullptr, *dotp = nullptr, *normp = nullptr;
+  int64_t* first = nullptr;
+  double* host = nullptr;  // [2 kmax] alpha, beta; [kmax] coefficients
 };
 
+hub_status gs_buffers(Work& W, int kmax, GSBufs& G) {
+  const size_t k = static_cast<size_t>(kmax) + 2;
+  const size_t dbl = 3 * k + 2 * k * hub::kGsDotRows + 2 * hub::kGsNormRows;
+  if (dbl * sizeof(double) > W.gs_bytes) {
+    if (W.gs) HUB_HIP(hipFree(W.gs));
+    if (W.h_gs) HUB_HIP(hipHostFree(W.h_gs));
+    W.gs = W.h_gs = nullptr;
+    W.gs_bytes = 0;
+    HUB_HIP(hipMalloc(reinterpret_cast<void**>(&W.gs), dbl * sizeof(double)));
+    HUB_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.h_gs), 3 * k * sizeof(double), hipHostMallocDefault));
+    W.gs_bytes = dbl * sizeof(double);
+  }
+  G.V = static_cast<char*>(W.slots);
+  G.alpha = W.gs;
+  G.beta = G.alpha + k;
+  G.coef = G.beta + k;
+  G.dotp = G.coef + k;
+  G.normp = G.dotp + 2 * k * hub::kGsDotRows;
+  G.first = reinterpret_cast<int64_t*>(G.normp + hub::kGsNormRows);
+  G.host = W.h_gs;
+  return HUB_OK;
+}
+
+// Up to kmax Lanczos iterations from the normalised V[0]; lowest Ritz value
+// in ritz, its vector's coefficients in svec.
 hub_status gs_lanczos(hub_basis h, double A, hipStream_t st, GSBufs& G, int kmax, const void* deflate,
-                      double tol_res, std::vector<double>& ritz, std::vector<double>& svec, int& kused,
-                      double& resid) {
+                      double tol_res, double& ritz, std::vector<double>& svec, double& resid) {
   const int64_t dim = h->D.dim;
   std::vector<double> cf(static_cast<size_t>(2) * kMaxNV * kMaxClasses, 0.0);
   coef_for(h->B, A, cf.data());
-  std::vector<double> alpha, beta;
-  // vectors used for orthogonalisation: [deflate] + V[0..j]
-  std::vector<void*> basis;
-  if (deflate) basis.push_back(const_cast<void*>(deflate));
-  int j = 0;
+  const size_t vb = static_cast<size_t>(dim) * 16;
+  const int most = static_cast<int>(std::min<int64_t>(kmax, dim - (deflate ? 1 : 0)));
+  double* const al = G.host;
+  double* const be = G.host + kmax;
+  int m = 0;
   resid = INFINITY;
-  for (j = 0; j < kmax; ++j) {
-    basis.push_back(G.V[j]);
-    void* w = G.V[j + 1];
-    hub::ApplyLaunch L{};
-    L.db = &h->D;
-    L.prec = 0;
-    L.nv = 1;
-    L.rows = h->rows_c128;
-    L.mode = hub::kPlain;
-    L.coef = cf.data();
-    L.x = G.V[j];
-    L.y = w;
-    L.stream = st;
-    HUB_HIP(hub::launch_apply(L));
-    HUB_HIP(hipMemcpyAsync(G.Vdev, basis.data(), basis.size() * sizeof(void*), hipMemcpyHostToDevice, st));
-    HUB_HIP(hipStreamSynchronize(st));
-    double a_j = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-      const int nb = static_cast<int>(basis.size());
-      for (int k0 = 0; k0 < nb; k0 += 64) {
-        const int kk = std::min(64, nb - k0);
-        HUB_HIP(hub::launch_multidot(dim, reinterpret_cast<const double2* const*>(G.Vdev) + k0, kk,
-                                     static_cast<const double2*>(w), G.coef + k0, h->w.partials_e, st));
+  for (int j = 0; j < most;) {
+    const int end = std::min(most, j + kGsBatch);
+    for (int q = j; q < end; ++q) {
+      double2* w = reinterpret_cast<double2*>(G.V + (q + 1) * vb);
+      hub::ApplyLaunch L{};
+      L.db = &h->D;
+      L.prec = 0;
+      L.nv = 1;
+      L.rows = h->rows_c128;
+      L.mode = hub::kPlain;
+      L.coef = cf.data();
+      L.x = G.V + q * vb;
+      L.y = w;
+      L.stream = st;
+      HUB_HIP(hub::launch_apply(L));
+      // first the vectors H v_q overlaps with by the three-term recurrence,
+      // then all of them for the rounding errors
+      int rows = 0, nrows = 0;
+      for (int pass = 0; pass < 2; ++pass) {
+        const int k0 = pass == 0 ? std::max(0, q - 1) : 0;
+        const hub::GsBasis B{static_cast<const double2*>(deflate), reinterpret_cast<const double2*>(G.V + k0 * vb),
+                             dim, q + 1 - k0 + (deflate ? 1 : 0)};
+        HUB_HIP(hub::launch_gs_dot(B, w, G.dotp, &rows, st));
+        HUB_HIP(hub::launch_gs_subtract(B, w, G.dotp, rows, G.normp, &nrows, G.alpha + q, pass > 0, st));
       }
-      for (int k0 = 0; k0 < nb; k0 += 64) {
-        const int kk = std::min(64, nb - k0);
-        HUB_HIP(hub::launch_multiaxpy(dim, reinterpret_cast<const double2* const*>(G.Vdev) + k0, kk, G.coef + k0,
-                                      static_cast<double2*>(w), st));
-      }
-      double2 cj;
-      HUB_HIP(hipMemcpyAsync(&cj, G.coef + nb - 1, sizeof(double2), hipMemcpyDeviceToHost, st));
-      HUB_HIP(hipStreamSynchronize(st));
-      a_j += cj.x;
+      HUB_HIP(hub::launch_gs_scale(dim, w, G.normp, nrows, w, nullptr, G.beta + q, st));
     }
-    HUB_HIP(hub::launch_norm2(dim, static_cast<const double2*>(w), h->w.scal, h->w.partials_e, st));
-    double n2 = 0.0;
-    HUB_HIP(hipMemcpyAsync(&n2, h->w.scal, sizeof(double), hipMemcpyDeviceToHost, st));
+    HUB_HIP(hipMemcpyAsync(al + j, G.alpha + j, (end - j) * sizeof(double), hipMemcpyDeviceToHost, st));
+    HUB_HIP(hipMemcpyAsync(be + j, G.beta + j, (end - j) * sizeof(double), hipMemcpyDeviceToHost, st));
     HUB_HIP(hipStreamSynchronize(st));
-    const double b_j = std::sqrt(n2);
-    alpha.push_back(a_j);
-    beta.push_back(b_j);
-    // Ritz values of T_{j+1}
-    const int m = j + 1;
-    std::vector<double> T(static_cast<size_t>(m) * m, 0.0), vals, vecs;
-    for (int i = 0; i < m; ++i) {
-      T[static_cast<size_t>(i) * m + i] = alpha[i];
-      if (i + 1 < m) T[static_cast<size_t>(i) * m + i + 1] = T[static_cast<size_t>(i + 1) * m + i] = beta[i];
-    }
-    hub::sym_eig(m, T, vals, vecs);
-    resid = b_j * std::fabs(vecs[static_cast<size_t>(m - 1) * m + 0]);
-    ritz = vals;
-    svec.assign(m, 0.0);
-    for (int i = 0; i < m; ++i) svec[i] = vecs[static_cast<size_t>(i) * m + 0];
-    kused = m;
-    if (resid < tol_res || b_j < 1e-14 * h->B.norm_inf || m == dim - (deflate ? 1 : 0)) break;
-    HUB_HIP(hub::launch_scale(dim, static_cast<double2*>(w), h->w.scal, double2{0, 0}, st));
+    m = end;
+    bool closed = false;  // an invariant subspace: the vectors after it are void
+    for (int q = j; q < end && !closed; ++q)
+      if (be[q] < 1e-14 * h->B.norm_inf) {
+        m = q + 1;
+        closed = true;
+      }
+    ritz = hub::tridiag_lowest(m, al, be, svec);
+    resid = be[m - 1] * std::fabs(svec[m - 1]);
+    if (resid < tol_res || closed) break;
+    j = end;
   }
   return HUB_OK;
 }
 
-// x = sum_i s_i V[i] into `out`
-hub_status gs_ritz_vector(hub_basis h, hipStream_t st, GSBufs& G, const std::vector<double>& s, void* out) {
-  const int64_t dim = h->D.dim;
+// out = sum_i s_i V[i], normalised, also to out2 if given
+hub_status gs_ritz_vector(hub_basis h, hipStream_t st, GSBufs& G, int kmax, const std::vector<double>& s, void* out,
+                          void* out2) {
   const int m = static_cast<int>(s.size());
-  HUB_HIP(hipMemsetAsync(out, 0, dim * 16, st));
-  std::vector<double2> c(m);
-  for (int i = 0; i < m; ++i) c[i] = double2{-s[i], 0.0};  // multiaxpy subtracts
-  HUB_HIP(hipMemcpyAsync(G.coef, c.data(), m * sizeof(double2), hipMemcpyHostToDevice, st));
-  HUB_HIP(hipMemcpyAsync(G.Vdev, G.V.data(), m * sizeof(void*), hipMemcpyHostToDevice, st));
-  HUB_HIP(hipStreamSynchronize(st));
-  for (int k0 = 0; k0 < m; k0 += 64) {
-    const int kk = std::min(64, m - k0);
-    HUB_HIP(hub::launch_multiaxpy(dim, reinterpret_cast<const double2* const*>(G.Vdev) + k0, kk, G.coef + k0,
-                                  static_cast<double2*>(out), st));
-  }
-  // normalise
-  HUB_HIP(hub::launch_norm2(dim, static_cast<const double2*>(out), h->w.scal, h->w.partials_e, st));
-  HUB_HIP(hub::launch_scale(dim, static_cast<double2*>(out), h->w.scal, double2{0, 0}, st));
-  HUB_HIP(hipStreamSynchronize(st));
+  double* const hc = G.host + 2 * kmax;
+  std::copy(s.begin(), s.end(), hc);
+  HUB_HIP(hipMemcpyAsync(G.coef, hc, m * sizeof(double), hipMemcpyHostToDevice, st));
+  int nrows = 0;
+  HUB_HIP(hub::launch_gs_combine(reinterpret_cast<const double2*>(G.V), h->D.dim, m, G.coef,
+                                 static_cast<double2*>(out), G.normp, &nrows, st));
+  HUB_HIP(hub::launch_gs_scale(h->D.dim, static_cast<const double2*>(out), G.normp, nrows,
+                               static_cast<double2*>(out), static_cast<double2*>(out2), nullptr, st));
   return HUB_OK;
 }
 
@@ -2416,91 +2428,53 @@ hub_status hub_ground_state(hub_basis h, double A, const hub_krylov_opts* opts, 
   s = ensure_workspace(h, static_cast<size_t>(dim) * 16, kmax + 1, 0);
   if (s != HUB_OK) return s;
   GSBufs G;
-  for (int k = 0; k <= kmax; ++k) G.V.push_back(static_cast<char*>(h->w.slots) + static_cast<size_t>(k) * dim * 16);
-  void* extra = nullptr;
-  HUB_HIP(hipMalloc(&extra, (kmax + 2) * (sizeof(void*) + 2 * sizeof(double2))));
-  struct Fr {
-    void* p;
-    ~Fr() { (void)hipFree(p); }
-  } fr{extra};
-  G.Vdev = static_cast<void**>(extra);
-  G.coef = reinterpret_cast<double2*>(static_cast<char*>(extra) + (kmax + 2) * sizeof(void*));
-  G.coef2 = G.coef + (kmax + 2);
-
-  // seeded random start (host), normalised on the device
-  auto random_start = [&](void* dst, uint64_t seed) -> hub_status {
-    std::mt19937_64 rng(seed);
-    std::normal_distribution<double> nd(0.0, 1.0);
-    std::vector<double2> x(static_cast<size_t>(dim));
-    for (auto& e : x) e = double2{nd(rng), nd(rng)};
-    HUB_HIP(hipMemcpy(dst, x.data(), x.size() * sizeof(double2), hipMemcpyHostToDevice));
-    HUB_HIP(hub::launch_norm2(dim, static_cast<const double2*>(dst), h->w.scal, h->w.partials_e, st));
-    HUB_HIP(hub::launch_scale(dim, static_cast<double2*>(dst), h->w.scal, double2{0, 0}, st));
-    return HUB_OK;
-  };
-  const double tol_res = tol * h->B.norm_inf;
-  s = random_start(G.V[0], 0x13498ULL);
+  s = gs_buffers(h->w, kmax, G);
   if (s != HUB_OK) return s;
-  std::vector<double> ritz, svec;
-  int kused = 0;
+  double2* const V0 = reinterpret_cast<double2*>(G.V);
+  double2* const psi = static_cast<double2*>(v_out);
+
+  const double tol_res = tol * h->B.norm_inf;
+  int nrows = 0;
+  HUB_HIP(hub::launch_gs_start(dim, 0x13498ULL, V0, G.normp, &nrows, st));
+  HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
+  std::vector<double> svec;
   double resid = INFINITY, e0 = 0.0;
   bool conv = false;
-  for (int restart = 0; restart < 200; ++restart) {
-    s = gs_lanczos(h, A, st, G, kmax, nullptr, tol_res, ritz, svec, kused, resid);
+  for (int restart = 0; restart < 200 && !conv; ++restart) {
+    s = gs_lanczos(h, A, st, G, kmax, nullptr, tol_res, e0, svec, resid);
     if (s != HUB_OK) return s;
-    e0 = ritz[0];
-    s = gs_ritz_vector(h, st, G, svec, v_out);
+    s = gs_ritz_vector(h, st, G, kmax, svec, psi, V0);
     if (s != HUB_OK) return s;
-    if (resid < tol_res) {
-      conv = true;
-      break;
-    }
-    HUB_HIP(hipMemcpyAsync(G.V[0], v_out, dim * 16, hipMemcpyDeviceToDevice, st));
+    conv = resid < tol_res;
   }
-  if (!conv) return fail(HUB_E_NOT_CONVERGED, "ground-state Lanczos did not reach the tolerance");
+  if (!conv) {
+    HUB_HIP(hipStreamSynchronize(st));
+    return fail(HUB_E_NOT_CONVERGED, "ground-state Lanczos did not reach the tolerance");
+  }
   // phase: largest-modulus component (lowest index within 1e-12 of the max) real positive
-  HUB_HIP(hub::launch_absmax(dim, static_cast<const double2*>(v_out), h->w.scal, h->w.partials_e, st));
-  double mx2 = 0.0;
-  HUB_HIP(hipMemcpyAsync(&mx2, h->w.scal, sizeof(double), hipMemcpyDeviceToHost, st));
-  HUB_HIP(hipStreamSynchronize(st));
-  const double th = mx2 * (1.0 - 1e-12) * (1.0 - 1e-12);
-  HUB_HIP(hipMemcpy(h->w.scal + 1, &th, sizeof(double), hipMemcpyHostToDevice));
-  HUB_HIP(hub::launch_first_above(dim, static_cast<const double2*>(v_out), h->w.scal + 1,
-                                  reinterpret_cast<int64_t*>(h->w.scal + 2), reinterpret_cast<int64_t*>(h->w.partials_e),
-                                  st));
-  int64_t kmaxidx = 0;
-  HUB_HIP(hipMemcpyAsync(&kmaxidx, h->w.scal + 2, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  HUB_HIP(hipStreamSynchronize(st));
-  double2 comp;
-  HUB_HIP(hipMemcpy(&comp, static_cast<double2*>(v_out) + kmaxidx, sizeof(double2), hipMemcpyDeviceToHost));
-  const double mag = std::hypot(comp.x, comp.y);
-  HUB_HIP(hub::launch_scale(dim, static_cast<double2*>(v_out), nullptr, double2{comp.x / mag, -comp.y / mag}, st));
+  HUB_HIP(hub::launch_gs_phase(dim, psi, G.normp, G.first, st));
   *E0 = e0;
   // gap: lowest Ritz value of H restricted to the complement of the ground state
   double g = INFINITY;
   if (dim > 1) {
-    s = random_start(G.V[0], 0x5eedULL);
-    if (s != HUB_OK) return s;
+    HUB_HIP(hub::launch_gs_start(dim, 0x5eedULL, V0, G.normp, &nrows, st));
+    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
     // remove the ground-state component of the start vector
-    HUB_HIP(hipMemcpyAsync(G.Vdev, &v_out, sizeof(void*), hipMemcpyHostToDevice, st));
-    HUB_HIP(hipStreamSynchronize(st));
-    HUB_HIP(hub::launch_multidot(dim, reinterpret_cast<const double2* const*>(G.Vdev), 1,
-                                 static_cast<const double2*>(G.V[0]), G.coef, h->w.partials_e, st));
-    HUB_HIP(hub::launch_multiaxpy(dim, reinterpret_cast<const double2* const*>(G.Vdev), 1, G.coef,
-                                  static_cast<double2*>(G.V[0]), st));
-    HUB_HIP(hub::launch_norm2(dim, static_cast<const double2*>(G.V[0]), h->w.scal, h->w.partials_e, st));
-    HUB_HIP(hub::launch_scale(dim, static_cast<double2*>(G.V[0]), h->w.scal, double2{0, 0}, st));
-    double r1 = INFINITY;
+    const hub::GsBasis B{nullptr, psi, dim, 1};
+    int rows = 0;
+    HUB_HIP(hub::launch_gs_dot(B, V0, G.dotp, &rows, st));
+    HUB_HIP(hub::launch_gs_subtract(B, V0, G.dotp, rows, G.normp, &nrows, G.alpha, false, st));
+    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
+    double r1 = INFINITY, e1 = 0.0;
     for (int restart = 0; restart < 20; ++restart) {
-      s = gs_lanczos(h, A, st, G, kmax, v_out, 1e-6 * h->B.norm_inf, ritz, svec, kused, r1);
+      s = gs_lanczos(h, A, st, G, kmax, v_out, 1e-6 * h->B.norm_inf, e1, svec, r1);
       if (s != HUB_OK) return s;
       if (r1 < 1e-6 * h->B.norm_inf) break;
-      void* tmp = G.V[kmax];  // Ritz vector into the spare slot, then restart from it
-      s = gs_ritz_vector(h, st, G, svec, tmp);
+      // restart from the Ritz vector, formed in the spare slot
+      s = gs_ritz_vector(h, st, G, kmax, svec, G.V + static_cast<size_t>(kmax) * dim * 16, V0);
       if (s != HUB_OK) return s;
-      HUB_HIP(hipMemcpyAsync(G.V[0], tmp, dim * 16, hipMemcpyDeviceToDevice, st));
     }
-    g = ritz[0] - e0;
+    g = e1 - e0;
   }
   HUB_HIP(hipStreamSynchronize(st));
   if (gap) *gap = g;

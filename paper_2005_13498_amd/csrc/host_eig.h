@@ -1,14 +1,13 @@
-// Small dense symmetric eigenproblems on the host (Lanczos Ritz values).
+// Lowest eigenpair of a small symmetric tridiagonal matrix (host, FP64).
 #pragma once
 
 #include <vector>
 
 namespace hub {
 
-// Eigenvalues (ascending) and orthonormal eigenvectors of the real symmetric
-// n x n matrix A (row-major), by cyclic Jacobi rotations: each rotation
-// zeroes one off-diagonal pair; sweeps repeat until the off-diagonal mass
-// is below 1e-30 of the total.  vecs[i*n + k] = component i of vector k.
-void sym_eig(int n, std::vector<double> A, std::vector<double>& vals, std::vector<double>& vecs);
+// T has the diagonal a[0..m-1] and the off-diagonal b[0..m-2], all b nonzero
+// (an unreduced Lanczos matrix, whose eigenvalues are simple).  Returns the
+// lowest eigenvalue and its normalised eigenvector in s[0..m-1].
+double tridiag_lowest(int m, const double* a, const double* b, std::vector<double>& s);
 
 }  // namespace hub

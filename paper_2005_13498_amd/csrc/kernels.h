@@ -225,7 +225,7 @@ hipError_t launch_step_log(int nv, const VecState* st, StepCtl* ctl, void* log, 
 
 // One-workgroup reductions of partial sums.
 hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, int nq, VecState* st, hipStream_t s);
-hipError_t launch_finalize(const double* partials, int nrows, int ncols, double* out, int op, hipStream_t s);
+hipError_t launch_finalize(const double* partials, int nrows, int ncols, double* out, hipStream_t s);
 
 // Site-resolved double occupation sum_k n_{i up} n_{i down} |x_k|^2 of one vector.
 hipError_t launch_site_docc(int prec, const DevBasis& db, const void* x, double* out, double* partials,
@@ -244,16 +244,5 @@ hipError_t launch_cop(int prec, int64_t n_t, int dim_dn_t, int dim_dn_s, int64_t
 // out[2k], out[2k+1] = <x_k | y_k> for nvec pairs (device output, fixed order).
 hipError_t launch_dots(int prec, int64_t n, int nvec, const void* x, const void* y, double* out, double* partials,
                        hipStream_t s);
-
-// BLAS-1 helpers for the ground-state Lanczos (complex double, one vector).
-hipError_t launch_multidot(int64_t n, const double2* const* vecs, int k, const double2* w, double2* out,
-                           double* partials, hipStream_t s);
-hipError_t launch_multiaxpy(int64_t n, const double2* const* vecs, int k, const double2* coef, double2* w,
-                            hipStream_t s);
-hipError_t launch_norm2(int64_t n, const double2* w, double* out, double* partials, hipStream_t s);
-hipError_t launch_scale(int64_t n, double2* w, const double* inv_from, double2 factor, hipStream_t s);
-hipError_t launch_absmax(int64_t n, const double2* w, double* out, double* partials, hipStream_t s);
-hipError_t launch_first_above(int64_t n, const double2* w, const double* thresh, int64_t* out, int64_t* partials,
-                              hipStream_t s);
 
 }  // namespace hub

@@ -188,31 +188,12 @@ __global__ void k_step_log(const VecState* st, StepCtl* ctl, CombineLog* log, do
   record_step<NV>(st, ctl, log, obs_log, nobs, 0);
 }
 
-// Column sums (op 0) or maxima (op 1) of a [nrows][ncols] partial array,
-// one workgroup per column, fixed order.
-__global__ __launch_bounds__(kBlock) void k_finalize(const double* partials, int nrows, int ncols, double* out,
-                                                     int op) {
+// Column sums of a [nrows][ncols] partial array, one workgroup per column,
+// fixed order.
+__global__ __launch_bounds__(kBlock) void k_finalize(const double* partials, int nrows, int ncols, double* out) {
   __shared__ double red[kWaves];
-  const int t = blockIdx.x;
-  double s = 0.0;  // the maxima are of non-negative partials
-  for (int b = threadIdx.x; b < nrows; b += blockDim.x) {
-    const double x = partials[(size_t)b * ncols + t];
-    s = op ? fmax(s, x) : s + x;
-  }
-  if (op) {
-    s = wave_max(s);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) red[w] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double m = 0.0;
-      for (int k = 0; k < kWaves; ++k) m = fmax(m, red[k]);
-      out[t] = m;
-    }
-  } else {
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) out[t] = s;
-  }
+  const double s = reduce_column(partials, nrows, ncols, blockIdx.x, red);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // Observables of an apply in kObsOnly mode: finalize its partials into st.
@@ -476,129 +457,6 @@ __global__ __launch_bounds__(kBlock) void k_spectral(int n_s, const double2* __r
   out[(size_t)m * n_nu + f] = n_s > 1 ? acc / M_PI : 0.0;
 }
 
-// ------------------------------- BLAS-1 ------------------------------------
-// <v_k, w> partials for k < kv: workgroup column blockIdx.y takes the chunk
-// of (up to) 8 vectors k0 = 8 blockIdx.y.., each in registers; partials
-// [gridDim.x][2 kv].
-__global__ __launch_bounds__(kBlock) void k_multidot(int64_t n, const double2* const* vecs, int kv,
-                                                     const double2* w, double* partials) {
-  __shared__ double red[kWaves * 16];
-  const int k0 = blockIdx.y * 8;
-  const int K = min(8, kv - k0);
-  const double2* vp[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) vp[k] = k < K ? vecs[k0 + k] : nullptr;
-  double acc[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-    const double2 b = w[i];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (k < K) {
-        const double2 a = vp[k][i];
-        acc[2 * k] += a.x * b.x + a.y * b.y;  // conj(a) * b
-        acc[2 * k + 1] += a.x * b.y - a.y * b.x;
-      }
-    }
-  }
-  // workgroup sums (fixed order), 2 K values for this chunk
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const double t = wave_sum(acc[q]);
-    if (lane == 0) red[wv * 16 + q] = t;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2 * K) {
-    double t = 0.0;
-    for (int k = 0; k < kWaves; ++k) t += red[k * 16 + threadIdx.x];
-    partials[(size_t)blockIdx.x * 2 * kv + 2 * k0 + threadIdx.x] = t;
-  }
-}
-
-__global__ void k_multiaxpy(int64_t n, const double2* const* vecs, int kv, const double2* coef, double2* w) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double2 t = w[i];
-    for (int k = 0; k < kv; ++k) {
-      const double2 a = vecs[k][i];
-      const double2 c = coef[k];
-      t.x -= c.x * a.x - c.y * a.y;
-      t.y -= c.x * a.y + c.y * a.x;
-    }
-    w[i] = t;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_norm2(int64_t n, const double2* w, double* partials) {
-  __shared__ double red[kWaves];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-    const double2 t = w[i];
-    s += t.x * t.x + t.y * t.y;
-  }
-  block_partials<1>(&s, 1, red, partials + blockIdx.x);
-}
-
-__global__ void k_scale(int64_t n, double2* w, const double* inv_from, double2 f) {
-  double2 c = f;
-  if (inv_from) {
-    const double nn = sqrt(*inv_from);
-    c = double2{nn > 0.0 ? 1.0 / nn : 0.0, 0.0};
-  }
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double2 t = w[i];
-    w[i] = double2{c.x * t.x - c.y * t.y, c.x * t.y + c.y * t.x};
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_absmax(int64_t n, const double2* w, double* partials) {
-  __shared__ double red[kWaves];
-  double m = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-    const double2 t = w[i];
-    m = fmax(m, t.x * t.x + t.y * t.y);
-  }
-  m = wave_max(m);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) red[wv] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double r = 0.0;
-    for (int k = 0; k < kWaves; ++k) r = fmax(r, red[k]);
-    partials[blockIdx.x] = r;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_first_above(int64_t n, const double2* w, const double* thresh,
-                                                        int64_t* partials) {
-  __shared__ int64_t red[kBlock];
-  const double th = *thresh;
-  int64_t best = n;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-    const double2 t = w[i];
-    if (t.x * t.x + t.y * t.y >= th) {
-      best = i;
-      break;
-    }
-  }
-  red[threadIdx.x] = best;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t r = n;
-    for (int k = 0; k < kBlock; ++k) r = red[k] < r ? red[k] : r;
-    partials[blockIdx.x] = r;
-  }
-}
-
-__global__ void k_first_final(const int64_t* partials, int nrows, int64_t n, int64_t* out) {
-  if (threadIdx.x == 0) {
-    int64_t r = n;
-    for (int b = 0; b < nrows; ++b) r = partials[b] < r ? partials[b] : r;
-    *out = r;
-  }
-}
-
 }  // namespace dev
 using namespace dev;
 
@@ -858,9 +716,9 @@ hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, int nq
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const double* partials, int nrows, int ncols, double* out, int op, hipStream_t s) {
+hipError_t launch_finalize(const double* partials, int nrows, int ncols, double* out, hipStream_t s) {
   if (ncols < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_finalize, dim3(ncols), dim3(kBlock), 0, s, partials, nrows, ncols, out, op);
+  hipLaunchKernelGGL(k_finalize, dim3(ncols), dim3(kBlock), 0, s, partials, nrows, ncols, out);
   return hipGetLastError();
 }
 
@@ -887,7 +745,7 @@ hipError_t launch_site_docc(int prec, const DevBasis& db, const void* x, double*
                        db.up_bits, db.dn_bits, static_cast<const float2*>(x), partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_finalize(partials, grid, db.n_sites, out, 0, s);
+  return launch_finalize(partials, grid, db.n_sites, out, s);
 }
 
 hipError_t launch_cop(int prec, int64_t n_t, int dim_dn_t, int dim_dn_s, int64_t n_s, int nvec, bool down,
@@ -913,49 +771,7 @@ hipError_t launch_dots(int prec, int64_t n, int nvec, const void* x, const void*
                        static_cast<const float2*>(y), partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_finalize(partials, grid, 2 * nvec, out, 0, s);
-}
-
-hipError_t launch_multidot(int64_t n, const double2* const* vecs, int k, const double2* w, double2* out,
-                           double* partials, hipStream_t s) {
-  if (k > 64) return hipErrorInvalidValue;
-  const int grid = elem_grid(n);
-  hipLaunchKernelGGL(k_multidot, dim3(grid, (k + 7) / 8), dim3(kBlock), 0, s, n, vecs, k, w, partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finalize(partials, grid, 2 * k, reinterpret_cast<double*>(out), 0, s);
-}
-hipError_t launch_multiaxpy(int64_t n, const double2* const* vecs, int k, const double2* coef, double2* w,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_multiaxpy, dim3(elem_grid(n)), dim3(kBlock), 0, s, n, vecs, k, coef, w);
-  return hipGetLastError();
-}
-hipError_t launch_norm2(int64_t n, const double2* w, double* out, double* partials, hipStream_t s) {
-  const int grid = elem_grid(n);
-  hipLaunchKernelGGL(k_norm2, dim3(grid), dim3(kBlock), 0, s, n, w, partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finalize(partials, grid, 1, out, 0, s);
-}
-hipError_t launch_scale(int64_t n, double2* w, const double* inv_from, double2 factor, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale, dim3(elem_grid(n)), dim3(kBlock), 0, s, n, w, inv_from, factor);
-  return hipGetLastError();
-}
-hipError_t launch_absmax(int64_t n, const double2* w, double* out, double* partials, hipStream_t s) {
-  const int grid = elem_grid(n);
-  hipLaunchKernelGGL(k_absmax, dim3(grid), dim3(kBlock), 0, s, n, w, partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_finalize(partials, grid, 1, out, 1, s);
-}
-hipError_t launch_first_above(int64_t n, const double2* w, const double* thresh, int64_t* out, int64_t* partials,
-                              hipStream_t s) {
-  const int grid = elem_grid(n);
-  hipLaunchKernelGGL(k_first_above, dim3(grid), dim3(kBlock), 0, s, n, w, thresh, partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_first_final, dim3(1), dim3(64), 0, s, partials, grid, n, out);
-  return hipGetLastError();
+  return launch_finalize(partials, grid, 2 * nvec, out, s);
 }
 
 }  // namespace hub
