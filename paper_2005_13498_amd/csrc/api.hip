@@ -114,12 +114,6 @@ struct Work {
 };
 
 constexpr int kMaxLanes = 4;
-// Blocks on the two-pass block kernels take fused Lanczos iterations up to
-// this many states (measured, member-steps/s fused vs with an update kernel:
-// 8-site blocks of 8 122 k vs 114 k, 10-site Green's-function members per
-// sector 67.6 k vs 66.2 k; 12-site c64 blocks of 4 8,569 vs 9,135 and
-// 14-site 454 vs 485 lose).
-constexpr int64_t kBlockFuseMaxDim = 65536;
 // Extra lanes are used only while all lanes' Krylov workspaces together stay
 // below this many bytes of device memory.
 constexpr size_t kLaneWorkBudget = size_t(48) << 30;
@@ -604,19 +598,17 @@ hub_status run_group(hub_basis h, hub_prec prec, int nv, void* user, int n_steps
                            : 2 * static_cast<size_t>(hub::colpass_grid(h->D, pi));
     if (two_obs) A.row_obs = W.partials + cg2;
     // From the second iteration on, the two-pass row pass (single vectors, or
-    // blocks on the block kernels in small sectors) also finishes the previous
-    // update (u_j = w_{j-1} - alpha s u_{j-1}) and the column pass takes the
-    // decision, so no separate update kernel runs in between (at j = 1 the row
-    // pass also finalizes the first apply's observables).  Fused blocks pay a
-    // full column pass in a step's last iteration (the decision comes one
-    // kernel later) and per-workgroup reductions over per-row and per-column
-    // partials; they gain only where the saved update launch dominates.
-    const bool blk_fuse = blk && dim <= kBlockFuseMaxDim;
-    const bool fusable = !o.reorth && (blk_fuse || hub::apply_two_pass(h->D, pi, nv, hub::kLanczos, false));
+    // blocks on the block kernels) also finishes the previous update (u_j =
+    // w_{j-1} - alpha s u_{j-1}) and the column pass takes the decision, so no
+    // separate update kernel runs in between (at j = 1 the row pass also
+    // finalizes the first apply's observables).  Eight vectors with an update
+    // kernel vs fused: 12 sites c64 9.50 vs 8.89 ms for 10 steps, 14 sites
+    // 40.8 vs 39.8 ms for 2.
+    const bool fusable = !o.reorth && (blk || hub::apply_two_pass(h->D, pi, nv, hub::kLanczos, false));
     A.fuse = fusable && jj >= 1;
     if (A.fuse) {
       const bool after_obs = jj == 1 && want_obs && sub == 0 &&
-                             (blk_fuse || hub::apply_two_pass(h->D, pi, nv, hub::kLanczos, true));
+                             (blk || hub::apply_two_pass(h->D, pi, nv, hub::kLanczos, true));
       A.alpha_partials = W.partials;
       A.alpha_nblk = blk ? h->D.dim_dn : hub::colpass_grid(h->D, pi);
       A.alpha_stride = after_obs ? hub::apply_nq_two_pass(true) : 1;
@@ -643,7 +635,7 @@ hub_status run_group(hub_basis h, hub_prec prec, int nv, void* user, int n_steps
   auto finish_sub = [&](int n, int sub) -> hub_status {
     const bool last = sub == S - 1;
     void* copy_to = (hook && hook->traj && nv == 1 && last) ? hook->traj + (n + 1) * hook->traj_stride : nullptr;
-    HUB_HIP(hub::launch_combine(pi, nv, dim, W.slot_ptrs, W.st, W.ctl, W.partials_e, n * S + sub + 1,
+    HUB_HIP(hub::launch_combine(pi, nv, dim, slot0, W.slots, W.st, W.ctl, W.partials_e, n * S + sub + 1,
                                 dlog_c + (static_cast<size_t>(n) * S + sub) * nv,
                                 (want_obs && sub == 0) ? dobs + static_cast<size_t>(n) * nv * kObsQ : nullptr,
                                 kObsQ, stream, copy_to));

@@ -136,9 +136,11 @@ static void build_spin(const Lattice& lat, int n_el, const std::vector<HopClass>
     T.tabg.assign(static_cast<size_t>(T.gslots) * T.dim, static_cast<uint16_t>(T.dim));
     for (int r = 0; r < T.dim; ++r)
       for (int c = 0; c < nc; ++c)
-        for (int s = T.slot_begin[c]; s < T.slot_begin[c + 1]; ++s)
+        for (int s = T.slot_begin[c]; s < T.slot_begin[c + 1]; ++s) {
+          const int v = T.tabc[static_cast<size_t>(r) * T.maxs_pad + s];
           T.tabg[static_cast<size_t>(r) * T.gslots + gbeg[c] + (s - T.slot_begin[c])] =
-              T.tabc[static_cast<size_t>(r) * T.maxs_pad + s];
+              static_cast<uint16_t>(v > T.dim ? (v - T.dim - 1) | 0x8000 : v);
+        }
   }
 }
 

@@ -18,8 +18,8 @@ namespace dev {
 // The column pass either stores y (plain product) or finishes a Lanczos
 // iteration: y = s_j (H u_j) - beta_{j-1} s_{j-1} u_{j-1}, alpha_j partials.
 // Each pass stages its tile row (column) of all NV vectors once in LDS,
-// followed by a zero element; a hop's table entry is src, src + dim + 1 for a
-// negative fermion sign, or dim (the zero element) for padding.  The NV
+// followed by a zero element; a hop's table entry is its source with the
+// fermion sign in bit 15, or dim (the zero element) for padding.  The NV
 // values of a tile element are L = NV / VPL 16-byte words (VPL = 2 complex64
 // or 1 complex128 value per word), and L consecutive lanes own one element,
 // a word each: global loads and stores of an element are contiguous across
@@ -102,10 +102,13 @@ __device__ __forceinline__ void word_sums(const double (&vals)[NQ], double* lds,
   }
 }
 
+// Words of a thread's tile row (column) loaded before the kernel's reduction.
+constexpr int kRowAhead = 2, kColAhead = 2;
+
 // One group of four slots: the signed sum of the staged words they index
 // (word k of each source element of L words), from the table word pair w.
 template <typename R, int L>
-__device__ __forceinline__ void group_sum(uint2 w, const uint4* xs, uint32_t dim, int k,
+__device__ __forceinline__ void group_sum(uint2 w, const uint4* xs, int k,
                                           typename CT<R>::T (&sum)[16 / sizeof(typename CT<R>::T)]) {
   using V = typename CT<R>::T;
   constexpr int VPL = 16 / sizeof(V);
@@ -113,13 +116,9 @@ __device__ __forceinline__ void group_sum(uint2 w, const uint4* xs, uint32_t dim
   for (int i = 0; i < VPL; ++i) sum[i] = V{0, 0};
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const uint32_t w2 = s < 2 ? w.x : w.y;
-    const uint32_t idx = (s & 1) ? (w2 >> 16) : (w2 & 0xFFFFu);
-    const bool neg = idx > dim;
-    const uint32_t src = neg ? idx - dim - 1u : idx;
-    const R sg = neg ? R(-1) : R(1);
+    const R sg = slot_sign<R>(w, s);
     V t[VPL];
-    from_word<V>(xs[static_cast<size_t>(src) * L + k], t);
+    from_word<V>(xs[slot_src(w, s) * L + k], t);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
       sum[i].x = fma(sg, t[i].x, sum[i].x);
@@ -183,27 +182,73 @@ __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
   static_assert(L >= 1 && NV % VPL == 0 && BLK % L == 0, "whole words per element");
   constexpr bool kL = MODE == M_LANCZOS || MODE == M_LANCZOS_OBS;
   constexpr bool kO = MODE == M_LANCZOS_OBS;
-  __shared__ double red[W * kObsQ * NV + W];
+  constexpr int kOC = kObsQ * NV;  // observables partials per row
+  __shared__ double red[W * kOC];
   __shared__ double sh_beta[NV];
   static_assert(!FUSE || MODE == M_LANCZOS, "fused row pass: Lanczos iterations j >= 1");
+  static_assert(kOC <= 64, "the observables of a row are reduced in one pass");
   const int tid = threadIdx.x;
   const int k = tid % L, e0 = tid / L;
+  const bool extra = kL && blockIdx.x == gridDim.x - 1;
+  if (kL) {
+    if (p.ctl->all_done) return;
+    if (!extra && p.j >= p.m_max && !FUSE) return;  // only the decision was needed
+  }
+  const int dd = p.dim_dn;
+  const int nw = dd * L;  // words of a tile row
+  const int a = extra ? 0 : xcd_remap(blockIdx.x, kL ? gridDim.x - 1 : gridDim.x);
+  const size_t roww = static_cast<size_t>(a) * nw;  // first word of the row
+  uint4* const w4 = static_cast<uint4*>(const_cast<void*>(p.x)) + roww;
+  const uint4* const u4 = FUSE ? static_cast<const uint4*>(p.xprev) + roww : nullptr;
+
+  // The row's first words, the first element's table entries and the lane's
+  // coefficients are loaded ahead of the reductions, so that one memory
+  // latency covers them all.
+  uint4 pw[kRowAhead], pu[FUSE ? kRowAhead : 1];
+  uint2 ev[kG];
+  uint32_t db = 0;
+  double eb = 0.0;
+  const uint2* tab2 = reinterpret_cast<const uint2*>(p.tab);
+  auto fetch = [&](int b) {
+#pragma unroll
+    for (int g = 0; g < kG; ++g) ev[g] = tab2[static_cast<size_t>(b) * kG + g];
+    db = p.dn_bits[b];
+    if (p.eps_dn) eb = p.eps_dn[b];
+  };
+  V cf[kG][VPL];
+  double2 ocf[kO ? kG : 1][VPL];
+  if (!extra) {
+#pragma unroll
+    for (int i = 0; i < kRowAhead; ++i) {
+      const int t = tid + i * BLK;
+      pw[i] = t < nw ? w4[t] : make_uint4(0u, 0u, 0u, 0u);
+      if constexpr (FUSE) pu[i] = t < nw ? u4[t] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (e0 < dd) fetch(e0);
+    // coefficients of this lane's vectors v = k VPL + i
+#pragma unroll
+    for (int g = 0; g < kG; ++g)
+#pragma unroll
+      for (int i = 0; i < VPL; ++i) {
+        const int v = k * VPL + i, c = p.grp_class[g];
+        cf[g][i] = V{static_cast<R>(p.coef[2 * (v * p.nc + c)]), static_cast<R>(p.coef[2 * (v * p.nc + c) + 1])};
+        if constexpr (kO) ocf[g][i] = make_double2(p.coef_obs[2 * (v * p.nc + c)], p.coef_obs[2 * (v * p.nc + c) + 1]);
+      }
+  }
   R cu[VPL];  // FUSE: alpha_{j-1} s_{j-1} of this lane's vectors
   if (FUSE) {
-    if (p.ctl->all_done) return;
-    for (int t = 0; t < NV; ++t) {
-      const double s = reduce_column<W>(p.alpha_partials, p.alpha_nblk, p.alpha_stride * NV, t, red);
-      if (tid == 0) sh_beta[t] = s;  // alpha_{j-1} of vector t
-    }
-    __syncthreads();
-    if (blockIdx.x == gridDim.x - 1) {
+    cols_total<NV, W>(cols_partial<NV, BLK>(p.alpha_partials, p.alpha_nblk, p.alpha_stride * NV), red, sh_beta);
+    if (extra) {  // sh_beta[v] = alpha_{j-1} of vector v
       if (tid < NV && p.st[tid].status == 0) p.st[tid].alpha[p.j - 1] = sh_beta[tid];
-      if (p.obs_row)  // [diag, docc, n2, down-hop part] of the rows, up-hop part in the columns' second column
-        for (int t = 0; t < kObsQ * NV; ++t) {
-          double s = reduce_column<W>(p.obs_row, p.dim_up, kObsQ * NV, t, red);
-          if (t / NV == kObsQ - 1) s += reduce_column<W>(p.alpha_partials, p.alpha_nblk, p.alpha_stride * NV, NV + t % NV, red);
-          if (tid == 0) p.st[t % NV].obs[t / NV] = s;
+      if (p.obs_row) {  // [diag, docc, n2, down-hop part] of the rows, up-hop part in the columns' second column
+        __shared__ double so[kOC], su[NV];
+        cols_total<kOC, W>(cols_partial<kOC, BLK>(p.obs_row, p.dim_up, kOC), red, so);
+        cols_total<NV, W>(cols_partial<NV, BLK>(p.alpha_partials + NV, p.alpha_nblk, p.alpha_stride * NV), red, su);
+        if (tid < kOC) {
+          const int q = tid / NV, v = tid % NV;
+          p.st[v].obs[q] = so[tid] + (q == kObsQ - 1 ? su[v] : 0.0);
         }
+      }
       __shared__ int sh_end;  // every running vector's estimate for m = j is below tol
       if (tid == 0) sh_end = 1;
       __syncthreads();
@@ -232,84 +277,85 @@ __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
       const int v = k * VPL + i;
       cu[i] = static_cast<R>(sh_beta[v] * p.st[v].scale[p.j - 1]);
     }
-  } else if (kL) {
-    if (p.ctl->all_done) return;
-    if (blockIdx.x == gridDim.x - 1) {
-      for (int t = 0; t < NV; ++t) {
-        const double s = reduce_column<W>(p.prev_partials, p.prev_nblk, NV, t, red);
-        if (tid == 0) sh_beta[t] = sqrt(s);
-      }
-      __syncthreads();
-      krylov_decide<NV, W>(p.j, sh_beta, p.st, p.ctl, p.m_max, p.tol, p.norm_inf);
-      return;
-    }
-    if (p.j >= p.m_max) return;  // only the decision was needed
+  } else if (extra) {
+    cols_total<NV, W>(cols_partial<NV, BLK>(p.prev_partials, p.prev_nblk, NV), red, sh_beta);
+    if (tid < NV) sh_beta[tid] = sqrt(sh_beta[tid]);
+    __syncthreads();
+    krylov_decide<NV, W>(p.j, sh_beta, p.st, p.ctl, p.m_max, p.tol, p.norm_inf);
+    return;
   }
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint4* xs = reinterpret_cast<uint4*>(smem_raw);
-  const int a = xcd_remap(blockIdx.x, kL ? gridDim.x - 1 : gridDim.x);
-  const int dd = p.dim_dn;
-  const size_t roww = static_cast<size_t>(a) * dd * L;  // first word of the row
-  if (FUSE) {
-    // u_j = w_{j-1} - alpha s u_{j-1} of the row, in place and staged; |u_j|^2
-    // per vector (a thread's words all hold the vectors of word index k)
-    uint4* w4 = static_cast<uint4*>(const_cast<void*>(p.x)) + roww;
-    const uint4* u4 = static_cast<const uint4*>(p.xprev) + roww;
-    double n2[VPL];
+  double n2[VPL];
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) n2[i] = 0.0;
-    for (int t = tid; t < (dd + 1) * L; t += BLK) {
-      uint4 o = make_uint4(0u, 0u, 0u, 0u);
-      if (t < dd * L) {
-        V wv[VPL], uv[VPL];
-        from_word<V>(w4[t], wv);
-        from_word<V>(u4[t], uv);
+  for (int i = 0; i < VPL; ++i) n2[i] = 0.0;
+  // stages word t of the row; FUSE: u_j = w_{j-1} - alpha s u_{j-1} first, in
+  // place, with |u_j|^2 per vector (a thread's words all hold the vectors of
+  // word index k)
+  auto stage = [&](int t, uint4 o, uint4 u) {
+    if constexpr (FUSE) {
+      V wv[VPL], uv[VPL];
+      from_word<V>(o, wv);
+      from_word<V>(u, uv);
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-          wv[i].x -= cu[i] * uv[i].x;
-          wv[i].y -= cu[i] * uv[i].y;
-          n2[i] += static_cast<double>(wv[i].x) * wv[i].x + static_cast<double>(wv[i].y) * wv[i].y;
-        }
-        o = to_word<V>(wv);
-        w4[t] = o;
+      for (int i = 0; i < VPL; ++i) {
+        wv[i].x -= cu[i] * uv[i].x;
+        wv[i].y -= cu[i] * uv[i].y;
+        n2[i] += static_cast<double>(wv[i].x) * wv[i].x + static_cast<double>(wv[i].y) * wv[i].y;
       }
-      xs[t] = o;
+      o = to_word<V>(wv);
+      w4[t] = o;
     }
+    xs[t] = o;
+  };
+#pragma unroll
+  for (int i = 0; i < kRowAhead; ++i) {
+    const int t = tid + i * BLK;
+    if (t < nw) stage(t, pw[i], pu[FUSE ? i : 0]);
+  }
+  // the rest of a long row, the next word's loads in flight
+  {
+    int t = tid + kRowAhead * BLK;
+    uint4 o = t < nw ? w4[t] : make_uint4(0u, 0u, 0u, 0u), u = o;
+    if constexpr (FUSE)
+      if (t < nw) u = u4[t];
+    while (t < nw) {
+      const int tn = t + BLK;
+      uint4 on = o, un = u;
+      if (tn < nw) {
+        on = w4[tn];
+        if constexpr (FUSE) un = u4[tn];
+      }
+      stage(t, o, u);
+      o = on;
+      u = un;
+      t = tn;
+    }
+  }
+  if (tid < L) xs[nw + tid] = make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (FUSE) {
     __shared__ double tn[NV];
     word_sums<W, L, VPL>(n2, red, tn);
     __syncthreads();
     for (int t = tid; t < NV; t += BLK) p.norm[static_cast<size_t>(a) * NV + t] = tn[(t % VPL) * L + t / VPL];
     if (!p.y) return;  // j = m_max: only the norm was needed
   } else {
-    const uint4* x4 = static_cast<const uint4*>(p.x) + roww;
-    for (int t = tid; t < (dd + 1) * L; t += BLK) xs[t] = t < dd * L ? x4[t] : make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
   }
-  // coefficients of this lane's vectors v = k VPL + i
-  V cf[kG][VPL];
-  double2 ocf[kO ? kG : 1][VPL];
-#pragma unroll
-  for (int g = 0; g < kG; ++g)
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-      const int v = k * VPL + i, c = p.grp_class[g];
-      cf[g][i] = V{static_cast<R>(p.coef[2 * (v * p.nc + c)]), static_cast<R>(p.coef[2 * (v * p.nc + c) + 1])};
-      if constexpr (kO) ocf[g][i] = make_double2(p.coef_obs[2 * (v * p.nc + c)], p.coef_obs[2 * (v * p.nc + c) + 1]);
-    }
-  __syncthreads();
 
   const uint32_t ua = p.up_bits[a];
   const double ea = p.eps_up ? p.eps_up[a] : 0.0;
-  const uint2* tab2 = reinterpret_cast<const uint2*>(p.tab);
   uint4* __restrict__ y4 = static_cast<uint4*>(p.y) + roww;
   double q[kO ? kObsQ * VPL : 1];
 #pragma unroll
   for (int i = 0; i < (kO ? kObsQ * VPL : 1); ++i) q[i] = 0.0;
   for (int b = e0; b < dd; b += EPW) {
-    uint2 ev[kG];
+    const double nd = static_cast<double>(__popc(ua & db));
+    const double dg = p.U * nd + ea + eb;
+    uint2 ec[kG];
 #pragma unroll
-    for (int g = 0; g < kG; ++g) ev[g] = tab2[static_cast<size_t>(b) * kG + g];
-    const double nd = static_cast<double>(__popc(ua & p.dn_bits[b]));
-    const double dg = p.U * nd + ea + (p.eps_dn ? p.eps_dn[b] : 0.0);
+    for (int g = 0; g < kG; ++g) ec[g] = ev[g];
+    if (b + EPW < dd) fetch(b + EPW);
     V xv[VPL], acc[VPL];
     from_word<V>(xs[static_cast<size_t>(b) * L + k], xv);
 #pragma unroll
@@ -320,7 +366,7 @@ __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
       V sum[VPL];
-      group_sum<R, L>(ev[g], xs, static_cast<uint32_t>(dd), k, sum);
+      group_sum<R, L>(ec[g], xs, k, sum);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
         acc[i] = cfma(cf[g][i], sum[i], acc[i]);
@@ -367,94 +413,127 @@ __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
   constexpr bool kO = MODE == M_LANCZOS_OBS;
   constexpr int kNQ = kO ? 2 : 1;  // per vector: alpha [, up-hop obs part]
   __shared__ double red[W * kNQ * NV];
+  __shared__ double sh_b[NV];
   const int tid = threadIdx.x;
   const int k = tid % L, e0 = tid / L;
+  static_assert(!FUSE || MODE == M_LANCZOS, "fused column pass: Lanczos iterations j >= 1");
+  const bool decide = FUSE && blockIdx.x == gridDim.x - 1;
+  if (kL) {
+    if (p.ctl->all_done) return;
+    // the row pass found every running vector's estimate for m = j below tol:
+    // the step ends here and only the decision is left
+    if (FUSE && p.ctl->eps_stop == p.j && !decide) return;
+    if (!decide && p.j >= p.m_max) return;  // only the decision was needed
+  }
+  const int b = decide ? 0 : xcd_remap(blockIdx.x, FUSE ? gridDim.x - 1 : gridDim.x);
+  const int du = p.dim_up, dd = p.dim_dn;
+  const int nw = du * L;  // words of a tile column
+  const uint4* const x4 = static_cast<const uint4*>(p.x);
+  uint4* const y4 = static_cast<uint4*>(p.y);
+  const uint4* const xp4 = static_cast<const uint4*>(p.xprev);
+  const bool prev = kL && p.j > 0;
+  auto word = [&](int t) { return (static_cast<size_t>(t / L) * dd + b) * L + t % L; };  // of staged word t
+
+  // The column's first words, the first element's table entries, partial
+  // product and previous vector, and the coefficients, ahead of the reduction.
+  uint4 px[kColAhead];
+  uint2 ev[kG];
+  uint4 yw, pw;
+  const uint2* tab2 = reinterpret_cast<const uint2*>(p.tab);
+  auto fetch = [&](int a) {
+#pragma unroll
+    for (int g = 0; g < kG; ++g) ev[g] = tab2[static_cast<size_t>(a) * kG + g];
+    const size_t o = (static_cast<size_t>(a) * dd + b) * L + k;  // this lane's word of element (a, b)
+    yw = y4[o];
+    if (prev) pw = xp4[o];
+  };
+  V cf[kG][VPL];
+  double2 ocf[kO ? kG : 1][VPL];
+  double sc[VPL];  // FUSE: s_{j-1} of this lane's vectors
+  if (!decide) {
+#pragma unroll
+    for (int i = 0; i < kColAhead; ++i) {
+      const int t = tid + i * BLK;
+      px[i] = t < nw ? x4[word(t)] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (e0 < du) fetch(e0);
+#pragma unroll
+    for (int g = 0; g < kG; ++g)
+#pragma unroll
+      for (int i = 0; i < VPL; ++i) {
+        const int v = k * VPL + i, c = p.grp_class[g];
+        cf[g][i] = V{static_cast<R>(p.coef[2 * (v * p.nc + c)]), static_cast<R>(p.coef[2 * (v * p.nc + c) + 1])};
+        if constexpr (kO) ocf[g][i] = make_double2(p.coef_obs[2 * (v * p.nc + c)], p.coef_obs[2 * (v * p.nc + c) + 1]);
+      }
+    if constexpr (FUSE)
+#pragma unroll
+      for (int i = 0; i < VPL; ++i) sc[i] = p.st[k * VPL + i].scale[p.j - 1];
+  }
+  double nrm = 0.0;
+  if constexpr (FUSE) nrm = cols_partial<NV, BLK>(p.norm, du, NV);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  uint4* xs = reinterpret_cast<uint4*>(smem_raw);
+  if (!decide) {
+#pragma unroll
+    for (int i = 0; i < kColAhead; ++i) {
+      const int t = tid + i * BLK;
+      if (t < nw) xs[t] = px[i];
+    }
+#pragma unroll 4
+    for (int t = tid + kColAhead * BLK; t < nw; t += BLK) xs[t] = x4[word(t)];
+    if (tid < L) xs[nw + tid] = make_uint4(0u, 0u, 0u, 0u);
+  }
   R sj[VPL], bp[VPL];
 #pragma unroll
   for (int i = 0; i < VPL; ++i) {
     sj[i] = 1;
     bp[i] = 0;
   }
-  static_assert(!FUSE || MODE == M_LANCZOS, "fused column pass: Lanczos iterations j >= 1");
-  if (FUSE) {
-    if (p.ctl->all_done) return;
-    // the row pass found every running vector's estimate for m = j below tol:
-    // the step ends here and only the decision is left
-    const bool decide = blockIdx.x == gridDim.x - 1;
-    if (p.ctl->eps_stop == p.j && !decide) return;
-    __shared__ double sh_b[NV];
-    for (int t = 0; t < NV; ++t) {
-      const double s = reduce_column<W>(p.norm, p.dim_up, NV, t, red);
-      if (tid == 0) sh_b[t] = sqrt(s);  // |u_j| = beta_{j-1} of vector t
-    }
-    __syncthreads();
+  if constexpr (FUSE) {
+    cols_total<NV, W>(nrm, red, sh_b);  // |u_j|^2; its barriers also cover the staged column
     if (decide) {
+      if (tid < NV) sh_b[tid] = sqrt(sh_b[tid]);
+      __syncthreads();
       block_decide_pre<NV, W>(p.j, sh_b, p.st, p.ctl, p.m_max, p.tol, p.norm_inf);
       return;
     }
-    if (p.j >= p.m_max) return;  // only the decision was needed
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
-      const int v = k * VPL + i;
-      const double bv = sh_b[v];
+      const double bv = sqrt(sh_b[k * VPL + i]);  // |u_j| = beta_{j-1}
       sj[i] = static_cast<R>(bv > 0.0 ? 1.0 / bv : 0.0);
-      bp[i] = static_cast<R>(bv > 0.0 ? bv * p.st[v].scale[p.j - 1] : 0.0);
+      bp[i] = static_cast<R>(bv > 0.0 ? bv * sc[i] : 0.0);
     }
-  } else if (kL) {
-    if (p.ctl->all_done) return;
-    if (p.j >= p.m_max) return;
+  } else {
+    if constexpr (kL)
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-      const VecState& S = p.st[k * VPL + i];
-      const double bv = p.j == 0 ? S.beta0 : (S.m >= p.j ? S.beta[p.j - 1] : 0.0);
-      sj[i] = static_cast<R>(bv > 0.0 ? 1.0 / bv : 0.0);
-      bp[i] = static_cast<R>(p.j > 0 && bv > 0.0 ? bv * S.scale[p.j - 1] : 0.0);
-    }
+      for (int i = 0; i < VPL; ++i) {
+        const VecState& S = p.st[k * VPL + i];
+        const double bv = p.j == 0 ? S.beta0 : (S.m >= p.j ? S.beta[p.j - 1] : 0.0);
+        sj[i] = static_cast<R>(bv > 0.0 ? 1.0 / bv : 0.0);
+        bp[i] = static_cast<R>(p.j > 0 && bv > 0.0 ? bv * S.scale[p.j - 1] : 0.0);
+      }
+    __syncthreads();
   }
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  uint4* xs = reinterpret_cast<uint4*>(smem_raw);
-  const int b = xcd_remap(blockIdx.x, FUSE ? gridDim.x - 1 : gridDim.x);
-  const int du = p.dim_up, dd = p.dim_dn;
-  {
-    const uint4* x4 = static_cast<const uint4*>(p.x);
-    for (int t = tid; t < (du + 1) * L; t += BLK) {
-      const int a = t / L, kk = t % L;
-      xs[t] = a < du ? x4[(static_cast<size_t>(a) * dd + b) * L + kk] : make_uint4(0u, 0u, 0u, 0u);
-    }
-  }
-  V cf[kG][VPL];
-  double2 ocf[kO ? kG : 1][VPL];
-#pragma unroll
-  for (int g = 0; g < kG; ++g)
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-      const int v = k * VPL + i, c = p.grp_class[g];
-      cf[g][i] = V{static_cast<R>(p.coef[2 * (v * p.nc + c)]), static_cast<R>(p.coef[2 * (v * p.nc + c) + 1])};
-      if constexpr (kO) ocf[g][i] = make_double2(p.coef_obs[2 * (v * p.nc + c)], p.coef_obs[2 * (v * p.nc + c) + 1]);
-    }
-  __syncthreads();
 
-  const uint2* tab2 = reinterpret_cast<const uint2*>(p.tab);
-  uint4* __restrict__ y4 = static_cast<uint4*>(p.y);
-  const uint4* __restrict__ xp4 = static_cast<const uint4*>(p.xprev);
   double q[kL ? kNQ * VPL : 1];
 #pragma unroll
   for (int i = 0; i < (kL ? kNQ * VPL : 1); ++i) q[i] = 0.0;
   for (int a = e0; a < du; a += EPW) {
-    uint2 ev[kG];
-#pragma unroll
-    for (int g = 0; g < kG; ++g) ev[g] = tab2[static_cast<size_t>(a) * kG + g];
-    const size_t o = (static_cast<size_t>(a) * dd + b) * L + k;  // this lane's word of element (a, b)
+    const size_t o = (static_cast<size_t>(a) * dd + b) * L + k;
     V acc[VPL], pv[VPL];
-    from_word<V>(y4[o], acc);
-    if (kL && p.j > 0) from_word<V>(xp4[o], pv);
+    from_word<V>(yw, acc);
+    if (prev) from_word<V>(pw, pv);
+    uint2 ec[kG];
+#pragma unroll
+    for (int g = 0; g < kG; ++g) ec[g] = ev[g];
+    if (a + EPW < du) fetch(a + EPW);
     double2 ko[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) ko[i] = make_double2(0.0, 0.0);
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
       V sum[VPL];
-      group_sum<R, L>(ev[g], xs, static_cast<uint32_t>(du), k, sum);
+      group_sum<R, L>(ec[g], xs, k, sum);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
         acc[i] = cfma(cf[g][i], sum[i], acc[i]);
@@ -466,7 +545,7 @@ __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
       from_word<V>(xs[static_cast<size_t>(a) * L + k], xv);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
-        const V pvv = p.j > 0 ? pv[i] : V{0, 0};
+        const V pvv = prev ? pv[i] : V{0, 0};
         acc[i].x = acc[i].x * sj[i] - bp[i] * pvv.x;
         acc[i].y = acc[i].y * sj[i] - bp[i] * pvv.y;
         q[i] += static_cast<double>(sj[i]) *

@@ -179,16 +179,16 @@ struct CombineLog {
 };
 
 // v = beta0 sum_k y_k s_k u_k over the m_v vectors of each vector v (in place
-// into slot 0), and |v|^2 partials [elem_grid][nv].  If some vector is still
+// into u_0 = state; u_1, u_2, .. one after another at slots), and |v|^2 partials [elem_grid][nv].  If some vector is still
 // undecided the step is abandoned: ctl->abort is set and slot 0 is kept.
 // Otherwise the first workgroup also records the step (as launch_step_log:
 // log [nv] and, if obs_log, the first apply's observables [nv][nobs]) and
 // clears the control block for the next step; seq >= 1 numbers the
 // (sub)steps of a call, and after one where a vector hit m_max the later
 // combines do nothing.
-hipError_t launch_combine(int prec, int nv, int64_t n, void* const* slots_dev, const VecState* st,
-                          StepCtl* ctl, double* partials, int seq, CombineLog* log, double* obs_log, int nobs,
-                          hipStream_t s, void* copy_to = nullptr);  // copy_to: a second copy of the result (nv = 1)
+hipError_t launch_combine(int prec, int nv, int64_t n, void* state, void* slots, const VecState* st, StepCtl* ctl,
+                          double* partials, int seq, CombineLog* log, double* obs_log, int nobs, hipStream_t s,
+                          void* copy_to = nullptr);  // copy_to: a second copy of the result (nv = 1)
 
 // Overlaps o_v = <c_v psi_v | phi_v> of nv members (same target sector and
 // spin of the operator) with source-sector states psi_v = traj + psi_off[v],

@@ -10,6 +10,7 @@
 #include "kernels_common.h"
 
 #include <algorithm>
+#include <cstdint>
 
 namespace hub {
 namespace dev {
@@ -30,11 +31,8 @@ __global__ __launch_bounds__(kBlock) void k_update(int64_t n, typename CT<R>::T*
   if (ctl->all_done) return;
   const int tid = threadIdx.x;
   const int qn = apply_nq * NV;
-  for (int t = 0; t < NV; ++t) {
-    const double s = reduce_column(apply_partials, apply_nblk, qn, t, red);  // alpha is column 0 * NV + t
-    if (tid == 0) sh_alpha[t] = s;
-  }
-  __syncthreads();
+  // alpha of vector v is column v
+  cols_total<NV, kWaves>(cols_partial<NV, kBlock>(apply_partials, apply_nblk, qn), red, sh_alpha);
   if (blockIdx.x == 0) {
     if (tid < NV && st[tid].status == 0) st[tid].alpha[j] = sh_alpha[tid];
     if (!row_obs) {
@@ -99,15 +97,71 @@ __device__ void record_step(const VecState* st, StepCtl* ctl, CombineLog* log, d
   }
 }
 
+// One word of the state: VPL consecutive values.
+template <typename R, int VPL>
+struct __align__(sizeof(typename CT<R>::T) * VPL) StateWord {
+  typename CT<R>::T v[VPL];
+};
+
+// |v|^2 partials of a state read word by word (the combine's result, or the
+// input of a call's first step and of a step that is run again): both kernels
+// add the same terms in the same order, so a step run again starts from the
+// same bits.
+template <int VPL, typename W>
+__device__ __forceinline__ void word_norm(const W& o, double (&n2)[VPL]) {
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) {
+    const double x = o.v[i].x, y = o.v[i].y;
+    n2[i] = fma(x, x, fma(y, y, n2[i]));
+  }
+}
+// Workgroup sums per vector, fixed order: partials[workgroup][NV].
+template <int NV, int VPL>
+__device__ __forceinline__ void word_norm_store(const double (&n2)[VPL], double* red, double* partials) {
+  constexpr int L = NV > VPL ? NV / VPL : 1, kP = NV == 1 ? 1 : VPL;  // words per element, sums per word
+  double s[kP];
+#pragma unroll
+  for (int i = 0; i < kP; ++i) s[i] = n2[i];
+  if constexpr (NV == 1)
+#pragma unroll
+    for (int i = 1; i < VPL; ++i) s[0] += n2[i];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < kP; ++i) {
+    double t = s[i];
+#pragma unroll
+    for (int off = 32; off >= L; off >>= 1) t += __shfl_xor(t, off);
+    if (lane < L) red[wv * kMaxNV + lane * kP + i] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double t = 0.0;
+    for (int k = 0; k < kWaves; ++k) t += red[k * kMaxNV + threadIdx.x];
+    partials[(size_t)blockIdx.x * NV + threadIdx.x] = t;
+  }
+}
+
 // v <- beta0 sum_{k<m_v} s_k y_k u_k into slot 0, and |v|^2 partials for the
 // next step's first apply; workgroup 0 then records the step (its other
 // workgroups read the control block only at their start, and the record's
-// halt applies from the next sequence number on).
-template <typename R, int NV>
-__global__ __launch_bounds__(kBlock) void k_combine(int64_t n, void* const* slots, const VecState* st,
-                                                    StepCtl* ctl, double* partials, int seq, CombineLog* log,
-                                                    double* obs_log, int nobs, void* out2) {
+// halt applies from the next sequence number on).  Slot 0 is the state, slots
+// 1, 2, .. lie `stride` words apart from `slots` on.  A thread takes a word of
+// VPL values (16 bytes where the vectors are so aligned, else one value) and
+// issues the loads of kCombineAhead slots together.  Eight vectors of 12
+// sites (complex64, groups of 4 on two lanes, about seven slots): 119 us per
+// group with one 8-byte value per thread and a pointer load per slot, 54 us
+// now; one complex128 vector 21.9 and 19.3 us.
+constexpr int kCombineAhead = 4;
+
+template <typename R, int NV, int VPL>
+__global__ __launch_bounds__(kBlock) void k_combine(int64_t words, typename CT<R>::T* state,
+                                                    const typename CT<R>::T* slots, int64_t stride,
+                                                    const VecState* st, StepCtl* ctl, double* partials, int seq,
+                                                    CombineLog* log, double* obs_log, int nobs,
+                                                    typename CT<R>::T* out2) {
   using V = typename CT<R>::T;
+  using Word = StateWord<R, VPL>;
+  constexpr int L = NV > VPL ? NV / VPL : 1;  // words per element (a word of one vector: consecutive elements)
   __shared__ double red[kWaves * kMaxNV];
   __shared__ double cr[kMaxNV][kMMax], ci[kMaxNV][kMMax];
   __shared__ int mv[kMaxNV];
@@ -116,6 +170,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(int64_t n, void* const* slot
   // with slot 0 unchanged; the flag makes the rest of the enqueued work idle.
   if (ctl->abort || (ctl->halt_from > 0 && seq >= ctl->halt_from)) return;
   bool undecided = false;
+#pragma unroll
   for (int v = 0; v < NV; ++v) undecided |= (st[v].status == 0);
   if (undecided) {
     if (blockIdx.x == 0 && tid == 0) {
@@ -133,44 +188,66 @@ __global__ __launch_bounds__(kBlock) void k_combine(int64_t n, void* const* slot
     if (k == 0) mv[vv] = S.m;
   }
   __syncthreads();
-  const int v = tid % NV;
-  const int m = mv[v];
-  V* out = static_cast<V*>(slots[0]);
-  double n2 = 0.0;
-  const int64_t total = n * NV;
-  for (int64_t i = (int64_t)blockIdx.x * kBlock + tid; i < total; i += (int64_t)gridDim.x * kBlock) {
-    double ar = 0.0, ai = 0.0;
-    for (int k = 0; k < m; ++k) {
-      const V u = static_cast<const V*>(slots[k])[i];
-      ar += cr[v][k] * u.x - ci[v][k] * u.y;
-      ai += cr[v][k] * u.y + ci[v][k] * u.x;
-    }
-    const V o = V{static_cast<R>(ar), static_cast<R>(ai)};
-    out[i] = o;
-    if (out2) static_cast<V*>(out2)[i] = o;
-    n2 += (double)o.x * o.x + (double)o.y * o.y;
+  // vector of value i of this thread's words (kBlock and the grid's stride are multiples of L)
+  int vec[VPL], m = 0;
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) {
+    vec[i] = NV == 1 ? 0 : (tid % L) * VPL + i;
+    m = max(m, mv[vec[i]]);
   }
-  block_partials<NV>(&n2, 1, red, partials + (size_t)blockIdx.x * NV);
+  double n2[VPL];
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) n2[i] = 0.0;
+  Word* const out = reinterpret_cast<Word*>(state);
+  const Word* const sl = reinterpret_cast<const Word*>(slots);
+  for (int64_t w = (int64_t)blockIdx.x * kBlock + tid; w < words; w += (int64_t)gridDim.x * kBlock) {
+    double ar[VPL], ai[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) ar[i] = ai[i] = 0.0;
+    for (int k0 = 0; k0 < m; k0 += kCombineAhead) {
+      Word u[kCombineAhead];
+#pragma unroll
+      for (int q = 0; q < kCombineAhead; ++q) {
+        const int k = min(k0 + q, m - 1);
+        u[q] = k == 0 ? out[w] : sl[(k - 1) * stride + w];
+      }
+#pragma unroll
+      for (int q = 0; q < kCombineAhead; ++q)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+          if (k0 + q < mv[vec[i]]) {  // slots past a vector's own m hold no vector of it
+            const double c = cr[vec[i]][k0 + q], d = ci[vec[i]][k0 + q];
+            ar[i] += c * u[q].v[i].x - d * u[q].v[i].y;
+            ai[i] += c * u[q].v[i].y + d * u[q].v[i].x;
+          }
+    }
+    Word o;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) o.v[i] = V{static_cast<R>(ar[i]), static_cast<R>(ai[i])};
+    word_norm<VPL>(o, n2);
+    out[w] = o;
+    if (out2) reinterpret_cast<Word*>(out2)[w] = o;
+  }
+  word_norm_store<NV, VPL>(n2, red, partials);
   if (blockIdx.x == 0) record_step<NV>(st, ctl, log, obs_log, nobs, seq);
 }
 
 // |v|^2 partials of the step's input (first step of a call), tau for every
 // vector, and a cleared control block.
-template <typename R, int NV>
-__global__ __launch_bounds__(kBlock) void k_step_begin(int64_t n, const typename CT<R>::T* x, VecState* st,
+template <typename R, int NV, int VPL>
+__global__ __launch_bounds__(kBlock) void k_step_begin(int64_t words, const typename CT<R>::T* x, VecState* st,
                                                        StepCtl* ctl, double tau, int norm, double* partials) {
-  using V = typename CT<R>::T;
+  using Word = StateWord<R, VPL>;
   __shared__ double red[kWaves * kMaxNV];
   if (ctl->abort) return;
   const int tid = threadIdx.x;
-  double n2 = 0.0;
   if (norm) {
-    const int64_t total = n * NV;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + tid; i < total; i += (int64_t)gridDim.x * kBlock) {
-      const V t = x[i];
-      n2 += (double)t.x * t.x + (double)t.y * t.y;
-    }
-    block_partials<NV>(&n2, 1, red, partials + (size_t)blockIdx.x * NV);
+    double n2[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) n2[i] = 0.0;
+    for (int64_t w = (int64_t)blockIdx.x * kBlock + tid; w < words; w += (int64_t)gridDim.x * kBlock)
+      word_norm<VPL>(reinterpret_cast<const Word*>(x)[w], n2);
+    word_norm_store<NV, VPL>(n2, red, partials);
   }
   if (blockIdx.x == 0 && tid < NV) st[tid].tau = tau;
   if (blockIdx.x == 0 && tid == 0) {
@@ -294,36 +371,67 @@ __global__ __launch_bounds__(kBlock) void k_dots(int64_t n, int nvec, const type
 // gathered straight from psi_v (no copy of c_v psi_v).  phi is interleaved
 // ([y][NV]) or in the ABI layout ([v][n_t]).  Partials [NV][grid][2]; the
 // kernel does nothing after an abandoned step (ctl->abort).
-template <typename R, int NV>
+// A thread takes the VPL members of one 16-byte word of an interleaved
+// element (one member otherwise), so that the record's gathers of a block
+// spread over the chip; 8 members of 10 sites (complex64): 32 us with one
+// thread per element on 52 workgroups and a reduction per sum, 10 us now.
+template <typename R, int NV, int VPL>
 __global__ __launch_bounds__(kBlock) void k_overlaps(OverlapArgs p) {
   using V = typename CT<R>::T;
-  __shared__ double red[kWaves];
+  struct __align__(sizeof(V) * VPL) Word {
+    V v[VPL];
+  };
+  constexpr int L = NV / VPL;  // words per element
+  __shared__ double red[kWaves * 2 * NV];
   if (p.ctl && p.ctl->abort) return;
-  const V* psi = static_cast<const V*>(p.traj);
-  const V* phi = static_cast<const V*>(p.phi);
-  double acc[2 * NV];
+  const V* const psi = static_cast<const V*>(p.traj);
+  const int tid = threadIdx.x, k = tid % L;
+  double acc[2 * VPL];
 #pragma unroll
-  for (int q = 0; q < 2 * NV; ++q) acc[q] = 0.0;
-  for (int64_t y = (int64_t)blockIdx.x * kBlock + threadIdx.x; y < p.n_t; y += (int64_t)gridDim.x * kBlock) {
-    const int a = static_cast<int>(y / p.dim_dn_t), b = static_cast<int>(y % p.dim_dn_t);
+  for (int q = 0; q < 2 * VPL; ++q) acc[q] = 0.0;
+  int64_t off[VPL];
+  const int32_t* map[VPL];
+  const int8_t* sgn[VPL];
+#pragma unroll
+  for (int i = 0; i < VPL; ++i) {
+    const int v = k * VPL + i;
+    off[i] = p.psi_off[v];
+    map[i] = p.maps + static_cast<size_t>(v) * p.map_len;
+    sgn[i] = p.sgns + static_cast<size_t>(v) * p.map_len;
+  }
+  const uint32_t ddt = static_cast<uint32_t>(p.dim_dn_t);
+  for (int64_t w = (int64_t)blockIdx.x * kBlock + tid; w < p.n_t * L; w += (int64_t)gridDim.x * kBlock) {
+    const int64_t y = w / L;
+    const int a = static_cast<int>(static_cast<uint32_t>(y) / ddt), b = static_cast<int>(y - (int64_t)a * ddt);
     const int r = p.down ? b : a;
+    Word f;
+    if (VPL > 1 || p.interleaved) f = static_cast<const Word*>(p.phi)[w];
+    else f.v[0] = static_cast<const V*>(p.phi)[k * p.n_t + y];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int src = p.maps[v * p.map_len + r];
+    for (int i = 0; i < VPL; ++i) {
+      const int src = map[i][r];
       if (src < 0) continue;
       const int64_t se = p.down ? (int64_t)a * p.dim_dn_s + src : (int64_t)src * p.dim_dn_s + b;
-      const V x = psi[p.psi_off[v] + se];
-      const V f = p.interleaved ? phi[y * NV + v] : phi[v * p.n_t + y];
-      const double sg = static_cast<double>(p.sgns[v * p.map_len + r]);
-      acc[2 * v] += sg * ((double)x.x * f.x + (double)x.y * f.y);
-      acc[2 * v + 1] += sg * ((double)x.x * f.y - (double)x.y * f.x);
+      const V x = psi[off[i] + se];
+      const double sg = static_cast<double>(sgn[i][r]);
+      acc[2 * i] += sg * ((double)x.x * f.v[i].x + (double)x.y * f.v[i].y);
+      acc[2 * i + 1] += sg * ((double)x.x * f.v[i].y - (double)x.y * f.v[i].x);
     }
   }
-  // member v's pair goes to partials + (v grid + workgroup) 2
+  // workgroup sums, fixed order; member v's pair goes to partials + (v grid + workgroup) 2
+  const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
-  for (int q = 0; q < 2 * NV; ++q) {
-    const double t = block_sum(acc[q], red);
-    if (threadIdx.x == 0) p.partials[((size_t)(q >> 1) * gridDim.x + blockIdx.x) * 2 + (q & 1)] = t;
+  for (int q = 0; q < 2 * VPL; ++q) {
+    double t = acc[q];
+#pragma unroll
+    for (int o = 32; o >= L; o >>= 1) t += __shfl_xor(t, o);
+    if (lane < L) red[wv * 2 * NV + lane * 2 * VPL + q] = t;
+  }
+  __syncthreads();
+  if (tid < 2 * NV) {
+    double t = 0.0;
+    for (int w = 0; w < kWaves; ++w) t += red[w * 2 * NV + tid];
+    p.partials[((size_t)(tid >> 1) * gridDim.x + blockIdx.x) * 2 + (tid & 1)] = t;
   }
 }
 
@@ -648,26 +756,77 @@ hipError_t launch_update(int prec, int nv, int64_t n, void* w, const void* uj, V
   return hipGetLastError();
 }
 
-hipError_t launch_combine(int prec, int nv, int64_t n, void* const* slots_dev, const VecState* st,
-                          StepCtl* ctl, double* partials, int seq, CombineLog* log, double* obs_log, int nobs,
-                          hipStream_t s, void* copy_to) {
-  const int grid = elem_grid(n * nv);
-  if (prec == 0) {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_combine<double, NVC>), dim3(grid), dim3(kBlock), 0, s, n, slots_dev,
-                                         st, ctl, partials, seq, log, obs_log, nobs, copy_to));
-  } else {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_combine<float, NVC>), dim3(grid), dim3(kBlock), 0, s, n, slots_dev,
-                                         st, ctl, partials, seq, log, obs_log, nobs, copy_to));
-  }
+// 16-byte words where every vector's storage is made of whole ones (an odd
+// number of complex64 values, or a caller's vector at an odd one, is not).
+template <typename R, int NV>
+static bool whole_words(int64_t n, const void* state, const void* a = nullptr, const void* b = nullptr) {
+  constexpr int VPL = 16 / sizeof(typename CT<R>::T);
+  auto odd = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 != 0; };
+  return (n * NV) % VPL == 0 && !odd(state) && !odd(a) && !odd(b);
+}
+
+template <typename R, int NV>
+static hipError_t combine_t(int64_t n, void* state, void* slots, const VecState* st, StepCtl* ctl, double* partials,
+                            int seq, CombineLog* log, double* obs_log, int nobs, hipStream_t s, void* copy_to) {
+  using V = typename CT<R>::T;
+  constexpr int VPL = 16 / sizeof(V);
+  const int grid = elem_grid(n * NV);
+  V* const x = static_cast<V*>(state);
+  const V* const sl = static_cast<const V*>(slots);
+  if (whole_words<R, NV>(n, state, slots, copy_to))
+    hipLaunchKernelGGL((k_combine<R, NV, VPL>), dim3(grid), dim3(kBlock), 0, s, n * NV / VPL, x, sl, n * NV / VPL, st,
+                       ctl, partials, seq, log, obs_log, nobs, static_cast<V*>(copy_to));
+  else
+    hipLaunchKernelGGL((k_combine<R, NV, 1>), dim3(grid), dim3(kBlock), 0, s, n * NV, x, sl, n * NV, st, ctl, partials,
+                       seq, log, obs_log, nobs, static_cast<V*>(copy_to));
   return hipGetLastError();
 }
 
-hipError_t launch_overlaps(int prec, int nv, const OverlapArgs& a, hipStream_t s) {
-  const int grid = overlap_grid(a.n_t);
+template <typename R, int NV>
+static void step_begin_t(int64_t n, const void* v, VecState* st, StepCtl* ctl, double tau, bool norm, double* partials,
+                         hipStream_t s) {
+  using V = typename CT<R>::T;
+  constexpr int VPL = 16 / sizeof(V);
+  const int grid = elem_grid(n * NV);
+  const V* const x = static_cast<const V*>(v);
+  if (whole_words<R, NV>(n, v))
+    hipLaunchKernelGGL((k_step_begin<R, NV, VPL>), dim3(grid), dim3(kBlock), 0, s, n * NV / VPL, x, st, ctl, tau,
+                       norm ? 1 : 0, partials);
+  else
+    hipLaunchKernelGGL((k_step_begin<R, NV, 1>), dim3(grid), dim3(kBlock), 0, s, n * NV, x, st, ctl, tau, norm ? 1 : 0,
+                       partials);
+}
+
+hipError_t launch_combine(int prec, int nv, int64_t n, void* state, void* slots, const VecState* st, StepCtl* ctl,
+                          double* partials, int seq, CombineLog* log, double* obs_log, int nobs, hipStream_t s,
+                          void* copy_to) {
   if (prec == 0) {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_overlaps<double, NVC>), dim3(grid), dim3(kBlock), 0, s, a));
+    HUB_NV_SWITCH(nv, return (combine_t<double, NVC>(n, state, slots, st, ctl, partials, seq, log, obs_log, nobs, s,
+                                                     copy_to)));
   } else {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_overlaps<float, NVC>), dim3(grid), dim3(kBlock), 0, s, a));
+    HUB_NV_SWITCH(nv, return (combine_t<float, NVC>(n, state, slots, st, ctl, partials, seq, log, obs_log, nobs, s,
+                                                    copy_to)));
+  }
+}
+
+template <typename R, int NV>
+static void overlaps_t(const OverlapArgs& a, hipStream_t s) {
+  constexpr int VPL = 16 / sizeof(typename CT<R>::T);
+  const int grid = overlap_grid(a.n_t);
+  if constexpr (VPL > 1 && NV % VPL == 0)  // a block's words are whole and aligned (its buffer is the library's)
+    if (a.interleaved) {
+      hipLaunchKernelGGL((k_overlaps<R, NV, VPL>), dim3(grid), dim3(kBlock), 0, s, a);
+      return;
+    }
+  hipLaunchKernelGGL((k_overlaps<R, NV, 1>), dim3(grid), dim3(kBlock), 0, s, a);
+}
+
+hipError_t launch_overlaps(int prec, int nv, const OverlapArgs& a, hipStream_t s) {
+  if (a.n_t > INT32_MAX) return hipErrorInvalidValue;  // tile positions are 32-bit (16 sites: 1.7e8)
+  if (prec == 0) {
+    HUB_NV_SWITCH(nv, (overlaps_t<double, NVC>(a, s)));
+  } else {
+    HUB_NV_SWITCH(nv, (overlaps_t<float, NVC>(a, s)));
   }
   return hipGetLastError();
 }
@@ -687,8 +846,8 @@ hipError_t launch_fill_probe(int prec, int64_t n, void* x, hipStream_t s) {
 }
 
 int overlap_grid(int64_t n_t) {
-  const int64_t g = (n_t + 4 * kBlock - 1) / (4 * kBlock);
-  return static_cast<int>(g < 1 ? 1 : (g > 256 ? 256 : g));
+  const int64_t g = (n_t + kBlock - 1) / kBlock;
+  return static_cast<int>(g < 1 ? 1 : (g > 1024 ? 1024 : g));
 }
 
 hipError_t launch_step_log(int nv, const VecState* st, StepCtl* ctl, void* log, double* obs_log, int nobs,
@@ -700,13 +859,10 @@ hipError_t launch_step_log(int nv, const VecState* st, StepCtl* ctl, void* log, 
 
 hipError_t launch_step_begin(int prec, int nv, int64_t n, const void* v, VecState* st, StepCtl* ctl, double tau,
                              bool norm, double* partials, hipStream_t s) {
-  const int grid = elem_grid(n * nv);
   if (prec == 0) {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_step_begin<double, NVC>), dim3(grid), dim3(kBlock), 0, s, n,
-                                         static_cast<const double2*>(v), st, ctl, tau, norm ? 1 : 0, partials));
+    HUB_NV_SWITCH(nv, (step_begin_t<double, NVC>(n, v, st, ctl, tau, norm, partials, s)));
   } else {
-    HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_step_begin<float, NVC>), dim3(grid), dim3(kBlock), 0, s, n,
-                                         static_cast<const float2*>(v), st, ctl, tau, norm ? 1 : 0, partials));
+    HUB_NV_SWITCH(nv, (step_begin_t<float, NVC>(n, v, st, ctl, tau, norm, partials, s)));
   }
   return hipGetLastError();
 }

@@ -84,6 +84,64 @@ __device__ inline double reduce_column(const double* partials, int nrows, int nc
   return block_sum<W>(s, lds);
 }
 
+// Totals of the first NC columns of a [nrows][ncols] partial-sum array in one
+// pass over it (NC a power of two up to 64), fixed order: every thread sums
+// its column's rows eight loads at a time, the wavefronts' sums meet in lds
+// (W * NC doubles) and out[NC] (LDS) gets the totals, visible to the whole
+// workgroup on return.  In two parts, so that a kernel can issue its other
+// loads in between: a reduction column by column waits out a memory latency
+// and three barriers per column.
+template <int NC, int BLK>
+__device__ __forceinline__ double cols_partial(const double* partials, int nrows, int ncols) {
+  static_assert(NC >= 1 && NC <= 64 && (NC & (NC - 1)) == 0 && BLK % 64 == 0, "a wavefront holds whole rows");
+  constexpr int kStep = BLK / NC, kU = 8;
+  const int c = threadIdx.x % NC;
+  double s = 0.0;
+  for (int r = threadIdx.x / NC; r < nrows; r += kU * kStep) {
+    double v[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const int rr = r + q * kStep;
+      v[q] = rr < nrows ? partials[static_cast<size_t>(rr) * ncols + c] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kU; ++q) s += v[q];
+  }
+  return s;
+}
+template <int NC, int W>
+__device__ __forceinline__ void cols_total(double s, double* lds, double* out) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 32; off >= NC; off >>= 1) s += __shfl_xor(s, off);
+  if (lane < NC) lds[w * NC + lane] = s;
+  __syncthreads();
+  if (threadIdx.x < NC) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) t += lds[k * NC + threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+// Entry s (0..3) of a grouped hop table's word pair: the staged source (dim,
+// the zero element, for padding) and the hop's sign as +-1.  The sign is a
+// bit of its own, so that a source costs one bit-field extract and a sign one
+// or two bit operations (told from an index offset they cost a comparison and
+// two selects more, a fifth of a gather's instructions).
+__device__ __forceinline__ uint32_t slot_src(uint2 w, int s) {
+  const uint32_t h = s < 2 ? w.x : w.y;
+  return (s & 1) ? (h >> 16) & 0x7FFFu : h & 0x7FFFu;
+}
+template <typename R>
+__device__ __forceinline__ R slot_sign(uint2 w, int s) {
+  const uint32_t h = s < 2 ? w.x : w.y;
+  const uint32_t b = ((s & 1) ? h : h << 16) & 0x80000000u;
+  if constexpr (sizeof(R) == 8) return __hiloint2double(static_cast<int>(b | 0x3FF00000u), 0);
+  else return __uint_as_float(b | 0x3F800000u);
+}
+
 template <typename V> __device__ __forceinline__ V cadd(V a, V b) { return V{a.x + b.x, a.y + b.y}; }
 template <typename V> __device__ __forceinline__ V csub(V a, V b) { return V{a.x - b.x, a.y - b.y}; }
 // acc + c s with the fused multiply-adds written out, so that every kernel

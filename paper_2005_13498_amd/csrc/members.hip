@@ -22,21 +22,17 @@ constexpr int kB = 4;          // elements per thread whose memory loads are iss
 // Sum over the workgroup, identical on every thread, fixed order.
 __device__ inline double msum(double v, double* red) { return block_sum<kMW>(v, red); }
 
-// Signed sum of the four staged values one table word pair indexes (src,
-// src + dim + 1 for a negative sign, dim = the zero slot); staged element q
-// is at xs[q * stride].
+// Signed sum of the four staged values one table word pair indexes; staged
+// element q is at xs[q * stride].
 template <typename V>
-__device__ __forceinline__ V group4(uint2 w, const V* xs, uint32_t dim, int stride) {
+__device__ __forceinline__ V group4(uint2 w, const V* xs, int stride) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const uint32_t w2 = k < 2 ? w.x : w.y;
-    const uint32_t idx = (k & 1) ? (w2 >> 16) : (w2 & 0xFFFFu);
-    const bool neg = idx > dim;
-    const uint32_t src = neg ? idx - dim - 1u : idx;
-    const V t = xs[static_cast<size_t>(src) * stride];
-    s.x += neg ? -t.x : t.x;
-    s.y += neg ? -t.y : t.y;
+    const auto sg = slot_sign<decltype(s.x)>(w, k);
+    const V t = xs[static_cast<int>(slot_src(w, k)) * stride];
+    s.x = fma(sg, t.x, s.x);
+    s.y = fma(sg, t.y, s.y);
   }
   return s;
 }
@@ -158,7 +154,7 @@ __global__ __launch_bounds__(kMT) void k_members(MembersArgs P) {
           const V xv = row[b];
           V acc = V{static_cast<R>(dg) * xv.x, static_cast<R>(dg) * xv.y};
           for (int g = 0; g < gdn; ++g)
-            acc = cfma(cf_dn[g], group4(tdn[b * gdn + g], row, static_cast<uint32_t>(dd), 1), acc);
+            acc = cfma(cf_dn[g], group4(tdn[b * gdn + g], row, 1), acc);
           z[a * dd + b] = acc;
         }
       }
@@ -211,7 +207,7 @@ __global__ __launch_bounds__(kMT) void k_members(MembersArgs P) {
           const int a = t / nc, c = t - a * nc;
           V acc = zv[k];
           for (int g = 0; g < gup; ++g)
-            acc = cfma(cf_up[g], group4(tup[a * gup + g], xs + c, static_cast<uint32_t>(du), cb), acc);
+            acc = cfma(cf_up[g], group4(tup[a * gup + g], xs + c, cb), acc);
           const V out = V{acc.x * sj - bp * pv[k].x, acc.y * sj - bp * pv[k].y};
           const V xv = xs[a * cb + c];
           qa += static_cast<double>(sj) * (static_cast<double>(xv.x) * out.x + static_cast<double>(xv.y) * out.y);

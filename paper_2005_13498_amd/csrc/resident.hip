@@ -9,9 +9,8 @@
 // staged once per Lanczos iteration as (dim_up + 1) x (dim_dn + 1) elements,
 // each row followed by a zero and a zero row last, so that a down hop of
 // element (a, b) reads row a and an up hop reads column b of the same array,
-// both at an index that carries the fermion sign (src, src + dim + 1 for a
-// negative sign, dim for padding), four slots of one class summed before the
-// class coefficient is applied.  Iteration j (v_j = s_j u_j):
+// both at a table entry that carries the fermion sign (dim for padding), four
+// slots of one class summed before the class coefficient is applied.  Iteration j (v_j = s_j u_j):
 //   w_j = s_j H u_j - beta_{j-1} s_{j-1} u_{j-1}      (registers)
 //   alpha_j = s_j Re <u_j, w_j>
 //   u_{j+1} = w_j - alpha_j s_j u_j                   (registers -> LDS)
@@ -33,24 +32,21 @@ constexpr int kRT = kResidentThreads;
 constexpr int kRW = kRT / 64;
 
 // Signed sum of the four staged values one table word pair indexes; staged
-// element q is at xs[q * stride], dim is the zero element.
+// element q is at xs[q * stride].
 template <typename V>
-__device__ __forceinline__ V slot_sum4(uint2 w, const V* xs, uint32_t dim, int stride) {
+__device__ __forceinline__ V slot_sum4(uint2 w, const V* xs, int stride) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const uint32_t w2 = k < 2 ? w.x : w.y;
-    const uint32_t idx = (k & 1) ? (w2 >> 16) : (w2 & 0xFFFFu);
-    const bool neg = idx > dim;
-    const uint32_t src = neg ? idx - dim - 1u : idx;
-    const V t = xs[static_cast<int>(src) * stride];
-    s.x += neg ? -t.x : t.x;
-    s.y += neg ? -t.y : t.y;
+    const auto sg = slot_sign<decltype(s.x)>(w, k);
+    const V t = xs[static_cast<int>(slot_src(w, k)) * stride];
+    s.x = fma(sg, t.x, s.x);
+    s.y = fma(sg, t.y, s.y);
   }
   return s;
 }
 
-// The same over staged columns, skipping padding entries (index dim): the
+// The same over staged columns, skipping padding entries (source dim): the
 // lanes of a wavefront mostly share the up string and so its padding, and a
 // padding read of the zero row would cost a full-width LDS access.
 template <typename V>
@@ -58,14 +54,12 @@ __device__ __forceinline__ V slot_sum4_skip(uint2 w, const V* xs, uint32_t dim, 
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const uint32_t w2 = k < 2 ? w.x : w.y;
-    const uint32_t idx = (k & 1) ? (w2 >> 16) : (w2 & 0xFFFFu);
-    if (idx == dim) continue;
-    const bool neg = idx > dim;
-    const uint32_t src = neg ? idx - dim - 1u : idx;
+    const uint32_t src = slot_src(w, k);
+    if (src == dim) continue;
+    const auto sg = slot_sign<decltype(s.x)>(w, k);
     const V t = xs[static_cast<int>(src) * stride];
-    s.x += neg ? -t.x : t.x;
-    s.y += neg ? -t.y : t.y;
+    s.x = fma(sg, t.x, s.x);
+    s.y = fma(sg, t.y, s.y);
   }
   return s;
 }
@@ -197,7 +191,7 @@ __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
     const V* row = xs + a * ld;
 #pragma unroll 2
     for (int g = 0; g < gdn; ++g) {
-      const V s = slot_sum4(tdn[b * gdn + g], row, static_cast<uint32_t>(dd), 1);
+      const V s = slot_sum4(tdn[b * gdn + g], row, 1);
       if (mid) acc = cfma(cf_dn[g], s, acc);
       if (obs) ko = cfma(of_dn[g], make_double2(s.x, s.y), ko);
     }
