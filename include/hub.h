@@ -160,7 +160,9 @@ hub_status hub_basis_hops(hub_basis basis, int32_t spin, int32_t *ptr, int32_t *
 /* y = H(A_v) x_v for nvec vectors (Eq. (hubbardhamiltonian) with the Peierls
  * phases of Eq. (peierls) at vector potential A_v; matrix-free).  A: host
  * array [nvec].  x, y: device, nvec * dim complex of precision `prec`,
- * distinct buffers.  Asynchronous on `stream`. */
+ * distinct buffers.  Asynchronous on `stream`.  Several vectors go in batches
+ * of up to 8 in this layout where no plan or path is set on the handle, else in
+ * interleaved groups. */
 hub_status hub_apply_H(hub_basis basis, const double *A, hub_prec prec, int32_t nvec,
                        const void *x, void *y, void *stream);
 
@@ -505,7 +507,8 @@ hub_status hub_set_tuning(hub_basis basis, hub_prec prec, const hub_tuning *t);
 /* The plan for nvec vectors (propagate = 1: hub_propagate, 0: hub_apply_H):
  * n_groups, and per group (host arrays of >= nvec entries, either may be
  * NULL) its size and kernels: 0 one pass, 1 two-pass single vector, 2
- * two-pass block kernels. */
+ * two-pass kernels over several vectors (blocks, or the batches hub_apply_H
+ * takes in the caller's layout). */
 hub_status hub_get_plan(hub_basis basis, hub_prec prec, int32_t nvec, int32_t propagate, int32_t *n_groups,
                         int32_t *sizes, int32_t *kernels);
 

@@ -364,17 +364,22 @@ hub_status check_common(hub_basis h, hub_prec prec, int32_t nvec) {
 // Lanczos-mode applies that do not also accumulate observables (every
 // prof_period-th such apply): one start/end pair per kernel, so a sampled
 // apply's time is its kernel time (row plus column pass for two passes).
+// batch >= 0: a batched plain product with that batch_columns.
 hub_status launch_apply_timed(hub_basis h, const hub::ApplyLaunch& L, int* grid = nullptr, bool fusing = false,
-                              int step = -1, int sub = 0) {
+                              int step = -1, int sub = 0, int batch = -1) {
+  auto launch = [&](const hub::ApplyLaunch& A) {
+    return batch >= 0 ? hub::launch_batch(A, batch) : hub::launch_apply(A, grid);
+  };
   // with fused iterations in the loop, only those (the dominant kernels) are timed
   bool timed = h->prof && (L.mode == hub::kPlain || (L.mode == hub::kLanczos && !L.obs && (!fusing || L.fuse)));
   if (timed) timed = (h->prof_count++ % h->prof_period) == 0;
   if (!timed) {
-    HUB_HIP(hub::launch_apply(L, grid));
+    HUB_HIP(launch(L));
     return HUB_OK;
   }
-  const bool two = hub::apply_two_pass(h->D, L.prec, L.nv, L.mode, L.obs) ||
-                   (L.nv > 1 && hub::block_two_pass(h->D, L.prec, L.nv));
+  const bool two = batch >= 0 ? batch > 0
+                              : hub::apply_two_pass(h->D, L.prec, L.nv, L.mode, L.obs) ||
+                                    (L.nv > 1 && hub::block_two_pass(h->D, L.prec, L.nv));
   std::array<hipEvent_t, 4> ev{nullptr, nullptr, nullptr, nullptr};
   for (int k = 0; k < (two ? 4 : 2); ++k) {
     if (!h->ev_free.empty()) {
@@ -389,7 +394,7 @@ hub_status launch_apply_timed(hub_basis h, const hub::ApplyLaunch& L, int* grid 
   T.ev_stop = ev[1];
   T.ev2_start = ev[2];
   T.ev2_stop = ev[3];
-  HUB_HIP(hub::launch_apply(T, grid));
+  HUB_HIP(launch(T));
   ProfSample smp;
   smp.ev = ev;
   smp.n = step;
@@ -475,6 +480,34 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
     g.push_back(s);
     left -= s;
   }
+  return g;
+}
+
+// hub_apply_H's groups of the automatic rule: batches in the caller's layout
+// (columns: batch_columns) where the caller and no tuned plan chose kernels or
+// group sizes, else the interleaved groups (columns -1) of groups_for.
+struct ApplyGroup {
+  int nv, columns;
+};
+std::vector<ApplyGroup> apply_groups(hub_basis h, int nvec, int prec) {
+  std::vector<ApplyGroup> g;
+  if (nvec > 1 && h->force_group == 0 && h->apply_group[prec] <= 0 && h->D.two_pass == -1 && h->D.block_path == -1) {
+    for (int left = nvec; left > 0;) {
+      int nv = std::min(left, kMaxNV);
+      int columns = hub::batch_columns(h->D, prec, nv);
+      // two columns of complex64 pairs: an odd vector alone is faster than half a
+      // pair (14 sites, 3 vectors: 431 + 202 us vs 809)
+      if (columns == 2 && prec == 1 && nv % 2) columns = --nv > 1 ? columns : -1;
+      if (columns < 0 && nv > 1) {
+        g.clear();
+        break;
+      }
+      g.push_back({nv, columns});
+      left -= nv;
+    }
+    if (!g.empty()) return g;
+  }
+  for (int nv : groups_for(h, nvec, prec, false)) g.push_back({nv, -1});
   return g;
 }
 
@@ -1297,13 +1330,17 @@ hub_status hub_apply_H(hub_basis h, const double* A, hub_prec prec, int32_t nvec
   const size_t es = elem_bytes(prec);
   const int64_t dim = h->D.dim;
   const int nc = h->D.nc;
-  const std::vector<int> groups = groups_for(h, nvec, pi, false);
-  int gmax = 1;
-  for (int g : groups) gmax = std::max(gmax, g);
-  s = ensure_workspace(h, static_cast<size_t>(dim) * gmax * es, 1, gmax > 1 ? static_cast<size_t>(dim) * gmax * es : 0);
-  if (s != HUB_OK) return s;
+  const std::vector<ApplyGroup> groups = apply_groups(h, nvec, pi);
+  int gmax = 1;  // largest interleaved group: needs the block buffers
+  for (const ApplyGroup& g : groups)
+    if (g.columns < 0) gmax = std::max(gmax, g.nv);
+  if (gmax > 1) {
+    s = ensure_workspace(h, static_cast<size_t>(dim) * gmax * es, 1, static_cast<size_t>(dim) * gmax * es);
+    if (s != HUB_OK) return s;
+  }
   int k0 = 0;
-  for (int nv : groups) {
+  for (const ApplyGroup& g : groups) {
+    const int nv = g.nv;
     std::vector<double> cf(static_cast<size_t>(2) * kMaxNV * kMaxClasses, 0.0);
     for (int v = 0; v < nv; ++v) coef_for(h->B, A[k0 + v], cf.data() + static_cast<size_t>(2) * v * nc);
     const char* xin = static_cast<const char*>(x) + static_cast<size_t>(k0) * dim * es;
@@ -1316,10 +1353,10 @@ hub_status hub_apply_H(hub_basis h, const double* A, hub_prec prec, int32_t nvec
     L.mode = hub::kPlain;
     L.coef = cf.data();
     L.stream = st;
-    if (nv == 1) {
+    if (nv == 1 || g.columns >= 0) {
       L.x = xin;
       L.y = yout;
-      s = launch_apply_timed(h, L);
+      s = launch_apply_timed(h, L, nullptr, false, -1, 0, g.columns);
       if (s != HUB_OK) return s;
     } else {
       HUB_HIP(hub::launch_interleave(pi, nv, dim, xin, h->w.blockbuf, true, st));
@@ -2792,12 +2829,17 @@ hub_status hub_get_plan(hub_basis h, hub_prec prec, int32_t nvec, int32_t propag
   if (prec != HUB_C128 && prec != HUB_C64) return fail(HUB_E_INVALID, "unknown precision");
   if (nvec < 1 || !n_groups) return fail(HUB_E_INVALID, "nvec must be >= 1 and n_groups non-null");
   const int pi = prec == HUB_C128 ? 0 : 1;
-  const std::vector<int> g = groups_for(h, nvec, pi, propagate != 0);
+  std::vector<ApplyGroup> g;
+  if (propagate)
+    for (int nv : groups_for(h, nvec, pi)) g.push_back({nv, -1});
+  else
+    g = apply_groups(h, nvec, pi);
   *n_groups = static_cast<int32_t>(g.size());
   for (size_t k = 0; k < g.size(); ++k) {
-    if (sizes) sizes[k] = g[k];
+    if (sizes) sizes[k] = g[k].nv;
     if (kernels) {
-      if (g[k] > 1) kernels[k] = hub::block_two_pass(h->D, pi, g[k]) ? 2 : 0;
+      if (g[k].columns >= 0) kernels[k] = g[k].columns > 0 ? 2 : 0;
+      else if (g[k].nv > 1) kernels[k] = hub::block_two_pass(h->D, pi, g[k].nv) ? 2 : 0;
       else kernels[k] = hub::apply_two_pass(h->D, pi, 1, propagate ? hub::kLanczos : hub::kPlain, false) ? 1 : 0;
     }
   }

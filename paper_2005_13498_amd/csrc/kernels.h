@@ -125,6 +125,13 @@ struct ApplyLaunch {
 // Each launcher returns the hipError_t of its launch.
 // grid_out: workgroups of the kernel that wrote the launch's partial sums.
 hipError_t launch_apply(const ApplyLaunch& L, int* grid_out = nullptr);
+// Plain products of 2 to kMaxNV vectors in the caller's layout, without
+// interleaved copies: batch_columns says how (0: one pass; 2, 4, 8: two passes
+// with that many columns per workgroup; -1: not available, the vectors go in
+// interleaved groups), launch_batch does it (L.x, L.y: the first vector,
+// L.nv vectors, L.coef).
+int batch_columns(const DevBasis& db, int prec, int nvec);
+hipError_t launch_batch(const ApplyLaunch& L, int columns);
 int apply_grid(const DevBasis& db, int prec, int nv);    // most workgroups any apply kernel writes partials for
 // Two-pass apply of blocks of nv = 2, 4, 8 interleaved vectors (a row pass
 // and a column pass, each staging its tile row or column of the whole block

@@ -570,6 +570,8 @@ using namespace dev;
 
 hipError_t launch_apply_c128(const ApplyLaunch& L, int grid, size_t lds, int* pgrid);
 hipError_t launch_apply_c64(const ApplyLaunch& L, int grid, size_t lds, int* pgrid);
+hipError_t launch_batch_c128(const ApplyLaunch& L, int nvec, int cw);
+hipError_t launch_batch_c64(const ApplyLaunch& L, int nvec, int cw);
 hipError_t launch_block_c128(const ApplyLaunch& L, int* pgrid);
 hipError_t launch_block_c64(const ApplyLaunch& L, int* pgrid);
 
@@ -685,6 +687,32 @@ hipError_t launch_apply(const ApplyLaunch& L, int* grid_out) {
   const hipError_t e = L.prec == 0 ? launch_apply_c128(L, grid, lds, &pgrid) : launch_apply_c64(L, grid, lds, &pgrid);
   if (grid_out) *grid_out = pgrid;
   return e;
+}
+
+int batch_columns(const DevBasis& db, int prec, int nvec) {
+  if (nvec < 2 || nvec > kMaxNV) return -1;
+  // One pass up to 11 sites (8 complex64 / complex128 vectors, one vs two
+  // passes: 10 sites 10.6 / 10.6 vs 13.2 / 13.6 us, 11 sites 23.4 / 29.0 vs
+  // 21.5 / 31.9; 12 sites 99.7 / 145.6 vs 68.8 / 124.0: a vector no longer
+  // fits an XCD's L2 and its up hops miss).
+  constexpr size_t kLds = 150 * 1024;
+  if (db.dim <= (1 << 18) && db.maxs_pad <= 24 && apply_lds_bytes(db, prec, 1, 1) <= kLds) return 0;
+  auto slots_ok = [](int g) { return g >= 4 && g <= 24; };
+  if (!slots_ok(db.dn_gslots) || !slots_ok(db.up_gslots) || (static_cast<size_t>(db.dim_dn) + 1) * 16 > kLds) return -1;
+  const size_t col = (static_cast<size_t>(db.dim_up) + 1) * 16;
+  const int groups = prec == 0 ? nvec : (nvec + 1) / 2;
+  // 8 columns per workgroup, one workgroup per compute unit, where that makes
+  // nearly whole rounds of the 256 (12 sites, 8 complex64 vectors, 464
+  // workgroups: 82.6 us vs 90.9 with 4 columns; 3 complex128 vectors, 348:
+  // 60.7 vs 54.5), else 4, or 2 where 4 do not fit (14 sites)
+  const int w8 = groups * ((db.dim_dn + 7) / 8), rounds = (w8 + 255) / 256;
+  if (8 * col <= kLds && 20 * w8 >= 17 * 256 * rounds) return 8;
+  return 4 * col <= kLds ? 4 : (2 * col <= kLds ? 2 : -1);
+}
+
+hipError_t launch_batch(const ApplyLaunch& L, int columns) {
+  if (L.nv < 1 || L.nv > kMaxNV) return hipErrorInvalidValue;
+  return L.prec == 0 ? launch_batch_c128(L, L.nv, columns) : launch_batch_c64(L, L.nv, columns);
 }
 
 #define HUB_NV_SWITCH(nv, CALL)                         \

@@ -1,0 +1,65 @@
+"""Plain products of several vectors in one call (hub_apply_H, nvec > 1): the
+batches in the caller's layout against the oracle's CSR matrix and against
+the single-vector kernels, at the edges of their rules: one pass and two
+passes with 8, 4 and 2 columns per workgroup, odd numbers of vectors, more
+than 8, odd dimensions (vectors at 8-byte offsets), on-site energies.  Every
+component is a sum of at most 32 hops and the diagonal, so it is within 64 eps
+|H|_inf max|x| of the reference whatever the order of the terms."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2005_13498_amd as hub
+from oracle import HubbardOracle, from_canonical
+from synth import chain, cluster_2d, random_graph, random_state, ring
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+EPS = {torch.complex128: 2.0 ** -52, torch.complex64: 2.0 ** -23}
+
+
+def _bound(B, x, dtype):
+    norm = hub.hub_basis_classes(B.handle)[2]
+    return 64 * EPS[dtype] * norm * float(torch.max(torch.abs(torch.view_as_real(x))))
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("lat,nu,nd,nvec", [(ring(6), 3, 2, 3), (ring(7), 4, 3, 2), (cluster_2d(3, 2), 3, 3, 9),
+                                            (random_graph(6, 9, 3), 3, 3, 5), (ring(5), 0, 2, 3), (ring(5), 5, 2, 2)])
+def test_batch_matches_oracle(lat, nu, nd, nvec, dtype):
+    B = hub.Basis(lat, 5.0, nu, nd, device=0)
+    ham = HubbardOracle(lat, 5.0, nu, nd)
+    X = random_state(B.dim, seed=9, nvec=nvec)
+    x = torch.tensor(X, dtype=dtype, device=DEV)
+    y = torch.full_like(x, float("nan"))
+    A = [0.3 * k - 0.4 for k in range(nvec)]
+    hub.hub_apply_H(B.handle, A, x, y)
+    for k in range(nvec):
+        v = from_canonical(x[k].cpu().numpy().astype(np.complex128), ham.states, lat.n_sites)
+        got = from_canonical(y[k].cpu().numpy().astype(np.complex128), ham.states, lat.n_sites)
+        assert np.max(np.abs(got - ham.apply(A[k], v))) <= _bound(B, x, dtype), k
+    B.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("lat,nu,nd,nvec,kernels", [
+    (ring(10), 5, 5, 8, [(8, 0)]), (ring(11), 6, 5, 11, [(8, 0), (3, 0)]), (chain(12), 5, 6, 2, [(2, 2)]),
+    (cluster_2d(3, 4), 6, 6, 3, [(3, 2)]), (cluster_2d(3, 4), 6, 6, 8, [(8, 2)]), (ring(13), 6, 7, 5, [(5, 2)]),
+    (ring(14), 7, 7, 3, None)])
+def test_batch_matches_single_vectors(lat, nu, nd, nvec, kernels, dtype):
+    B = hub.Basis(lat, 8.0, nu, nd, device=0)
+    prec = hub.HUB_C128 if dtype == torch.complex128 else hub.HUB_C64
+    plan = hub.hub_get_plan(B.handle, prec, nvec, False)
+    if kernels is None:  # 14 sites: pairs of complex64 vectors, the odd one alone
+        assert plan == ([(3, 2)] if prec == hub.HUB_C128 else [(2, 2), (1, 1)])
+    else:
+        assert plan == kernels
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x = torch.randn(nvec, B.dim, dtype=dtype, device=DEV, generator=gen)
+    y, z = torch.full_like(x, float("nan")), torch.empty_like(x)
+    A = [0.2 * k - 0.3 for k in range(nvec)]
+    hub.hub_apply_H(B.handle, A, x, y)
+    for k in range(nvec):
+        hub.hub_apply_H(B.handle, [A[k]], x[k], z[k])
+    assert float(torch.max(torch.abs(torch.view_as_real(y - z)))) <= _bound(B, x, dtype)
+    B.close()
