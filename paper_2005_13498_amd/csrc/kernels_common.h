@@ -28,15 +28,51 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk) {
   return x * q + min(x, rem) + k;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+// v of another lane by a DPP move, zero where the pattern names no lane or the
+// row is masked out.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
+  return __hiloint2double(hi, lo);
 }
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;  // DPP controls
+
+// Totals over the wavefront, the same on every lane, fixed order (every lane
+// active): shifts within the rows of 16 lanes leave a row's total in its last
+// lane, two broadcasts carry the rows' totals to lane 63.  A DPP move is an
+// ordinary VALU operand, where a shuffle waits out an LDS permute (a double
+// over six shuffles takes about 420 cycles).
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp<kRowShr + 1>(v);
+  v += dpp<kRowShr + 2>(v);
+  v += dpp<kRowShr + 4>(v);
+  v += dpp<kRowShr + 8>(v);
+  v += dpp<kRowBcast15, 0xA>(v);
+  v += dpp<kRowBcast31, 0xC>(v);
+  return lane_value(v, 63);
+}
+// Maximum of non-negative values.
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  return v;
+  v = fmax(v, dpp<kRowShr + 1>(v));
+  v = fmax(v, dpp<kRowShr + 2>(v));
+  v = fmax(v, dpp<kRowShr + 4>(v));
+  v = fmax(v, dpp<kRowShr + 8>(v));
+  v = fmax(v, dpp<kRowBcast15, 0xA>(v));
+  v = fmax(v, dpp<kRowBcast31, 0xC>(v));
+  return lane_value(v, 63);
+}
+// Total over each row of 16 lanes where every row holds the same values.
+__device__ __forceinline__ double row_total(double v) {
+  v += dpp<kRowShr + 1>(v);
+  v += dpp<kRowShr + 2>(v);
+  v += dpp<kRowShr + 4>(v);
+  v += dpp<kRowShr + 8>(v);
+  return lane_value(v, 15);
 }
 
 // Sum over the workgroup (W waves), identical on every thread, fixed order.

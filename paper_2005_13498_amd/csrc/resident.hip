@@ -20,6 +20,13 @@
 // s_k u_k.  The observables of each step's input (Eqs. (docc), (energy)) are
 // summed in FP64 from the first iteration's group sums with the coefficients
 // of the sample time.
+//
+// The one workgroup's VALU issue bounds it (71 % busy: about 226 instructions
+// an element and iteration, most of them addresses, signs and products of the
+// hops).  Sums across lanes by DPP and up sources kept as LDS offsets took 50
+// steps of 70 x 70 complex128 elements (450 iterations) from 5.64 to 5.19 ms.
+// Threads that own rows of one column and decode its down hops once need more
+// registers than 1,024 threads have, and spill: 6.35 ms.
 #include "kernels_common.h"
 #include "resident.h"
 
@@ -31,33 +38,33 @@ namespace {
 constexpr int kRT = kResidentThreads;
 constexpr int kRW = kRT / 64;
 
-// Signed sum of the four staged values one table word pair indexes; staged
-// element q is at xs[q * stride].
+// Signed sum of the four values one table word pair names, at those offsets
+// from xs.
 template <typename V>
-__device__ __forceinline__ V slot_sum4(uint2 w, const V* xs, int stride) {
+__device__ __forceinline__ V slot_sum4(uint2 w, const V* xs) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const auto sg = slot_sign<decltype(s.x)>(w, k);
-    const V t = xs[static_cast<int>(slot_src(w, k)) * stride];
+    const V t = xs[slot_src(w, k)];
     s.x = fma(sg, t.x, s.x);
     s.y = fma(sg, t.y, s.y);
   }
   return s;
 }
 
-// The same over staged columns, skipping padding entries (source dim): the
+// The same over staged columns, skipping padding entries (offset pad): the
 // lanes of a wavefront mostly share the up string and so its padding, and a
 // padding read of the zero row would cost a full-width LDS access.
 template <typename V>
-__device__ __forceinline__ V slot_sum4_skip(uint2 w, const V* xs, uint32_t dim, int stride) {
+__device__ __forceinline__ V slot_sum4_skip(uint2 w, const V* xs, uint32_t pad) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint32_t src = slot_src(w, k);
-    if (src == dim) continue;
+    if (src == pad) continue;
     const auto sg = slot_sign<decltype(s.x)>(w, k);
-    const V t = xs[static_cast<int>(src) * stride];
+    const V t = xs[src];
     s.x = fma(sg, t.x, s.x);
     s.y = fma(sg, t.y, s.y);
   }
@@ -65,15 +72,15 @@ __device__ __forceinline__ V slot_sum4_skip(uint2 w, const V* xs, uint32_t dim, 
 }
 
 // Sums over the workgroup of NQ per-thread values, identical on every
-// thread, fixed order: each wave's butterfly sum, then the kRW wave sums
-// butterflied across lanes (lane l reads wave l % kRW's sum).  lds holds
+// thread, fixed order: each wave's sum, then the kRW wave sums across the
+// lanes of a row (lane l reads wave l % kRW's sum).  lds holds
 // kRW * NQ doubles; successive calls alternate between two such buffers (the
 // caller's flip), so one barrier per call suffices: a buffer is written again
 // only after every thread has passed the next call's barrier, which follows
 // its reads of this one.
 template <int NQ>
 __device__ __forceinline__ void block_sums(double (&v)[NQ], double* lds2, int& flip) {
-  static_assert(kRW == 16, "wave sums are combined by a 16-lane butterfly");
+  static_assert(kRW == 16, "wave sums are combined across a row of 16 lanes");
   double* lds = lds2 + flip * kRW * (1 + kObsQ);
   flip ^= 1;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -85,10 +92,7 @@ __device__ __forceinline__ void block_sums(double (&v)[NQ], double* lds2, int& f
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    double r = lds[(lane & (kRW - 1)) * NQ + q];
-#pragma unroll
-    for (int off = 1; off < kRW; off <<= 1) r += __shfl_xor(r, off);
-    v[q] = r;
+    v[q] = row_total(lds[(lane & (kRW - 1)) * NQ + q]);
   }
 }
 
@@ -146,8 +150,14 @@ __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
   {
     const uint2* g1 = reinterpret_cast<const uint2*>(P.dn_tab);
     for (int i = tid; i < dd * gdn; i += kRT) tdn[i] = g1[i];
+    // up sources as offsets within a staged column, src * ld (the tile's at
+    // most 20,480 staged elements leave the sign bit free)
     const uint2* g2 = reinterpret_cast<const uint2*>(P.up_tab);
-    for (int i = tid; i < du * gup; i += kRT) tup[i] = g2[i];
+    auto scaled = [&](uint32_t h) {
+      const uint32_t lo = (h & 0x7FFFu) * ld, hi = (h >> 16 & 0x7FFFu) * ld;
+      return (h & 0x80008000u) | lo | hi << 16;
+    };
+    for (int i = tid; i < du * gup; i += kRT) tup[i] = make_uint2(scaled(g2[i].x), scaled(g2[i].y));
     for (int i = tid; i < du; i += kRT) {
       upb[i] = P.up_bits[i];
       if (has_eps) epu[i] = P.eps_up ? P.eps_up[i] : 0.0;
@@ -191,14 +201,14 @@ __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
     const V* row = xs + a * ld;
 #pragma unroll 2
     for (int g = 0; g < gdn; ++g) {
-      const V s = slot_sum4(tdn[b * gdn + g], row, 1);
+      const V s = slot_sum4(tdn[b * gdn + g], row);
       if (mid) acc = cfma(cf_dn[g], s, acc);
       if (obs) ko = cfma(of_dn[g], make_double2(s.x, s.y), ko);
     }
     const V* col = xs + b;
 #pragma unroll 2
     for (int g = 0; g < gup; ++g) {
-      const V s = slot_sum4_skip(tup[a * gup + g], col, static_cast<uint32_t>(du), ld);
+      const V s = slot_sum4_skip(tup[a * gup + g], col, static_cast<uint32_t>(du * ld));
       if (mid) acc = cfma(cf_up[g], s, acc);
       if (obs) ko = cfma(of_up[g], make_double2(s.x, s.y), ko);
     }
