@@ -2326,48 +2326,64 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
 }
 
 // ---------------------------------------------------------------------------
-// Ground state: restarted Lanczos with full reorthogonalisation, complex
-// double; the lowest Ritz pair of the tridiagonal on the host.
+// Ground state: restarted Lanczos with orthogonal vectors, complex double; the
+// lowest Ritz pair of the tridiagonal on the host.
 namespace {
 
 // Iterations enqueued between two looks at the residual (the host waits once
-// per batch; iterations past the one that converges are dropped).
-constexpr int kGsBatch = 8;
+// per batch; iterations past the one that converges are dropped).  10 sites:
+// 6.8 ms at 8 iterations, 5.5 at 16; what a batch loses of the orthogonality
+// doubles with its length at first (1e-13 of |H| = 60 at 8, 2e-13 at 16).
+constexpr int kGsBatch = 16;
+// Lanczos vectors kept: up to kGsWider times m_max within kGsWideBytes.
+constexpr int kGsWider = 4;
+constexpr int64_t kGsWideBytes = int64_t{256} << 20;
 
 // Device scalars and partial sums of a run with kmax Lanczos vectors, in the
 // lane's workspace, and the pinned host mirror of alpha, beta and coefficients.
 struct GSBufs {
   char* V = nullptr;  // kmax + 1 vectors, one after another
-  double *alpha = nullptr, *beta = nullptr, *coef = nullptr, *dotp = nullptr, *normp = nullptr;
+  hub::GsIter* it = nullptr;
+  double *coef = nullptr, *dotp = nullptr, *normp = nullptr;
   int64_t* first = nullptr;
-  double* host = nullptr;  // [2 kmax] alpha, beta; [kmax] coefficients
+  hub::GsIter* h_it = nullptr;  // pinned host copies
+  double* h_coef = nullptr;
+  bool all = false;  // orthogonalise every product against every vector
 };
 
 hub_status gs_buffers(Work& W, int kmax, GSBufs& G) {
   const size_t k = static_cast<size_t>(kmax) + 2;
-  const size_t dbl = 3 * k + 2 * k * hub::kGsDotRows + 2 * hub::kGsNormRows;
+  const size_t dbl = 5 * k + 2 * k * hub::kGsDotRows + 2 * hub::kGsNormRows;
   if (dbl * sizeof(double) > W.gs_bytes) {
     if (W.gs) HUB_HIP(hipFree(W.gs));
     if (W.h_gs) HUB_HIP(hipHostFree(W.h_gs));
     W.gs = W.h_gs = nullptr;
     W.gs_bytes = 0;
     HUB_HIP(hipMalloc(reinterpret_cast<void**>(&W.gs), dbl * sizeof(double)));
-    HUB_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.h_gs), 3 * k * sizeof(double), hipHostMallocDefault));
+    HUB_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.h_gs), 5 * k * sizeof(double), hipHostMallocDefault));
     W.gs_bytes = dbl * sizeof(double);
   }
   G.V = static_cast<char*>(W.slots);
-  G.alpha = W.gs;
-  G.beta = G.alpha + k;
-  G.coef = G.beta + k;
+  G.it = reinterpret_cast<hub::GsIter*>(W.gs);
+  G.coef = W.gs + 4 * k;
   G.dotp = G.coef + k;
   G.normp = G.dotp + 2 * k * hub::kGsDotRows;
   G.first = reinterpret_cast<int64_t*>(G.normp + hub::kGsNormRows);
-  G.host = W.h_gs;
+  G.h_it = reinterpret_cast<hub::GsIter*>(W.h_gs);
+  G.h_coef = W.h_gs + 4 * k;
   return HUB_OK;
 }
 
 // Up to kmax Lanczos iterations from the normalised V[0]; lowest Ritz value
-// in ritz, its vector's coefficients in svec.
+// in ritz, its vector's coefficients (of the stored vectors) in svec.
+//
+// A product is orthogonalised against the vectors it overlaps with by the
+// three-term recurrence, and the last two of a batch against every vector,
+// which the next batch then starts from as if all had been.  What those two
+// passes took out (GsIter::loss) is the orthogonality lost since and is how
+// far H V = V T + r is off: it counts in the residual, and a batch that lost
+// more than a quarter of the tolerance is done again with every product
+// orthogonalised against every vector, as are the batches after it.
 hub_status gs_lanczos(hub_basis h, double A, hipStream_t st, GSBufs& G, int kmax, const void* deflate,
                       double tol_res, double& ritz, std::vector<double>& svec, double& resid) {
   const int64_t dim = h->D.dim;
@@ -2375,12 +2391,13 @@ hub_status gs_lanczos(hub_basis h, double A, hipStream_t st, GSBufs& G, int kmax
   coef_for(h->B, A, cf.data());
   const size_t vb = static_cast<size_t>(dim) * 16;
   const int most = static_cast<int>(std::min<int64_t>(kmax, dim - (deflate ? 1 : 0)));
-  double* const al = G.host;
-  double* const be = G.host + kmax;
-  int m = 0;
+  const double most_loss = 0.25 * std::min(tol_res, 1e-9 * h->B.norm_inf);
+  const double2* const V = reinterpret_cast<const double2*>(G.V);
+  std::vector<double> al, be, off;
   resid = INFINITY;
   for (int j = 0; j < most;) {
     const int end = std::min(most, j + kGsBatch);
+    int rows = 0, nrows = 0;
     for (int q = j; q < end; ++q) {
       double2* w = reinterpret_cast<double2*>(G.V + (q + 1) * vb);
       hub::ApplyLaunch L{};
@@ -2394,30 +2411,37 @@ hub_status gs_lanczos(hub_basis h, double A, hipStream_t st, GSBufs& G, int kmax
       L.y = w;
       L.stream = st;
       HUB_HIP(hub::launch_apply(L));
-      // first the vectors H v_q overlaps with by the three-term recurrence,
-      // then all of them for the rounding errors
-      int rows = 0, nrows = 0;
-      for (int pass = 0; pass < 2; ++pass) {
+      for (int pass = 0; pass < (G.all || q >= end - 2 ? 2 : 1); ++pass) {
         const int k0 = pass == 0 ? std::max(0, q - 1) : 0;
-        const hub::GsBasis B{static_cast<const double2*>(deflate), reinterpret_cast<const double2*>(G.V + k0 * vb),
-                             dim, q + 1 - k0 + (deflate ? 1 : 0)};
-        HUB_HIP(hub::launch_gs_dot(B, w, G.dotp, &rows, st));
-        HUB_HIP(hub::launch_gs_subtract(B, w, G.dotp, rows, G.normp, &nrows, G.alpha + q, pass > 0, st));
+        const hub::GsBasis B{static_cast<const double2*>(deflate), V, G.it, dim, k0, q + 1 - k0 + (deflate ? 1 : 0)};
+        HUB_HIP(hub::launch_gs_dot(B, w, G.dotp, &rows, G.normp, nrows, pass == 0 && q > j ? G.it + q - 1 : nullptr,
+                                   st));
+        HUB_HIP(hub::launch_gs_subtract(B, w, G.dotp, rows, G.normp, &nrows, G.it + q, pass > 0, st));
       }
-      HUB_HIP(hub::launch_gs_scale(dim, w, G.normp, nrows, w, nullptr, G.beta + q, st));
     }
-    HUB_HIP(hipMemcpyAsync(al + j, G.alpha + j, (end - j) * sizeof(double), hipMemcpyDeviceToHost, st));
-    HUB_HIP(hipMemcpyAsync(be + j, G.beta + j, (end - j) * sizeof(double), hipMemcpyDeviceToHost, st));
+    HUB_HIP(hub::launch_gs_beta(G.normp, nrows, G.it + end - 1, st));
+    HUB_HIP(hipMemcpyAsync(G.h_it + j, G.it + j, (end - j) * sizeof(hub::GsIter), hipMemcpyDeviceToHost, st));
     HUB_HIP(hipStreamSynchronize(st));
-    m = end;
+    const double lost = end - j < 2 ? G.h_it[end - 1].loss : std::max(G.h_it[end - 2].loss, G.h_it[end - 1].loss);
+    if (!G.all && !(lost <= most_loss)) {
+      G.all = true;
+      continue;
+    }
     bool closed = false;  // an invariant subspace: the vectors after it are void
-    for (int q = j; q < end && !closed; ++q)
-      if (be[q] < 1e-14 * h->B.norm_inf) {
-        m = q + 1;
-        closed = true;
-      }
-    ritz = hub::tridiag_lowest(m, al, be, svec);
+    for (int q = j; q < end && !closed; ++q) {
+      al.push_back(G.h_it[q].alpha);
+      be.push_back(G.h_it[q].beta);
+      off.push_back(!G.all && q >= end - 2 ? G.h_it[q].loss : 0.0);
+      closed = be[q] < 1e-14 * h->B.norm_inf;
+    }
+    const int m = static_cast<int>(al.size());
+    ritz = hub::tridiag_lowest(m, al.data(), be.data(), svec);
+    double rest = 0.0;
+    for (int q = 0; q < m; ++q) rest += off[q] * std::fabs(svec[q]);
     resid = be[m - 1] * std::fabs(svec[m - 1]);
+    if (resid < tol_res && resid + rest >= tol_res) G.all = true;  // what was lost is all that is left
+    resid += rest;
+    for (int q = 1; q < m; ++q) svec[q] *= G.h_it[q - 1].inv;
     if (resid < tol_res || closed) break;
     j = end;
   }
@@ -2425,17 +2449,15 @@ hub_status gs_lanczos(hub_basis h, double A, hipStream_t st, GSBufs& G, int kmax
 }
 
 // out = sum_i s_i V[i], normalised, also to out2 if given
-hub_status gs_ritz_vector(hub_basis h, hipStream_t st, GSBufs& G, int kmax, const std::vector<double>& s, void* out,
-                          void* out2) {
+hub_status gs_ritz_vector(hub_basis h, hipStream_t st, GSBufs& G, const std::vector<double>& s, void* out, void* out2) {
   const int m = static_cast<int>(s.size());
-  double* const hc = G.host + 2 * kmax;
-  std::copy(s.begin(), s.end(), hc);
-  HUB_HIP(hipMemcpyAsync(G.coef, hc, m * sizeof(double), hipMemcpyHostToDevice, st));
+  std::copy(s.begin(), s.end(), G.h_coef);
+  HUB_HIP(hipMemcpyAsync(G.coef, G.h_coef, m * sizeof(double), hipMemcpyHostToDevice, st));
   int nrows = 0;
   HUB_HIP(hub::launch_gs_combine(reinterpret_cast<const double2*>(G.V), h->D.dim, m, G.coef,
                                  static_cast<double2*>(out), G.normp, &nrows, st));
   HUB_HIP(hub::launch_gs_scale(h->D.dim, static_cast<const double2*>(out), G.normp, nrows,
-                               static_cast<double2*>(out), static_cast<double2*>(out2), nullptr, st));
+                               static_cast<double2*>(out), static_cast<double2*>(out2), st));
   return HUB_OK;
 }
 
@@ -2453,8 +2475,17 @@ hub_status hub_ground_state(hub_basis h, double A, const hub_krylov_opts* opts, 
   if (kmax < 2) return fail(HUB_E_INVALID, "opts.m_max must be >= 2");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t dim = h->D.dim;
-  kmax = static_cast<int>(std::min<int64_t>(kmax, dim));
+  // vectors kept between restarts: a restart costs the Krylov space about half
+  // of its progress, so up to kGsWider m_max of them where that is little
+  // memory (10 sites: 209 + 119 iterations with restarts at 60, 144 + 96 without)
+  const int64_t vecs = kGsWideBytes / (dim * 16) - 1;
+  const int most = static_cast<int>(std::min<int64_t>(kmax, dim));
+  kmax = static_cast<int>(std::min({dim, std::max<int64_t>(kmax, vecs), static_cast<int64_t>(kmax) * kGsWider}));
   s = ensure_workspace(h, static_cast<size_t>(dim) * 16, kmax + 1, 0);
+  if (s != HUB_OK && kmax > most) {  // no memory for the wider space
+    kmax = most;
+    s = ensure_workspace(h, static_cast<size_t>(dim) * 16, kmax + 1, 0);
+  }
   if (s != HUB_OK) return s;
   GSBufs G;
   s = gs_buffers(h->w, kmax, G);
@@ -2465,14 +2496,14 @@ hub_status hub_ground_state(hub_basis h, double A, const hub_krylov_opts* opts, 
   const double tol_res = tol * h->B.norm_inf;
   int nrows = 0;
   HUB_HIP(hub::launch_gs_start(dim, 0x13498ULL, V0, G.normp, &nrows, st));
-  HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
+  HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, st));
   std::vector<double> svec;
   double resid = INFINITY, e0 = 0.0;
   bool conv = false;
-  for (int restart = 0; restart < 200 && !conv; ++restart) {
+  for (int restart = 0; restart * kmax < 200 * most && !conv; ++restart) {
     s = gs_lanczos(h, A, st, G, kmax, nullptr, tol_res, e0, svec, resid);
     if (s != HUB_OK) return s;
-    s = gs_ritz_vector(h, st, G, kmax, svec, psi, V0);
+    s = gs_ritz_vector(h, st, G, svec, psi, V0);
     if (s != HUB_OK) return s;
     conv = resid < tol_res;
   }
@@ -2487,20 +2518,21 @@ hub_status hub_ground_state(hub_basis h, double A, const hub_krylov_opts* opts, 
   double g = INFINITY;
   if (dim > 1) {
     HUB_HIP(hub::launch_gs_start(dim, 0x5eedULL, V0, G.normp, &nrows, st));
-    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
+    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, st));
     // remove the ground-state component of the start vector
-    const hub::GsBasis B{nullptr, psi, dim, 1};
+    const hub::GsBasis B{nullptr, psi, G.it, dim, 0, 1};
     int rows = 0;
-    HUB_HIP(hub::launch_gs_dot(B, V0, G.dotp, &rows, st));
-    HUB_HIP(hub::launch_gs_subtract(B, V0, G.dotp, rows, G.normp, &nrows, G.alpha, false, st));
-    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, nullptr, st));
+    HUB_HIP(hub::launch_gs_dot(B, V0, G.dotp, &rows, nullptr, 0, nullptr, st));
+    HUB_HIP(hub::launch_gs_subtract(B, V0, G.dotp, rows, G.normp, &nrows, G.it, false, st));
+    HUB_HIP(hub::launch_gs_scale(dim, V0, G.normp, nrows, V0, nullptr, st));
     double r1 = INFINITY, e1 = 0.0;
-    for (int restart = 0; restart < 20; ++restart) {
+    G.all = false;
+    for (int restart = 0; restart * kmax < 20 * most; ++restart) {
       s = gs_lanczos(h, A, st, G, kmax, v_out, 1e-6 * h->B.norm_inf, e1, svec, r1);
       if (s != HUB_OK) return s;
       if (r1 < 1e-6 * h->B.norm_inf) break;
       // restart from the Ritz vector, formed in the spare slot
-      s = gs_ritz_vector(h, st, G, kmax, svec, G.V + static_cast<size_t>(kmax) * dim * 16, V0);
+      s = gs_ritz_vector(h, st, G, svec, G.V + static_cast<size_t>(kmax) * dim * 16, V0);
       if (s != HUB_OK) return s;
     }
     g = e1 - e0;

@@ -1,18 +1,19 @@
-// Ground-state Lanczos kernels: complex double, one vector, full
-// reorthogonalisation.  An iteration is the H v kernels and then five
-// launches, with no host wait in between: inner products and subtraction of
-// the two vectors that H v overlaps with (and of the deflated one), the same
-// against every vector, with |w|^2, and the normalisation.  The first pair
-// takes the large components out, so the second leaves w orthogonal to
-// rounding, as two passes over every vector did, at half their traffic.  Inner products of small sectors are latency-bound, so the
-// (vector, chunk) pairs are spread over workgroups and the subtraction adds
-// the few partial rows itself and reads the vectors in independent groups of
-// eight.  10 sites (63,504
-// states): the subtraction of up to 60 vectors took 56 us on average when each
-// vector's load waited for the last, 8 us now (4 TB/s out of the caches); a
-// whole ground state with its gap 192 ms with a dense eigenproblem, three
-// waits on the host per iteration and start vectors from the host, 13.2 ms
-// now.
+// Ground-state Lanczos kernels: complex double, one vector, orthogonal to
+// rounding.  An iteration is the H v kernels and two launches, with no host
+// wait in between: inner products and subtraction of the two vectors that H v
+// overlaps with (and of the deflated one).  The last two iterations of a batch
+// have the same two launches once more against every vector, which takes out
+// what the three-term recurrence let grow back; gs_lanczos checks how much
+// that was.  Vectors are stored as subtracted, with their norms beside them.
+// Inner products of small sectors are latency-bound, so the (vector, chunk)
+// pairs are spread over workgroups and the subtraction adds the few partial
+// rows itself and reads the vectors in independent groups of eight.
+// 10 sites (63,504 states): the subtraction of up to 60 vectors took 56 us on
+// average when each vector's load waited for the last, 8 us now (4 TB/s out of
+// the caches).  A whole ground state with its gap took 192 ms with a dense
+// eigenproblem, three waits on the host per iteration and start vectors from
+// the host, 12.6 ms with every product against every vector of up to 60, and
+// 5.5 ms now (240 iterations, whose three launches of 4 to 6 us bound it).
 #include "ground.h"
 
 #include <algorithm>
@@ -28,9 +29,25 @@ constexpr int kDotVecs = 4;   // vectors per inner-product workgroup
 constexpr int kSubVecs = 8;   // vectors whose loads a subtraction issues together
 constexpr int kSubMost = 1024;  // vectors of one subtraction launch (coefficients in LDS)
 
+__device__ __forceinline__ int gs_index(const GsBasis& B, int k) {  // in V, or -1: deflate
+  return B.deflate ? (k == 0 ? -1 : B.first + k - 1) : B.first + k;
+}
 __device__ __forceinline__ const double2* gs_vec(const GsBasis& B, int k) {
-  if (B.deflate) return k == 0 ? B.deflate : B.V + static_cast<int64_t>(k - 1) * B.dim;
-  return B.V + static_cast<int64_t>(k) * B.dim;
+  const int i = gs_index(B, k);
+  return i < 0 ? B.deflate : B.V + static_cast<int64_t>(i) * B.dim;
+}
+__device__ __forceinline__ double gs_inv(const GsBasis& B, int k) {
+  const int i = gs_index(B, k);
+  return i > 0 ? B.it[i - 1].inv : 1.0;
+}
+
+// beta = sqrt(sum of normp) and its inverse, by a workgroup.
+__device__ __forceinline__ void gs_beta(const double* normp, int nrows, GsIter* it, double* red) {
+  const double n = sqrt(reduce_column(normp, nrows, 1, 0, red));
+  if (threadIdx.x == 0) {
+    it->beta = n;
+    it->inv = n > 0.0 ? 1.0 / n : 0.0;
+  }
 }
 
 // Workgroup sum of |w|^2 into normp[blockIdx.x].
@@ -42,8 +59,13 @@ __device__ __forceinline__ void store_norm(double n2, double* red, double* normp
 }  // namespace
 
 __global__ __launch_bounds__(kBlock) void k_gs_dot(GsBasis B, const double2* __restrict__ w, int64_t len,
-                                                   double* dotp) {
+                                                   double* dotp, const double* __restrict__ normp, int nrows,
+                                                   GsIter* prev) {
   __shared__ double red[kWaves * 2 * kDotVecs];
+  if (prev && blockIdx.x == 0 && blockIdx.y == 0) {  // the subtraction after this launch needs it first
+    gs_beta(normp, nrows, prev, red);
+    __syncthreads();
+  }
   const int k0 = blockIdx.y * kDotVecs, K = min(kDotVecs, B.nb - k0);
   const double2* vp[kDotVecs];
 #pragma unroll
@@ -83,21 +105,32 @@ __global__ __launch_bounds__(kBlock) void k_gs_dot(GsBasis B, const double2* __r
 // wavefronts per SIMD waiting on loads.
 __global__ __launch_bounds__(kBlock) void k_gs_subtract(GsBasis B, int k0, int kn, double2* __restrict__ w,
                                                         const double* __restrict__ dotp, int rows, double* normp,
-                                                        double* alpha, int add) {
+                                                        GsIter* it, int all) {
   __shared__ double2 part[kWaves][64];
   extern __shared__ double sc[];  // [2 kn], padded to a whole group of vectors
   const int groups = (kn + kSubVecs - 1) / kSubVecs;
+  const bool last = k0 + kn == B.nb;
+  const double inv = gs_inv(B, B.nb - 1);
+  const double f = all || k0 > 0 ? 1.0 : inv;  // w's factor: once
+  double l2 = 0.0;
   for (int t = threadIdx.x; t < 2 * kSubVecs * groups; t += kBlock) {
     double s = 0.0;
     if (t < 2 * kn) {
 #pragma unroll 8
       for (int r = 0; r < rows; ++r) s += dotp[static_cast<size_t>(r) * 2 * B.nb + 2 * k0 + t];
+      const double ik = gs_inv(B, k0 + (t >> 1));
+      s *= ik * (all ? 1.0 : inv);  // <v_k, f w>
+      l2 += s * s;
+      if (last && t == 2 * (kn - 1) && blockIdx.x == 0) it->alpha = (all ? it->alpha : 0.0) + s;
+      s *= ik;
     }
     sc[t] = s;
   }
+  if (all && blockIdx.x == 0) {
+    l2 = block_sum(l2, &part[0][0].x);
+    if (threadIdx.x == 0) it->loss = k0 > 0 ? hypot(it->loss, sqrt(l2)) : sqrt(l2);
+  }
   __syncthreads();
-  const bool last = k0 + kn == B.nb;
-  if (last && blockIdx.x == 0 && threadIdx.x == 0) *alpha = (add ? *alpha : 0.0) + sc[2 * (kn - 1)];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   double n2 = 0.0;
   for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * 64; i0 < B.dim; i0 += static_cast<int64_t>(gridDim.x) * 64) {
@@ -120,6 +153,8 @@ __global__ __launch_bounds__(kBlock) void k_gs_subtract(GsBasis B, int k0, int k
     __syncthreads();
     if (wv == 0 && i < B.dim) {
       double2 o = w[i];
+      o.x *= f;
+      o.y *= f;
 #pragma unroll
       for (int q = 0; q < kWaves; ++q) {
         o.x -= part[q][lane].x;
@@ -155,11 +190,15 @@ __global__ __launch_bounds__(kBlock) void k_gs_combine(const double2* __restrict
   store_norm(n2, red, normp);
 }
 
+__global__ __launch_bounds__(kBlock) void k_gs_beta(const double* __restrict__ normp, int nrows, GsIter* it) {
+  __shared__ double red[kWaves];
+  gs_beta(normp, nrows, it, red);
+}
+
 __global__ __launch_bounds__(kBlock) void k_gs_scale(int64_t dim, const double2* x, const double* __restrict__ normp,
-                                                     int nrows, double2* dst, double2* dst2, double* norm) {
+                                                     int nrows, double2* dst, double2* dst2) {
   __shared__ double red[kWaves];
   const double n = sqrt(reduce_column(normp, nrows, 1, 0, red));
-  if (norm && blockIdx.x == 0 && threadIdx.x == 0) *norm = n;
   const double f = n > 0.0 ? 1.0 / n : 0.0;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < dim;
        i += static_cast<int64_t>(gridDim.x) * kBlock) {
@@ -276,25 +315,26 @@ static int gs_grid(int64_t dim) {
   return static_cast<int>(std::min<int64_t>((dim + kBlock - 1) / kBlock, kGsNormRows));
 }
 
-hipError_t launch_gs_dot(const GsBasis& B, const double2* w, double* dotp, int* rows, hipStream_t s) {
+hipError_t launch_gs_dot(const GsBasis& B, const double2* w, double* dotp, int* rows, const double* normp, int nrows,
+                         GsIter* prev, hipStream_t s) {
   // about 512 workgroups of at least 1,024 elements
   const int groups = (B.nb + kDotVecs - 1) / kDotVecs;
   const int64_t most = std::max<int64_t>(1, (B.dim + 1023) / 1024);
   const int c = static_cast<int>(std::min<int64_t>({most, kGsDotRows, std::max(1, 512 / groups)}));
   const int64_t len = ((B.dim + c - 1) / c + kBlock - 1) / kBlock * kBlock;
-  hipLaunchKernelGGL(k_gs_dot, dim3(c, groups), dim3(kBlock), 0, s, B, w, len, dotp);
+  hipLaunchKernelGGL(k_gs_dot, dim3(c, groups), dim3(kBlock), 0, s, B, w, len, dotp, normp, nrows, prev);
   *rows = c;
   return hipGetLastError();
 }
 
 hipError_t launch_gs_subtract(const GsBasis& B, double2* w, const double* dotp, int rows, double* normp, int* nrows,
-                              double* alpha, bool add, hipStream_t s) {
+                              GsIter* it, bool all, hipStream_t s) {
   const int grid = static_cast<int>(std::min<int64_t>((B.dim + 63) / 64, kGsNormRows));
   for (int k0 = 0; k0 < B.nb; k0 += kSubMost) {
     const int kn = std::min(kSubMost, B.nb - k0);
     const size_t lds = static_cast<size_t>((kn + kSubVecs - 1) / kSubVecs) * kSubVecs * 2 * sizeof(double);
-    hipLaunchKernelGGL(k_gs_subtract, dim3(grid), dim3(kBlock), lds, s, B, k0, kn, w, dotp, rows, normp, alpha,
-                       add ? 1 : 0);
+    hipLaunchKernelGGL(k_gs_subtract, dim3(grid), dim3(kBlock), lds, s, B, k0, kn, w, dotp, rows, normp, it,
+                       all ? 1 : 0);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -309,9 +349,14 @@ hipError_t launch_gs_combine(const double2* V, int64_t dim, int m, const double*
   return hipGetLastError();
 }
 
+hipError_t launch_gs_beta(const double* normp, int nrows, GsIter* it, hipStream_t s) {
+  hipLaunchKernelGGL(k_gs_beta, dim3(1), dim3(kBlock), 0, s, normp, nrows, it);
+  return hipGetLastError();
+}
+
 hipError_t launch_gs_scale(int64_t dim, const double2* x, const double* normp, int nrows, double2* dst, double2* dst2,
-                           double* norm, hipStream_t s) {
-  hipLaunchKernelGGL(k_gs_scale, dim3(gs_grid(dim)), dim3(kBlock), 0, s, dim, x, normp, nrows, dst, dst2, norm);
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_gs_scale, dim3(gs_grid(dim)), dim3(kBlock), 0, s, dim, x, normp, nrows, dst, dst2);
   return hipGetLastError();
 }
 
