@@ -452,7 +452,9 @@ hub_status hub_set_schedule(hub_basis basis, int32_t chunk, int32_t margin);
  *           strings fit in LDS (a row pass for the diagonal and the down
  *           hops, then a column pass that stages those columns, as +x and
  *           -x or, when two copies do not fit, as +x with the sign taken
- *           from the hop's index, and adds the up hops);
+ *           from the hop's index, and adds the up hops), and for plain
+ *           applies of vectors larger than 32 MiB, whose column pass gathers
+ *           from global memory in an order that the L2s hold;
  *   path -1 (default): two passes when they fit and the vector is larger
  *           than 4 MiB, one pass otherwise.
  * Blocks of 2, 4 or 8 vectors (paths 1 and -1) run the two-pass block

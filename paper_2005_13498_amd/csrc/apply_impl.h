@@ -663,6 +663,218 @@ hipError_t colpass_s(const ApplyLaunch& L, int* pgrid) {
                                      : colpass_w<R, MODE, FUSE, false, kColW>(L, pgrid);
 }
 
+// Plain products of one vector larger than the eight L2s, in two passes
+// without staging a column.  In one pass a row's up hops read eight other rows
+// that no L2 holds, 9.5 vectors of traffic.  The column pass here takes 64
+// columns (complex64: 128) of every row in turn, in the order of the rows, so
+// that the source rows' segments stay in the L2 of the XCD that works on those
+// columns.  A wavefront owns one row's segment: its hops, source addresses and
+// coefficients are the same on every lane and live in scalar registers.  What
+// is left is bound by fabric traffic: 16 sites, complex128, 2.38 ms for x 2.3
+// times, y in and out at 5.6 TB/s; 64 lanes over 8 rows of 8 columns read x
+// once by count but twice by lines (a row is no whole number of them), 3.6 ms.
+// The terms are added in the one-pass kernel's order: bit-identical.
+struct GatherArgs {
+  int dim_up, dim_dn, row_groups;
+  const int32_t* up_ptr;
+  const uint32_t* up_hops;
+  double up_coef[2 * 2 * kMaxClasses];  // [class][sign] complex
+  const void* x;
+  void* y;  // in: row-pass partial product, out: result
+};
+
+constexpr int kGatherWaves = 4;  // rows per workgroup
+template <typename R>
+constexpr int kGatherCols = sizeof(R) == 8 ? 1 : 2;  // columns per lane, 64 apart
+
+// STREAM: y passes the caches by, which leaves them to x.  With vectors over
+// 64 MiB only: below, y is still in the Infinity Cache from the row pass (47 MB,
+// 13 sites complex128: 60 us against 65 streamed; 94 MB, 14 sites complex64:
+// 157 against 140).
+template <bool STREAM, typename V>
+__device__ __forceinline__ V stream_load(const V* q) {
+  if (!STREAM) return *q;
+  typedef decltype(V().x) S;
+  typedef S vec __attribute__((ext_vector_type(2)));
+  const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(q));
+  return V{v.x, v.y};
+}
+template <bool STREAM, typename V>
+__device__ __forceinline__ void stream_store(V* q, V t) {
+  if (!STREAM) {
+    *q = t;
+    return;
+  }
+  typedef decltype(V().x) S;
+  typedef S vec __attribute__((ext_vector_type(2)));
+  vec v;
+  v.x = t.x;
+  v.y = t.y;
+  __builtin_nontemporal_store(v, reinterpret_cast<vec*>(q));
+}
+
+template <typename R, bool STREAM>
+__global__ __launch_bounds__(64 * kGatherWaves) void k_colgather(GatherArgs p) {
+  using V = typename CT<R>::T;
+  constexpr int C = kGatherCols<R>, kG = 8;
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  const int a = __builtin_amdgcn_readfirstlane(lb % p.row_groups * kGatherWaves + (threadIdx.x >> 6));
+  const int b = lb / p.row_groups * (64 * C) + (threadIdx.x & 63);
+  if (a >= p.dim_up || b >= p.dim_dn) return;
+  const V* __restrict__ x = static_cast<const V*>(p.x) + b;
+  V* y = static_cast<V*>(p.y) + static_cast<size_t>(a) * p.dim_dn + b;
+  const int h0 = p.up_ptr[a], hn = p.up_ptr[a + 1];
+  bool in[C];
+  V acc[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    in[c] = b + 64 * c < p.dim_dn;
+    acc[c] = in[c] ? stream_load<STREAM>(y + 64 * c) : V{0, 0};
+  }
+  for (int h = h0; h < hn; h += kG) {
+    uint32_t e[kG];
+    V t[kG][C];
+#pragma unroll
+    for (int k = 0; k < kG; ++k) e[k] = p.up_hops[min(h + k, hn - 1)];
+#pragma unroll
+    for (int k = 0; k < kG; ++k) {
+      if (h + k >= hn) break;
+      const V* row = x + static_cast<size_t>(e[k] & 0xFFFFu) * p.dim_dn;
+#pragma unroll
+      for (int c = 0; c < C; ++c) t[k][c] = in[c] ? row[64 * c] : V{0, 0};
+    }
+#pragma unroll
+    for (int k = 0; k < kG; ++k) {
+      if (h + k >= hn) break;
+      const int cs = static_cast<int>(((e[k] >> 16) & 0xFFu) * 2u + (e[k] >> 31));
+      const V cf = V{static_cast<R>(p.up_coef[2 * cs]), static_cast<R>(p.up_coef[2 * cs + 1])};
+#pragma unroll
+      for (int c = 0; c < C; ++c) acc[c] = cfma(cf, t[k][c], acc[c]);
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (in[c]) stream_store<STREAM>(y + 64 * c, acc[c]);
+}
+
+template <typename R>
+hipError_t colgather(const ApplyLaunch& L) {
+  const DevBasis& db = *L.db;
+  GatherArgs p;
+  p.dim_up = db.dim_up;
+  p.dim_dn = db.dim_dn;
+  p.up_ptr = db.up_ptr;
+  p.up_hops = db.up_hops;
+  pack_signed_coefs(L.coef, db.nc, kMaxClasses, p.up_coef);
+  p.x = L.x;
+  p.y = L.y;
+  const int w = 64 * kGatherCols<R>;
+  p.row_groups = (db.dim_up + kGatherWaves - 1) / kGatherWaves;
+  const int grid = (db.dim_dn + w - 1) / w * p.row_groups;
+  const bool stream = static_cast<double>(db.dim) * sizeof(typename CT<R>::T) > 64.0 * 1024 * 1024;
+  return launch_ev(stream ? k_colgather<R, true> : k_colgather<R, false>, grid, 64 * kGatherWaves, 0, L.stream,
+                   L.ev2_start, L.ev2_stop, p);
+}
+
+// Its row pass where a row does not fit LDS (15 and 16 sites): diagonal and
+// down hops, whose sources are gathered from the row in global memory.  A
+// workgroup takes 256 columns of kRowLoop rows, so a column's table is read
+// once for all of them, and the workgroups of the same rows run side by side
+// on one XCD, whose L2 then holds those rows (one workgroup per row had 64
+// rows in flight on an L2 of 20).  The L1's rate bounds it, 34 64-byte
+// accesses per gather of a wavefront: 16 sites, complex128, 2.01 ms, 2.55 with
+// a workgroup per row; with half the loads in flight and twice the wavefronts
+// 2.32.
+struct RowArgs {
+  int dim_up, dim_dn, chunks;
+  double U;
+  const uint32_t* up_bits;
+  const uint32_t* dn_bits;
+  const double* eps_up;
+  const double* eps_dn;
+  const uint16_t* dn_tab;  // [dim_dn][4 G], src | sign << 15, pad dim_dn
+  double group_coef[2 * 8];
+  const void* x;
+  void* y;
+};
+
+constexpr int kRowLoop = 4;
+
+template <typename R, int G>
+__global__ __launch_bounds__(kBlock) void k_rowgather(RowArgs p) {
+  using V = typename CT<R>::T;
+  const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = lb % p.chunks * kBlock + threadIdx.x;
+  if (b >= p.dim_dn) return;
+  const uint32_t dd = static_cast<uint32_t>(p.dim_dn);
+  const uint2* tab2 = reinterpret_cast<const uint2*>(p.dn_tab);
+  uint2 w[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) w[g] = tab2[static_cast<size_t>(b) * G + g];
+  const uint32_t db = p.dn_bits[b];
+  const double eb = p.eps_dn ? p.eps_dn[b] : 0.0;
+  const int a0 = lb / p.chunks * kRowLoop, a1 = min(p.dim_up, a0 + kRowLoop);
+  for (int a = a0; a < a1; ++a) {
+    const V* __restrict__ row = static_cast<const V*>(p.x) + static_cast<size_t>(a) * dd;
+    const V xv = row[b];
+    V t[4 * G];
+#pragma unroll
+    for (int s = 0; s < 4 * G; ++s) {
+      const uint32_t src = slot_src(w[s >> 2], s & 3);
+      t[s] = V{0, 0};
+      if (src != dd) t[s] = row[src];
+    }
+    const double nd = static_cast<double>(__popc(p.up_bits[a] & db));
+    const double dg = p.U * nd + (p.eps_up ? p.eps_up[a] : 0.0) + eb;
+    V acc = V{static_cast<R>(dg) * xv.x, static_cast<R>(dg) * xv.y};
+#pragma unroll
+    for (int s = 0; s < 4 * G; ++s) {
+      const R sg = slot_sign<R>(w[s >> 2], s & 3);
+      const V cf = V{static_cast<R>(p.group_coef[2 * (s >> 2)]), static_cast<R>(p.group_coef[2 * (s >> 2) + 1])};
+      acc = cfma(cf, V{sg * t[s].x, sg * t[s].y}, acc);
+    }
+    static_cast<V*>(p.y)[static_cast<size_t>(a) * dd + b] = acc;
+  }
+}
+
+template <typename R, int G>
+hipError_t rowgather_t(const ApplyLaunch& L) {
+  const DevBasis& db = *L.db;
+  RowArgs p;
+  p.dim_up = db.dim_up;
+  p.dim_dn = db.dim_dn;
+  p.chunks = (db.dim_dn + kBlock - 1) / kBlock;
+  p.U = db.U;
+  p.up_bits = db.up_bits;
+  p.dn_bits = db.dn_bits;
+  p.eps_up = db.eps_up;
+  p.eps_dn = db.eps_dn;
+  p.dn_tab = db.dn_tabg;
+  for (int g = 0; g < G; ++g) {
+    p.group_coef[2 * g] = L.coef[2 * db.dn_gclass[g]];
+    p.group_coef[2 * g + 1] = L.coef[2 * db.dn_gclass[g] + 1];
+  }
+  p.x = L.x;
+  p.y = L.y;
+  const int grid = p.chunks * ((db.dim_up + kRowLoop - 1) / kRowLoop);
+  return launch_ev(k_rowgather<R, G>, grid, kBlock, 0, L.stream, L.ev_start, L.ev_stop, p);
+}
+
+template <typename R>
+hipError_t rowgather(const ApplyLaunch& L) {
+  switch (L.db->dn_gslots) {
+    case 4: return rowgather_t<R, 1>(L);
+    case 8: return rowgather_t<R, 2>(L);
+    case 12: return rowgather_t<R, 3>(L);
+    case 16: return rowgather_t<R, 4>(L);
+    case 20: return rowgather_t<R, 5>(L);
+    case 24: return rowgather_t<R, 6>(L);
+    case 28: return rowgather_t<R, 7>(L);
+    case 32: return rowgather_t<R, 8>(L);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 template <typename R, int MODE, int BLK>
 hipError_t apply_gdn_s(const ApplyLaunch& L, int grid) {
   switch (L.db->maxs_pad) {
@@ -683,19 +895,26 @@ template <typename R, int NV>
 hipError_t apply_mode(const ApplyLaunch& L, int grid, size_t lds, int* pgrid) {
   if (pgrid) *pgrid = grid;
   if constexpr (NV == 1) {
+    const bool two = apply_two_pass(*L.db, L.prec, 1, L.mode, L.obs);
+    const bool gather = two && L.mode == kPlain && apply_gathers(*L.db, L.prec);
     if (apply_global_rows(*L.db, L.prec, 1)) {  // a row does not fit LDS
+      if (gather) {
+        const hipError_t e = rowgather<R>(L);
+        return e != hipSuccess ? e : colgather<R>(L);
+      }
       if (L.mode == kPlain) return apply_gdn_s<R, M_PLAIN, 1024>(L, grid);
       if (L.mode == kObsOnly) return apply_gdn_s<R, M_OBS, 256>(L, grid);
       if (L.obs) return apply_gdn_s<R, M_LANCZOS_OBS, 256>(L, grid);
       return apply_gdn_s<R, M_LANCZOS, 1024>(L, grid);
     }
     const bool longrow = L.db->dim_dn >= kRowsLong;
-    if (apply_two_pass(*L.db, L.prec, 1, L.mode, L.obs)) {
+    if (two) {
       hipError_t e;
       if (L.mode == kPlain) {
         e = longrow ? apply_s<R, 1, M_PLAIN, 1024, false>(L, grid, lds)
                     : apply_s<R, 1, M_PLAIN, 256, false>(L, grid, lds);
-        return e != hipSuccess ? e : colpass_s<R, M_PLAIN>(L, pgrid);
+        if (e != hipSuccess) return e;
+        return gather ? colgather<R>(L) : colpass_s<R, M_PLAIN>(L, pgrid);
       }
       if (L.obs) {  // observables of the step's first vector
         e = apply_s<R, 1, M_LANCZOS_OBS, 256, false>(L, grid, lds);

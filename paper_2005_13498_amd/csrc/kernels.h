@@ -144,6 +144,9 @@ size_t block_lds_bytes(const DevBasis& db, int prec, int nv);
 // for all up strings in LDS and adds the up hops (and the Lanczos epilogue).
 constexpr int kColW = 4;
 bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs);
+// Two-pass plain products of one vector gather their up hops from global
+// memory instead of staging columns.
+bool apply_gathers(const DevBasis& db, int prec);
 // Rows whose staged copy (+x, -x) exceeds the LDS budget (16 sites): the
 // one-pass kernel then gathers the down hops from the row in global memory.
 bool apply_global_rows(const DevBasis& db, int prec, int nv);

@@ -621,18 +621,28 @@ bool apply_global_rows(const DevBasis& db, int prec, int nv) {
   return nv == 1 && apply_lds_bytes(db, prec, 1, 1) > 150 * 1024;
 }
 
+// Larger than the eight XCDs' L2s together: one vector, one pass / staged
+// columns / gathered columns, in us: 24 MB (13 sites, complex64) - / 40 / 40;
+// 47 MB (13 sites, complex128) - / 67 / 60; 94 MB (14 sites, complex64) 200 /
+// 200 / 140; 188 MB (14 sites, complex128) 300 / 306 / 249; 2.6 GB (16 sites,
+// complex128, nothing fits LDS) 5040 / - / 4390.
+bool apply_gathers(const DevBasis& db, int prec) {
+  if (apply_global_rows(db, prec, 1) && db.dn_gslots == 0) return false;  // no grouped table for the row pass
+  return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) > 32.0 * 1024 * 1024;
+}
+
 bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs) {
   if (nv != 1 || !(mode == kPlain || mode == kLanczos) || db.two_pass == 0 || !db.up_tab) return false;
   if (obs && mode != kLanczos) return false;
-  if (colpass_lds_bytes(db, prec) > 150 * 1024) return false;
+  const bool gather = mode == kPlain && apply_gathers(db, prec);
+  if (!gather && colpass_lds_bytes(db, prec) > 150 * 1024) return false;
   if (db.two_pass == 1) return true;
   if (db.tuned_single[prec] >= 0) return db.tuned_single[prec] == 1;
   // automatic: when a vector is larger than one XCD's L2 the up-hop row
   // gathers of the one-pass kernel stream from the Infinity Cache.  With 2
-  // staged columns (complex128, 14 sites) only the Lanczos iterations gain
-  // (fused updates); a plain apply stays faster in one pass (263 vs 306 us,
-  // while complex64's 4 single-copy columns take 151 instead of 213 us).
-  if (mode == kPlain && colpass_width(db, prec) < kColW) return false;
+  // staged columns only the Lanczos iterations gain (fused updates), not a
+  // plain apply.
+  if (mode == kPlain && !gather && colpass_width(db, prec) < kColW) return false;
   return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) >= 4.0 * 1024 * 1024;
 }
 

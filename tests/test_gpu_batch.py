@@ -45,12 +45,12 @@ def test_batch_matches_oracle(lat, nu, nd, nvec, dtype):
 @pytest.mark.parametrize("lat,nu,nd,nvec,kernels", [
     (ring(10), 5, 5, 8, [(8, 0)]), (ring(11), 6, 5, 11, [(8, 0), (3, 0)]), (chain(12), 5, 6, 2, [(2, 2)]),
     (cluster_2d(3, 4), 6, 6, 3, [(3, 2)]), (cluster_2d(3, 4), 6, 6, 8, [(8, 2)]), (ring(13), 6, 7, 5, [(5, 2)]),
-    (ring(14), 7, 7, 3, None)])
+    (ring(14), 7, 7, 3, [(1, 1)] * 3), (ring(14), 7, 3, 3, None)])
 def test_batch_matches_single_vectors(lat, nu, nd, nvec, kernels, dtype):
     B = hub.Basis(lat, 8.0, nu, nd, device=0)
     prec = hub.HUB_C128 if dtype == torch.complex128 else hub.HUB_C64
     plan = hub.hub_get_plan(B.handle, prec, nvec, False)
-    if kernels is None:  # 14 sites: pairs of complex64 vectors, the odd one alone
+    if kernels is None:  # two staged columns: pairs of complex64 vectors, the odd one alone
         assert plan == ([(3, 2)] if prec == hub.HUB_C128 else [(2, 2), (1, 1)])
     else:
         assert plan == kernels
