@@ -129,11 +129,14 @@ __global__ __launch_bounds__(kMlpBlock) void k_mlp_forward(const float* __restri
 // 80 words: the four row groups of a read fall on different banks).  Column 8
 // of gW1's feature operand is 1, so its product also gives the bias gradient.
 // Bound: 216 matrix instructions of 32 cycles per tile, about as much again
-// in the two GELUs, two wavefronts per SIMD to overlap the two.  A workgroup
-// adds its eight wavefronts pairwise through LDS, 16 bytes a lane (in turn,
-// each adding to sums in LDS, took 30 us more), and leaves one partial row.
-// 48,000 rows: 775 us with one row per wavefront and lane broadcasts, 35 us
-// now; 38 TFLOP/s.
+// in the two GELUs, two wavefronts per SIMD to overlap the two: 5 us per tile
+// of a SIMD, after 14 us for the first tile of a workgroup with its staging
+// and sums.  A workgroup adds its eight wavefronts through LDS, 16 bytes a
+// lane, the second of two rounds by every thread, which stores what it added
+// (pairwise in three rounds, one wavefront storing, 3 us more; in turn, each
+// adding to sums in LDS, 30 us more), and leaves one partial row.  48,000
+// rows: 775 us with one row per wavefront and lane broadcasts, 29 us now; 45
+// TFLOP/s.
 using f32x4 = __attribute__((ext_vector_type(4))) float;
 constexpr int kGradWaves = 8, kGradBlock = 64 * kGradWaves;
 constexpr int kTile = 16;         // data rows of a wavefront's tile
@@ -153,10 +156,17 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Sum over the 16 lanes (data rows) of a lane's row group.
+// Sum over the 16 lanes (data rows) of a lane's row group, by rotations
+// within the group (DPP row_ror: vector operands, no LDS permute).
+template <int CTRL>
+__device__ __forceinline__ float row_rotated(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float row_sum(float v) {
-#pragma unroll
-  for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v += row_rotated<0x128>(v);
+  v += row_rotated<0x124>(v);
+  v += row_rotated<0x122>(v);
+  v += row_rotated<0x121>(v);
   return v;
 }
 
@@ -328,7 +338,8 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
     }
   gb3 = row_sum(gb3);
   loss = row_sum(loss);
-  // the wavefronts' sums, halves added pairwise in a fixed order
+  // the wavefronts' sums in a fixed order: the upper half is added to the
+  // lower, then every thread adds those four for 3.5 of the words and stores
   f32x4 sums[kSums];
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
@@ -343,30 +354,35 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
     scal[0][wv] = gb3;
     scal[1][wv] = loss;
   }
-  for (int half = kGradWaves / 2; half >= 1; half /= 2) {
-    __syncthreads();  // the tiles, and the sums of the previous half, are no longer read
-    if (wv >= half && wv < 2 * half)
+  constexpr int kHalf = kGradWaves / 2;
+  __syncthreads();  // the tiles are no longer read
+  if (wv >= kHalf)
 #pragma unroll
-      for (int k = 0; k < kSums; ++k) sh[((wv - half) * kSums + k) * 64 + lane] = sums[k];
-    __syncthreads();
-    if (wv < half)
+    for (int k = 0; k < kSums; ++k) sh[((wv - kHalf) * kSums + k) * 64 + lane] = sums[k];
+  __syncthreads();
+  if (wv < kHalf)  // each lane rewrites the words that it alone has read
 #pragma unroll
-      for (int k = 0; k < kSums; ++k) sums[k] += sh[(wv * kSums + k) * 64 + lane];
-  }
-  if (wv != 0) return;
+    for (int k = 0; k < kSums; ++k) {
+      const int q = (wv * kSums + k) * 64 + lane;
+      sh[q] = sums[k] + sh[q];
+    }
+  __syncthreads();
   float* const G = part + (size_t)blockIdx.x * kGradStride;
+  for (int k = wv; k < kSums; k += kGradWaves) {
+    f32x4 q = sh[k * 64 + lane];
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+    for (int w = 1; w < kHalf; ++w) q += sh[(w * kSums + k) * 64 + lane];
+    const int t = k < 16 ? k >> 2 : k & 3;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int u = 16 * t + 4 * g + r;  // matrix row: the unit of the outer layer
-#pragma unroll
-      for (int k = 0; k < 4; ++k) G[oW2 + u * kHid + 16 * k + c] = sums[4 * t + k][r];
-      if (c < kIn) G[oW1 + u * kIn + c] = sums[16 + t][r];
-      else if (c == kIn) G[oB1 + u] = sums[16 + t][r];
-      else if (c == kIn + 1) G[oB2 + u] = sums[20 + t][r];
-      else if (c == kIn + 2) G[oW3 + u] = sums[24 + t][r];
+      if (k < 16) G[oW2 + u * kHid + 16 * (k & 3) + c] = q[r];
+      else if (k < 20 && c < kIn) G[oW1 + u * kIn + c] = q[r];
+      else if (k < 20 && c == kIn) G[oB1 + u] = q[r];
+      else if (k >= 20 && c == 0) G[(k < 24 ? oB2 : oW3) + u] = q[r];
     }
+  }
+  if (wv != 0) return;
   if (lane < 2) {
     float q = 0.f;
     for (int w = 0; w < kGradWaves; ++w) q += scal[lane][w];
@@ -377,8 +393,9 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
 // Adam on the fixed-order sum of the workgroups' partials; parameter kP
 // reports L.  kAdamSlices threads share a parameter, each with every
 // kAdamSlices-th partial row (one thread per parameter waits out every row's
-// load: 60 us for 256 rows; 7 us now).
-constexpr int kAdamCols = 64, kAdamSlices = 16;
+// load: 60 us for 256 rows; 5 us now, 7 with twice the parameters and half the
+// threads each).
+constexpr int kAdamCols = 32, kAdamSlices = 32;
 __global__ __launch_bounds__(kAdamCols * kAdamSlices) void k_mlp_adam(const float* __restrict__ part, int n_part,
                                                                       float* __restrict__ P, float* __restrict__ m,
                                                                       float* __restrict__ v, int t, float lr,
@@ -388,6 +405,7 @@ __global__ __launch_bounds__(kAdamCols * kAdamSlices) void k_mlp_adam(const floa
   const int p = blockIdx.x * kAdamCols + c;
   float sum = 0.f;
   if (p <= kP)
+#pragma unroll 8
     for (int w = s; w < n_part; w += kAdamSlices) sum += part[(size_t)w * kGradStride + p];
   red[s][c] = sum;
   __syncthreads();
