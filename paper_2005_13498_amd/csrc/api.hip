@@ -956,7 +956,6 @@ hub_status run_group(hub_basis h, hub_prec prec, int nv, void* user, int n_steps
   }
   // observables at the last sample time reached (after n_steps steps, or
   // after the step that stopped at m_max)
-  bool split_obs = false;
   if (want_obs) {
     StepCtl c2 = StepCtl{};  // clear a stop flag left by the last step
     *W.h_ctl = c2;
@@ -970,30 +969,18 @@ hub_status run_group(hub_basis h, hub_prec prec, int nv, void* user, int n_steps
     A.coef_obs = A.coef;
     A.j = 0;
     int ogrid = 0;
-    if (nv > 1 && !hub::apply_fits(h->D, pi, nv)) {
-      // the group's row does not fit the one-pass kernel (blocks on the
-      // two-pass block kernels): back to the caller's layout first, then the
-      // observables of one vector at a time
-      HUB_HIP(hub::launch_interleave(pi, nv, dim, slot0, user, false, stream));
-      split_obs = true;
-      for (int v = 0; v < nv; ++v) {
-        hub::ApplyLaunch A1 = A;
-        A1.nv = 1;
-        A1.x = static_cast<const char*>(user) + static_cast<size_t>(v) * dim * es;
-        A1.coef = A.coef + static_cast<size_t>(v) * 2 * nc;
-        A1.coef_obs = A1.coef;
-        HUB_HIP(hub::launch_apply(A1, &ogrid));
-        HUB_HIP(hub::launch_finalize_obs(1, W.partials, ogrid, hub::apply_nq(hub::kObsOnly, true, nc), W.st + v,
-                                         stream));
-      }
+    if (nv > 1 && hub::block_two_pass(h->D, pi, nv)) {
+      A.row_obs = W.partials + static_cast<size_t>(h->D.dim_dn) * nv;
+      HUB_HIP(hub::launch_apply(A, &ogrid));
+      HUB_HIP(hub::launch_finalize_obs(nv, A.row_obs, h->D.dim_up, W.partials, ogrid, W.st, stream));
     } else {
       HUB_HIP(hub::launch_apply(A, &ogrid));
-      HUB_HIP(hub::launch_finalize_obs(nv, W.partials, ogrid, hub::apply_nq(hub::kObsOnly, true, nc), W.st, stream));
+      HUB_HIP(hub::launch_finalize_obs(nv, W.partials, ogrid, nullptr, 0, W.st, stream));
     }
     HUB_HIP(hub::launch_step_log(nv, W.st, W.ctl, nullptr, dobs + static_cast<size_t>(*steps_done) * nv * kObsQ,
                                  kObsQ, stream));
   }
-  if (nv > 1 && !split_obs) HUB_HIP(hub::launch_interleave(pi, nv, dim, slot0, user, false, stream));
+  if (nv > 1) HUB_HIP(hub::launch_interleave(pi, nv, dim, slot0, user, false, stream));
 
   // copy logs back
   const int nd = *steps_done;
@@ -1089,7 +1076,7 @@ hub_status observables_into(hub_basis h, const double* A, hub_prec prec, int32_t
     L.stream = st;
     int grid = 0;
     HUB_HIP(hub::launch_apply(L, &grid));
-    HUB_HIP(hub::launch_finalize_obs(1, partials, grid, hub::apply_nq(hub::kObsOnly, true, nc), vst, st));
+    HUB_HIP(hub::launch_finalize_obs(1, partials, grid, nullptr, 0, vst, st));
     double o[kObsQ];
     HUB_HIP(hipMemcpyAsync(o, reinterpret_cast<char*>(vst) + offsetof(VecState, obs), sizeof(o),
                            hipMemcpyDeviceToHost, st));

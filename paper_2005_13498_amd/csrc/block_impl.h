@@ -82,16 +82,14 @@ __device__ __forceinline__ uint4 to_word(const V (&w)[16 / sizeof(V)]) {
 // Sums over the workgroup of NQ per-lane values, separately for each word
 // index k = lane % L (the lanes of one word index hold the same vectors):
 // out[q * L + k] = sum over the threads with that k of vals[q], fixed order
-// (shuffles in each wave, then the waves in order).  lds holds W * NQ * L
+// (within each wave, then the waves in order).  lds holds W * NQ * L
 // doubles.
 template <int W, int L, int NQ>
 __device__ __forceinline__ void word_sums(const double (&vals)[NQ], double* lds, double* out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    double v = vals[q];
-#pragma unroll
-    for (int off = 32; off >= L; off >>= 1) v += __shfl_xor(v, off);
+    const double v = wave_sum_mod<L>(vals[q]);
     if (lane < L) lds[(w * NQ + q) * L + lane] = v;
   }
   __syncthreads();
@@ -106,23 +104,24 @@ __device__ __forceinline__ void word_sums(const double (&vals)[NQ], double* lds,
 constexpr int kRowAhead = 2, kColAhead = 2;
 
 // One group of four slots: the signed sum of the staged words they index
-// (word k of each source element of L words), from the table word pair w.
-template <typename R, int L>
+// (word k of each source element of L words), from the table word pair w, in
+// the precision S.
+template <typename R, int L, typename S = R>
 __device__ __forceinline__ void group_sum(uint2 w, const uint4* xs, int k,
-                                          typename CT<R>::T (&sum)[16 / sizeof(typename CT<R>::T)]) {
+                                          typename CT<S>::T (&sum)[16 / sizeof(typename CT<R>::T)]) {
   using V = typename CT<R>::T;
   constexpr int VPL = 16 / sizeof(V);
 #pragma unroll
-  for (int i = 0; i < VPL; ++i) sum[i] = V{0, 0};
+  for (int i = 0; i < VPL; ++i) sum[i] = typename CT<S>::T{0, 0};
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const R sg = slot_sign<R>(w, s);
+    const S sg = slot_sign<S>(w, s);
     V t[VPL];
     from_word<V>(xs[slot_src(w, s) * L + k], t);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
-      sum[i].x = fma(sg, t[i].x, sum[i].x);
-      sum[i].y = fma(sg, t[i].y, sum[i].y);
+      sum[i].x = fma(sg, static_cast<S>(t[i].x), sum[i].x);
+      sum[i].y = fma(sg, static_cast<S>(t[i].y), sum[i].y);
     }
   }
 }
@@ -174,14 +173,15 @@ __device__ void block_decide_pre(int j, const double* beta_new, VecState* st, St
 // when every running vector's estimate is below tol the step ends at m = j
 // and the column pass skips its apply.  M_LANCZOS_OBS (the step's first apply): per
 // row, [diag, docc, |x|^2, down-hop part of Re <x|K(t_obs)|x>] for every
-// vector into partials [dim_up][kObsQ][NV].
+// vector into partials [dim_up][kObsQ][NV].  M_OBS (the state a run ends
+// with): those alone, the hops summed in FP64.
 template <typename R, int NV, int MODE, int MAXS, int BLK, bool FUSE>
 __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
   using V = typename CT<R>::T;
   constexpr int VPL = 16 / sizeof(V), L = NV / VPL, EPW = BLK / L, W = BLK / 64, kG = MAXS / 4;
   static_assert(L >= 1 && NV % VPL == 0 && BLK % L == 0, "whole words per element");
   constexpr bool kL = MODE == M_LANCZOS || MODE == M_LANCZOS_OBS;
-  constexpr bool kO = MODE == M_LANCZOS_OBS;
+  constexpr bool kX = MODE == M_OBS, kO = MODE == M_LANCZOS_OBS || kX;
   constexpr int kOC = kObsQ * NV;  // observables partials per row
   __shared__ double red[W * kOC];
   __shared__ double sh_beta[NV];
@@ -365,15 +365,16 @@ __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
     for (int i = 0; i < VPL; ++i) ko[i] = make_double2(0.0, 0.0);
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      V sum[VPL];
-      group_sum<R, L>(ec[g], xs, k, sum);
+      using S = std::conditional_t<kX, double, R>;
+      typename CT<S>::T sum[VPL];
+      group_sum<R, L, S>(ec[g], xs, k, sum);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
-        acc[i] = cfma(cf[g][i], sum[i], acc[i]);
+        if constexpr (!kX) acc[i] = cfma(cf[g][i], sum[i], acc[i]);
         if constexpr (kO) ko[i] = cfma(ocf[g][i], make_double2(sum[i].x, sum[i].y), ko[i]);
       }
     }
-    y4[static_cast<size_t>(b) * L + k] = to_word<V>(acc);
+    if constexpr (!kX) y4[static_cast<size_t>(b) * L + k] = to_word<V>(acc);
     if constexpr (kO) {
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
@@ -403,15 +404,16 @@ __global__ __launch_bounds__(BLK) void k_brow(BArgs p) {
 // Re <x|K(t_obs)|x>).  A vector whose step ended at an earlier iteration
 // gets a zero result.  FUSE: |u_j| comes from the row pass's per-row norms and
 // an extra last workgroup takes the decision for m = j (a vector that has
-// stopped gets a result no later step reads).
+// stopped gets a result no later step reads).  M_OBS: the up-hop part alone,
+// partials [grid][NV].
 template <typename R, int NV, int MODE, int MAXS, int BLK, bool FUSE>
 __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
   using V = typename CT<R>::T;
   constexpr int VPL = 16 / sizeof(V), L = NV / VPL, EPW = BLK / L, W = BLK / 64, kG = MAXS / 4;
   static_assert(L >= 1 && NV % VPL == 0 && BLK % L == 0, "whole words per element");
   constexpr bool kL = MODE == M_LANCZOS || MODE == M_LANCZOS_OBS;
-  constexpr bool kO = MODE == M_LANCZOS_OBS;
-  constexpr int kNQ = kO ? 2 : 1;  // per vector: alpha [, up-hop obs part]
+  constexpr bool kX = MODE == M_OBS, kO = MODE == M_LANCZOS_OBS || kX;
+  constexpr int kNQ = kO && !kX ? 2 : 1;  // per vector: alpha, up-hop obs part
   __shared__ double red[W * kNQ * NV];
   __shared__ double sh_b[NV];
   const int tid = threadIdx.x;
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
 #pragma unroll
     for (int g = 0; g < kG; ++g) ev[g] = tab2[static_cast<size_t>(a) * kG + g];
     const size_t o = (static_cast<size_t>(a) * dd + b) * L + k;  // this lane's word of element (a, b)
-    yw = y4[o];
+    if constexpr (!kX) yw = y4[o];
     if (prev) pw = xp4[o];
   };
   V cf[kG][VPL];
@@ -515,13 +517,14 @@ __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
     __syncthreads();
   }
 
-  double q[kL ? kNQ * VPL : 1];
+  constexpr bool kQ = kL || kX;
+  double q[kQ ? kNQ * VPL : 1];
 #pragma unroll
-  for (int i = 0; i < (kL ? kNQ * VPL : 1); ++i) q[i] = 0.0;
+  for (int i = 0; i < (kQ ? kNQ * VPL : 1); ++i) q[i] = 0.0;
   for (int a = e0; a < du; a += EPW) {
     const size_t o = (static_cast<size_t>(a) * dd + b) * L + k;
     V acc[VPL], pv[VPL];
-    from_word<V>(yw, acc);
+    if constexpr (!kX) from_word<V>(yw, acc);
     if (prev) from_word<V>(pw, pv);
     uint2 ec[kG];
 #pragma unroll
@@ -532,30 +535,35 @@ __global__ __launch_bounds__(BLK) void k_bcol(BArgs p) {
     for (int i = 0; i < VPL; ++i) ko[i] = make_double2(0.0, 0.0);
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      V sum[VPL];
-      group_sum<R, L>(ec[g], xs, k, sum);
+      using S = std::conditional_t<kX, double, R>;
+      typename CT<S>::T sum[VPL];
+      group_sum<R, L, S>(ec[g], xs, k, sum);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
-        acc[i] = cfma(cf[g][i], sum[i], acc[i]);
+        if constexpr (!kX) acc[i] = cfma(cf[g][i], sum[i], acc[i]);
         if constexpr (kO) ko[i] = cfma(ocf[g][i], make_double2(sum[i].x, sum[i].y), ko[i]);
       }
     }
-    if constexpr (kL) {
+    if constexpr (kQ) {
       V xv[VPL];
       from_word<V>(xs[static_cast<size_t>(a) * L + k], xv);
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
+        if constexpr (kX) {
+          q[i] += static_cast<double>(xv[i].x) * ko[i].x + static_cast<double>(xv[i].y) * ko[i].y;
+          continue;
+        }
         const V pvv = prev ? pv[i] : V{0, 0};
         acc[i].x = acc[i].x * sj[i] - bp[i] * pvv.x;
         acc[i].y = acc[i].y * sj[i] - bp[i] * pvv.y;
         q[i] += static_cast<double>(sj[i]) *
                 (static_cast<double>(xv[i].x) * acc[i].x + static_cast<double>(xv[i].y) * acc[i].y);
-        if constexpr (kO) q[VPL + i] += static_cast<double>(xv[i].x) * ko[i].x + static_cast<double>(xv[i].y) * ko[i].y;
+        if constexpr (kNQ == 2) q[VPL + i] += static_cast<double>(xv[i].x) * ko[i].x + static_cast<double>(xv[i].y) * ko[i].y;
       }
     }
-    y4[o] = to_word<V>(acc);
+    if constexpr (!kX) y4[o] = to_word<V>(acc);
   }
-  if constexpr (kL) {
+  if constexpr (kQ) {
     __shared__ double tot[kNQ * NV];
     word_sums<W, L, kNQ * VPL>(q, red, tot);
     __syncthreads();
@@ -610,7 +618,7 @@ constexpr int kBlkThreads = 512;
 template <typename R, int NV, int MODE, int MAXS_R, int MAXS_C, bool FUSE>
 hipError_t block_pair(const ApplyLaunch& L, int* pgrid) {
   const DevBasis& db = *L.db;
-  constexpr bool kO = MODE == M_LANCZOS_OBS;
+  constexpr bool kO = MODE == M_LANCZOS_OBS || MODE == M_OBS;
   const size_t es = sizeof(typename CT<R>::T);
   // row pass
   BArgs pr = block_args(L, true);
@@ -664,6 +672,7 @@ hipError_t block_row_s(const ApplyLaunch& L, int* pgrid) {
 template <typename R, int NV>
 hipError_t block_mode(const ApplyLaunch& L, int* pgrid) {
   if (L.mode == kPlain) return block_row_s<R, NV, M_PLAIN>(L, pgrid);
+  if (L.mode == kObsOnly) return block_row_s<R, NV, M_OBS>(L, pgrid);
   if (L.mode != kLanczos) return hipErrorInvalidValue;
   if (L.obs) return block_row_s<R, NV, M_LANCZOS_OBS>(L, pgrid);
   if (L.fuse) return block_row_s<R, NV, M_LANCZOS, true>(L, pgrid);

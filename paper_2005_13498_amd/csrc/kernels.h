@@ -108,7 +108,7 @@ struct ApplyLaunch {
   // optional timing events attached to the dispatches: start/end of the
   // (first) kernel, and of the column pass when the apply has two kernels
   hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev2_start = nullptr, ev2_stop = nullptr;
-  // two-pass Lanczos apply with observables: the row pass's obs partials
+  // two-pass apply with observables (blocks: also kObsOnly): the row pass's obs partials
   // [dim_up][kObsQ][nv] go here (the column pass writes alpha and the up-hop part)
   double* row_obs = nullptr;
   // two-pass Lanczos iteration j >= 2 with the update of u_j fused into the
@@ -234,7 +234,8 @@ hipError_t launch_step_log(int nv, const VecState* st, StepCtl* ctl, void* log, 
                            hipStream_t s);
 
 // One-workgroup reductions of partial sums.
-hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, int nq, VecState* st, hipStream_t s);
+hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, const double* hops, int ncols, VecState* st,
+                               hipStream_t s);
 hipError_t launch_finalize(const double* partials, int nrows, int ncols, double* out, hipStream_t s);
 
 // Site-resolved double occupation sum_k n_{i up} n_{i down} |x_k|^2 of one vector.

@@ -273,15 +273,21 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const double* partials, int
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// Observables of an apply in kObsOnly mode: finalize its partials into st.
+// Observables of an apply in kObsOnly mode: finalize its partials
+// [nrows][kObsQ][NV] into st, the block kernels' up-hop parts [ncols][NV] with
+// them (all columns in one pass: 4 vectors of 12 sites took 20 us one column
+// after another).
 template <int NV>
-__global__ __launch_bounds__(kBlock) void k_finalize_obs(const double* partials, int nrows, int nq, VecState* st) {
-  __shared__ double red[kWaves];
-  const int qn = nq * NV;
-  for (int t = 0; t < qn; ++t) {
-    const double s = reduce_column(partials, nrows, qn, t, red);
-    if (threadIdx.x == 0) st[t % NV].obs[t / NV] = s;
-  }
+__global__ __launch_bounds__(kBlock) void k_finalize_obs(const double* partials, int nrows, const double* hops,
+                                                         int ncols, VecState* st) {
+  constexpr int NC = kObsQ * NV;
+  __shared__ double red[kWaves * NC], so[NC], su[NV];
+  const double rows = cols_partial<NC, kBlock>(partials, nrows, NC);
+  const double cols = ncols > 0 ? cols_partial<NV, kBlock>(hops, ncols, NV) : 0.0;
+  cols_total<NC, kWaves>(rows, red, so);
+  cols_total<NV, kWaves>(cols, red, su);
+  const int t = threadIdx.x, q = t / NV;
+  if (t < NC) st[t % NV].obs[q] = so[t] + (q == kObsQ - 1 ? su[t % NV] : 0.0);
 }
 
 template <typename R>
@@ -685,7 +691,7 @@ bool apply_fits(const DevBasis& db, int prec, int nv) {
 }
 
 hipError_t launch_apply(const ApplyLaunch& L, int* grid_out) {
-  if (L.nv > 1 && L.mode != kObsOnly && block_two_pass(*L.db, L.prec, L.nv)) {
+  if (L.nv > 1 && block_two_pass(*L.db, L.prec, L.nv)) {
     int pgrid = 0;
     const hipError_t e = L.prec == 0 ? launch_block_c128(L, &pgrid) : launch_block_c64(L, &pgrid);
     if (grid_out) *grid_out = pgrid;
@@ -905,8 +911,10 @@ hipError_t launch_step_begin(int prec, int nv, int64_t n, const void* v, VecStat
   return hipGetLastError();
 }
 
-hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, int nq, VecState* st, hipStream_t s) {
-  HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_finalize_obs<NVC>), dim3(1), dim3(kBlock), 0, s, partials, nrows, nq, st));
+hipError_t launch_finalize_obs(int nv, const double* partials, int nrows, const double* hops, int ncols, VecState* st,
+                               hipStream_t s) {
+  HUB_NV_SWITCH(nv, hipLaunchKernelGGL((k_finalize_obs<NVC>), dim3(1), dim3(kBlock), 0, s, partials, nrows, hops,
+                                       ncols, st));
   return hipGetLastError();
 }
 

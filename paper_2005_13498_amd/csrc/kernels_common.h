@@ -66,6 +66,19 @@ __device__ __forceinline__ double wave_max(double v) {
   v = fmax(v, dpp<kRowBcast31, 0xC>(v));
   return lane_value(v, 63);
 }
+// Sum over the lanes with the same lane % L, on every lane, fixed order:
+// rotations within the rows of 16 lanes, then two shuffles across them.
+template <int L>
+__device__ __forceinline__ double wave_sum_mod(double v) {
+  constexpr int kRowRor = 0x120;
+  if constexpr (L <= 8) v += dpp<kRowRor + 8>(v);
+  if constexpr (L <= 4) v += dpp<kRowRor + 4>(v);
+  if constexpr (L <= 2) v += dpp<kRowRor + 2>(v);
+  if constexpr (L <= 1) v += dpp<kRowRor + 1>(v);
+  if constexpr (L <= 16) v += __shfl_xor(v, 16);
+  if constexpr (L <= 32) v += __shfl_xor(v, 32);
+  return v;
+}
 // Total over each row of 16 lanes where every row holds the same values.
 __device__ __forceinline__ double row_total(double v) {
   v += dpp<kRowShr + 1>(v);
@@ -148,8 +161,7 @@ __device__ __forceinline__ double cols_partial(const double* partials, int nrows
 template <int NC, int W>
 __device__ __forceinline__ void cols_total(double s, double* lds, double* out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 32; off >= NC; off >>= 1) s += __shfl_xor(s, off);
+  s = wave_sum_mod<NC>(s);
   if (lane < NC) lds[w * NC + lane] = s;
   __syncthreads();
   if (threadIdx.x < NC) {

@@ -176,3 +176,30 @@ def test_block_propagation_ring14_c64_vs_c128():
     finally:
         B.close()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("lat,U,nu,nd", CASES)
+@pytest.mark.parametrize("group", [2, 4, 8])
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_block_final_observables(lat, U, nu, nd, group, dtype):
+    """The observables of the state a run of blocks ends with, against the
+    oracle's of the state it returns (exactly those numbers in both
+    precisions): sums and products are in FP64, a few thousand terms of at
+    most |H|_inf |x|^2."""
+    B = hub.Basis(lat, U, nu, nd)
+    try:
+        prec = hub.HUB_C128 if dtype == torch.complex128 else hub.HUB_C64
+        hub.hub_set_tuning(B.handle, prec, {"single_two_pass": 1, "block_two_pass": [0, 1, 1, 1], "apply_group": group,
+                                            "prop_group": group, "prop_group_large": group})
+        hub.hub_set_propagate_path(B.handle, 0)
+        ham = HubbardOracle(lat, U, nu, nd)
+        pulses = [PulseParams(0, 0.1 * (k + 1), 8.0, 0.02, 0.15) for k in range(group)]
+        x = torch.from_numpy(random_state(B.dim, seed=13, nvec=group)).to(DEV).to(dtype).contiguous()
+        _, obs, _ = hub.hub_propagate(B.handle, pulses, 0.0, 0.01, 1, hub.make_opts(tol=1e-8, m_max=30), x)
+        bound = 1e-12 * max(1.0, hub.hub_basis_classes(B.handle)[2])
+        for k in range(group):
+            v = from_canonical(x[k].cpu().numpy().astype(np.complex128), ham.states, lat.n_sites)
+            ref = observables(ham, v, pulse_A(pulses[k], 0.01))[:3]
+            assert np.max(np.abs(obs[1, k, 1:4] - np.array(ref))) <= bound, k
+    finally:
+        B.close()
