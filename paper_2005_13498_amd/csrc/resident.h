@@ -43,11 +43,13 @@ struct ResidentArgs {
 
 // LDS bytes of a resident workgroup: the tables, strings and on-site energies
 // (16-byte aligned pieces in the kernel's order), then the tile with a zero
-// column and a zero row, (dim_up + 1) (dim_dn + 1) elements.
-inline size_t resident_lds_bytes(int dim_up, int dim_dn, int gs_up, int gs_dn, bool eps, int prec) {
+// column and a zero row, (dim_up + 1) (dim_dn + 1) elements.  wide: hop table
+// entries of 32 bits instead of 16.
+inline size_t resident_lds_bytes(int dim_up, int dim_dn, int gs_up, int gs_dn, bool eps, int prec, bool wide = false) {
   auto a16 = [](size_t b) { return (b + 15) & ~size_t(15); };
-  size_t t = a16(size_t(dim_dn) * (gs_dn / 4) * 8) + a16(size_t(dim_up) * (gs_up / 4) * 8) + a16(size_t(dim_up) * 4) +
-             a16(size_t(dim_dn) * 4);
+  const size_t gb = wide ? 16 : 8;  // bytes of a group of four entries
+  size_t t = a16(size_t(dim_dn) * (gs_dn / 4) * gb) + a16(size_t(dim_up) * (gs_up / 4) * gb) +
+             a16(size_t(dim_up) * 4) + a16(size_t(dim_dn) * 4);
   if (eps) t += a16(size_t(dim_up) * 8) + a16(size_t(dim_dn) * 8);
   return t + size_t(dim_up + 1) * (dim_dn + 1) * (prec == 0 ? 16 : 8);
 }

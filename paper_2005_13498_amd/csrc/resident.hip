@@ -21,12 +21,15 @@
 // summed in FP64 from the first iteration's group sums with the coefficients
 // of the sample time.
 //
-// The one workgroup's VALU issue bounds it (71 % busy: about 226 instructions
+// The one workgroup's VALU issue bounds it (71 % busy: about 200 instructions
 // an element and iteration, most of them addresses, signs and products of the
-// hops).  Sums across lanes by DPP and up sources kept as LDS offsets took 50
-// steps of 70 x 70 complex128 elements (450 iterations) from 5.64 to 5.19 ms.
-// Threads that own rows of one column and decode its down hops once need more
-// registers than 1,024 threads have, and spill: 6.35 ms.
+// hops).  50 steps of 70 x 70 complex128 elements (450 iterations) took 5.64
+// ms; with sums across lanes by DPP and up sources kept as LDS offsets 5.19,
+// with 32-bit hop table entries 4.87.  Threads that own rows of one column and
+// decode its down hops once need more registers than 1,024 threads have, and
+// spill: 6.35 ms.
+#include <type_traits>
+
 #include "kernels_common.h"
 #include "resident.h"
 
@@ -38,17 +41,43 @@ namespace {
 constexpr int kRT = kResidentThreads;
 constexpr int kRW = kRT / 64;
 
-// Signed sum of the four values one table word pair names, at those offsets
-// from xs.
+// A group of four hop table entries, offset in elements | sign: 16 bits each,
+// or 32 bits each where the tables still fit beside the tile.  A wide entry's
+// sign is bit 31, which shifting the offset to bytes drops: one instruction to
+// an address and one to the sign as +-1, where a halfword takes three or four
+// (50 steps of 8 sites: 5.19 -> 4.87 ms).
 template <typename V>
-__device__ __forceinline__ V slot_sum4(uint2 w, const V* xs) {
+struct Hop {
+  const V* at;
+  decltype(V().x) sign;
+};
+template <typename V>
+__device__ __forceinline__ Hop<V> hop(uint2 w, int k, const V* xs) {
+  return {xs + slot_src(w, k), slot_sign<decltype(V().x)>(w, k)};
+}
+template <typename V>
+__device__ __forceinline__ Hop<V> hop(uint4 w, int k, const V* xs) {
+  const uint32_t h = k < 2 ? (k == 0 ? w.x : w.y) : (k == 2 ? w.z : w.w);
+  constexpr int kShift = sizeof(V) == 16 ? 4 : 3;
+  const V* at = reinterpret_cast<const V*>(reinterpret_cast<const char*>(xs) + (h << kShift));
+  if constexpr (sizeof(V) == 16) return {at, __hiloint2double((h & 0x80000000u) | 0x3FF00000u, 0)};
+  else return {at, __uint_as_float((h & 0x80000000u) | 0x3F800000u)};
+}
+__device__ __forceinline__ bool hop_pad(uint2 w, int k, uint32_t pad) { return slot_src(w, k) == pad; }
+__device__ __forceinline__ bool hop_pad(uint4 w, int k, uint32_t pad) {
+  return (k < 2 ? (k == 0 ? w.x : w.y) : (k == 2 ? w.z : w.w)) == pad;
+}
+
+// Signed sum of the four values a group names, at those offsets from xs.
+template <typename V, typename T>
+__device__ __forceinline__ V slot_sum4(T w, const V* xs) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const auto sg = slot_sign<decltype(s.x)>(w, k);
-    const V t = xs[slot_src(w, k)];
-    s.x = fma(sg, t.x, s.x);
-    s.y = fma(sg, t.y, s.y);
+    const Hop<V> h = hop(w, k, xs);
+    const V t = *h.at;
+    s.x = fma(h.sign, t.x, s.x);
+    s.y = fma(h.sign, t.y, s.y);
   }
   return s;
 }
@@ -56,17 +85,16 @@ __device__ __forceinline__ V slot_sum4(uint2 w, const V* xs) {
 // The same over staged columns, skipping padding entries (offset pad): the
 // lanes of a wavefront mostly share the up string and so its padding, and a
 // padding read of the zero row would cost a full-width LDS access.
-template <typename V>
-__device__ __forceinline__ V slot_sum4_skip(uint2 w, const V* xs, uint32_t pad) {
+template <typename V, typename T>
+__device__ __forceinline__ V slot_sum4_skip(T w, const V* xs, uint32_t pad) {
   V s = V{0, 0};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const uint32_t src = slot_src(w, k);
-    if (src == pad) continue;
-    const auto sg = slot_sign<decltype(s.x)>(w, k);
-    const V t = xs[src];
-    s.x = fma(sg, t.x, s.x);
-    s.y = fma(sg, t.y, s.y);
+    if (hop_pad(w, k, pad)) continue;
+    const Hop<V> h = hop(w, k, xs);
+    const V t = *h.at;
+    s.x = fma(h.sign, t.x, s.x);
+    s.y = fma(h.sign, t.y, s.y);
   }
   return s;
 }
@@ -112,7 +140,7 @@ __device__ __forceinline__ int opaque(int x) {
 
 }  // namespace
 
-template <typename R, int EPT>
+template <typename R, int EPT, bool WIDE>
 __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
   using V = typename CT<R>::T;
   __shared__ double red[2 * kRW * (1 + kObsQ)];  // two reduction buffers (block_sums)
@@ -139,8 +167,9 @@ __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
     lp += (bytes + 15) & ~size_t(15);
     return q;
   };
-  uint2* tdn = reinterpret_cast<uint2*>(carve(static_cast<size_t>(dd) * gdn * 8));
-  uint2* tup = reinterpret_cast<uint2*>(carve(static_cast<size_t>(du) * gup * 8));
+  using Tab = std::conditional_t<WIDE, uint4, uint2>;
+  Tab* tdn = reinterpret_cast<Tab*>(carve(static_cast<size_t>(dd) * gdn * sizeof(Tab)));
+  Tab* tup = reinterpret_cast<Tab*>(carve(static_cast<size_t>(du) * gup * sizeof(Tab)));
   uint32_t* upb = reinterpret_cast<uint32_t*>(carve(static_cast<size_t>(du) * 4));
   uint32_t* dnb = reinterpret_cast<uint32_t*>(carve(static_cast<size_t>(dd) * 4));
   const bool has_eps = P.eps_up != nullptr || P.eps_dn != nullptr;
@@ -148,16 +177,21 @@ __global__ __launch_bounds__(kRT) void k_resident(ResidentArgs P) {
   double* epd = has_eps ? reinterpret_cast<double*>(carve(static_cast<size_t>(dd) * 8)) : nullptr;
   V* xs = reinterpret_cast<V*>(lp);
   {
-    const uint2* g1 = reinterpret_cast<const uint2*>(P.dn_tab);
-    for (int i = tid; i < dd * gdn; i += kRT) tdn[i] = g1[i];
-    // up sources as offsets within a staged column, src * ld (the tile's at
-    // most 20,480 staged elements leave the sign bit free)
-    const uint2* g2 = reinterpret_cast<const uint2*>(P.up_tab);
-    auto scaled = [&](uint32_t h) {
-      const uint32_t lo = (h & 0x7FFFu) * ld, hi = (h >> 16 & 0x7FFFu) * ld;
-      return (h & 0x80008000u) | lo | hi << 16;
+    // sources as offsets, up hops' within a staged column: src * ld (the
+    // tile's at most 20,480 staged elements leave a halfword's sign bit free)
+    auto entries = [&](uint2 g, uint32_t scale) {
+      auto off = [&](uint32_t h) { return (h & 0x7FFFu) * scale; };
+      if constexpr (WIDE)
+        return uint4{off(g.x) | (g.x & 0x8000u) << 16, off(g.x >> 16) | (g.x & 0x80000000u),
+                     off(g.y) | (g.y & 0x8000u) << 16, off(g.y >> 16) | (g.y & 0x80000000u)};
+      else
+        return uint2{(g.x & 0x80008000u) | off(g.x) | off(g.x >> 16) << 16,
+                     (g.y & 0x80008000u) | off(g.y) | off(g.y >> 16) << 16};
     };
-    for (int i = tid; i < du * gup; i += kRT) tup[i] = make_uint2(scaled(g2[i].x), scaled(g2[i].y));
+    const uint2* g1 = reinterpret_cast<const uint2*>(P.dn_tab);
+    const uint2* g2 = reinterpret_cast<const uint2*>(P.up_tab);
+    for (int i = tid; i < dd * gdn; i += kRT) tdn[i] = entries(g1[i], 1);
+    for (int i = tid; i < du * gup; i += kRT) tup[i] = entries(g2[i], ld);
     for (int i = tid; i < du; i += kRT) {
       upb[i] = P.up_bits[i];
       if (has_eps) epu[i] = P.eps_up ? P.eps_up[i] : 0.0;
@@ -464,9 +498,9 @@ int resident_ept(int prec, int64_t dim) {
   return 0;
 }
 
-template <typename R, int EPT>
-hipError_t launch_resident_t(const ResidentArgs& a, size_t lds, hipStream_t s) {
-  auto fn = k_resident<R, EPT>;
+template <typename R, int EPT, bool WIDE>
+hipError_t launch_resident_w(const ResidentArgs& a, size_t lds, hipStream_t s) {
+  auto fn = k_resident<R, EPT, WIDE>;
   static const int max_dyn = dyn_lds_opt_in(reinterpret_cast<const void*>(fn));
   if (lds > static_cast<size_t>(max_dyn)) return hipErrorInvalidValue;
   ResidentArgs args = a;
@@ -474,12 +508,21 @@ hipError_t launch_resident_t(const ResidentArgs& a, size_t lds, hipStream_t s) {
   return hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(a.nvec), dim3(kRT), kargs, lds, s);
 }
 
+template <typename R, int EPT>
+hipError_t launch_resident_t(const ResidentArgs& a, size_t lds, hipStream_t s) {
+  constexpr int prec = sizeof(R) == 8 ? 0 : 1;
+  const size_t wide = resident_lds_bytes(a.dim_up, a.dim_dn, a.gs_up, a.gs_dn, a.eps_up != nullptr || a.eps_dn != nullptr,
+                                         prec, true);
+  if (wide <= static_cast<size_t>(resident_lds_limit(prec))) return launch_resident_w<R, EPT, true>(a, wide, s);
+  return launch_resident_w<R, EPT, false>(a, lds, s);
+}
+
 }  // namespace dev
 
 int resident_lds_limit(int prec) {
   // every instantiation has the same static LDS; the largest one stands for all
-  static const int lim_d = dev::dyn_lds_opt_in(reinterpret_cast<const void*>(dev::k_resident<double, 8>));
-  static const int lim_f = dev::dyn_lds_opt_in(reinterpret_cast<const void*>(dev::k_resident<float, 16>));
+  static const int lim_d = dev::dyn_lds_opt_in(reinterpret_cast<const void*>(dev::k_resident<double, 8, false>));
+  static const int lim_f = dev::dyn_lds_opt_in(reinterpret_cast<const void*>(dev::k_resident<float, 16, false>));
   return prec == 0 ? lim_d : lim_f;
 }
 

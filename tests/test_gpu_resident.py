@@ -310,3 +310,28 @@ def test_resident_automatic_choice(lat, nu, nd, dtype, nv, resident):
         assert hub.hub_controller_read_stats(B.handle)["lanczos_launches"] > 0
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("lat,nu,nd,dtype,bar", [
+    (ring(12), 1, 4, torch.complex128, 1e-12), (ring(12), 1, 4, torch.complex64, 1e-5),
+    (ring(14), 1, 4, torch.complex64, 1e-5), (ring(14), 4, 1, torch.complex64, 1e-5),
+    (chain(9), 4, 4, torch.complex64, 1e-5), (ring(9), 3, 3, torch.complex128, 1e-12)])
+def test_hop_table_entries(lat, nu, nd, dtype, bar):
+    """Sectors near the stepper's limits, whose hop tables have entries of 32
+    bits (12 x 495, 126 x 126, 84 x 84) or, where those leave no room for the
+    tile, of 16 (14 x 1,001 and 1,001 x 14), against the launch path: the same
+    recurrence in another order of summation, four steps."""
+    B = hub.Basis(lat, 8.0, nu, nd, device=0)
+    try:
+        x = random_state(B.dim, seed=21, nvec=2)
+        pulses = [PulseParams(0, 0.3 * (k + 1), 8.0, 0.02, 0.05) for k in range(2)]
+        got = {}
+        for path in (0, 1):
+            hub.hub_set_propagate_path(B.handle, path)
+            v = torch.from_numpy(x).to(DEV).to(dtype).contiguous()
+            _, obs, log = hub.hub_propagate(B.handle, pulses, 0.0, 0.01, 4, hub.make_opts(tol=1e-8, m_max=30), v)
+            got[path] = (v.cpu().numpy().astype(np.complex128), obs)
+        assert np.linalg.norm(got[0][0] - got[1][0]) <= bar * np.linalg.norm(got[0][0])
+        assert np.max(np.abs(got[0][1] - got[1][1])) <= bar * max(1.0, np.max(np.abs(got[0][1])))
+    finally:
+        B.close()
