@@ -242,9 +242,10 @@ hub_status hub_propagate(hub_basis basis, const hub_pulse *pulses, double t_star
  * m_max or turns non-finite (its later observables are NaN), as concurrent
  * groups do on the launch path.  path -1 (default): 1 where it applies, the
  * apply kernels are automatic (hub_set_apply_path -1) and nvec * 6144 is at
- * least the sector's dimension (one workgroup per
- * vector runs at one compute unit's LDS rate: a single large vector is
- * better spread over the GPU), else 0.  Both paths give the same results up
+ * least the sector's dimension (one workgroup per vector runs at one compute
+ * unit's LDS rate: a single large vector is better spread over the GPU; c64
+ * sectors of more than 8,192 states from 33 vectors on, of more than 12,288
+ * from 65), else 0.  Both paths give the same results up
  * to rounding.  Errors: HUB_E_INVALID. */
 hub_status hub_set_propagate_path(hub_basis basis, int32_t path);
 

@@ -1399,12 +1399,13 @@ hub_status hub_observables_noalloc(hub_basis h, const double* A, hub_prec prec, 
 namespace {
 
 // Automatic choice of the resident stepper: nvec vectors of dim states run
-// there when nvec * kResidentAutoElems >= dim.  One workgroup per vector runs
-// at a compute unit's rate, so a single large vector is better spread over
-// the GPU one launch at a time (measured, steps/s resident vs launches, one
-// vector: 6-site 400 states 2.3x, 8-site 4,900 states 1.13-1.16x (c128) and
-// 1.27x (c64), 9-site 7,056 states 0.76x (c128; 1.11x with 4 vectors) and
-// 0.95x (c64); batches of 64 vectors 3-9x).
+// there when nvec * kResidentAutoElems >= dim and nvec is at least
+// resident_min_vectors.  One workgroup per vector runs at a compute unit's
+// rate, so a single large vector is better spread over the GPU one launch at a
+// time (us per step, resident / launches, one vector: 6-site 400 states 32 /
+// 102, 8-site 4,900 states 80 / 109 (c128) and 74 / 108 (c64), 9-site 7,056
+// states 123 / 108 (c128; 126 / 131 with 12 vectors) and 97 / 108 (c64);
+// batches of 64 vectors 44 / 255, 92 / 292 and 149 / 301).
 constexpr int64_t kResidentAutoElems = 6144;
 
 // The resident stepper takes the sector: one workgroup's threads own every
@@ -1599,7 +1600,8 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     // automatic: not where the caller chose the apply kernels (hub_set_apply_path),
     // and only for enough vectors per state
     const bool kernels_auto = h->D.two_pass == -1 && h->D.block_path == -1;
-    const bool worth = static_cast<int64_t>(nvec) * kResidentAutoElems >= dim;
+    const bool worth = static_cast<int64_t>(nvec) * kResidentAutoElems >= dim &&
+                       nvec >= hub::resident_min_vectors(pi, dim);
     if (opts_ok && fits && (h->prop_path == 1 || (kernels_auto && worth)))
       return run_resident(h, prec, nvec, v_inout, n_steps, A_mid, A_sample, A_gauss, t_start, dt, o, obs, log, st);
   }

@@ -54,6 +54,17 @@ inline size_t resident_lds_bytes(int dim_up, int dim_dn, int gs_up, int gs_dn, b
   return t + size_t(dim_up + 1) * (dim_dn + 1) * (prec == 0 ? 16 : 8);
 }
 
+// Vectors from which the resident stepper is the faster one for its larger
+// instantiations (1: at any number).  With 12 or 16 complex64 elements per
+// thread it spills, and the launch path has four groups of eight vectors in
+// flight: us per step, resident / launches, at 1, 8, 32 and 48 vectors 10,584
+// states 164 / 104, 166 / 125, 177 / 160, 193 / 293; at 8, 64 and 96 15,876
+// states 288 / 127, 360 / 319, 393 / 472.
+inline int resident_min_vectors(int prec, int64_t dim) {
+  if (prec == 0 || dim <= 8 * kResidentThreads) return 1;
+  return dim <= 12 * kResidentThreads ? 33 : 65;
+}
+
 // Dynamic LDS the resident kernel of `prec` may use on this device (0 if none).
 int resident_lds_limit(int prec);
 

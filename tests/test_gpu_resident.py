@@ -335,3 +335,17 @@ def test_hop_table_entries(lat, nu, nd, dtype, bar):
         assert np.max(np.abs(got[0][1] - got[1][1])) <= bar * max(1.0, np.max(np.abs(got[0][1])))
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("lat,nu,nd,nv,resident", [
+    (ring(9), 3, 4, 32, False), (ring(9), 3, 4, 33, True),      # 10,584 states
+    (ring(9), 4, 4, 3, False), (ring(9), 4, 4, 65, True)])      # 15,876 states
+def test_automatic_choice_of_large_complex64_tiles(lat, nu, nd, nv, resident):
+    B = hub.Basis(lat, 8.0, nu, nd, device=0)
+    try:
+        x = _vecs(B.dim, nv, 103, torch.complex64)
+        hub.hub_controller_read_stats(B.handle)
+        hub.hub_propagate(B.handle, _pulses(nv), 0.0, 0.02, 2, hub.make_opts(tol=1e-6, m_max=30), x)
+        assert (hub.hub_controller_read_stats(B.handle)["lanczos_launches"] == 0) == resident
+    finally:
+        B.close()
