@@ -453,7 +453,11 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   while (gmax > 1 && hub::apply_lds_bytes(h->D, prec, gmax, 1) > 48 * 1024) gmax /= 2;
   // single vectors run the two-pass kernels with fused updates, which beat
   // interleaved one-pass blocks whenever they apply
-  if (hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) gmax = 1;
+  // (complex128 below 4 MiB: pairs and fours on the one-pass kernels, 11 sites,
+  // 5 vectors 291 vs 371 us a step)
+  const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
+  const bool blocks = automatic && prec == 0 && nvec > 1 && h->D.dim * 16 < 4 * 1024 * 1024;
+  if (!blocks && hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) gmax = 1;
   // except complex64 propagations of several vectors: there blocks of 4 on
   // the two-pass block kernels beat single vectors on concurrent lanes (per
   // vector-step, 8 vectors: 12 sites 139.5 vs 165.5 us, 14 sites 2,204 vs

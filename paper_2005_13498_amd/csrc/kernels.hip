@@ -649,7 +649,12 @@ bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs) {
   // staged columns only the Lanczos iterations gain (fused updates), not a
   // plain apply.
   if (mode == kPlain && !gather && colpass_width(db, prec) < kColW) return false;
-  return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) >= 4.0 * 1024 * 1024;
+  // Lanczos iterations, whose update the row pass then takes in, gain from 1
+  // MiB on: us per step, one pass / two, 10 sites complex128 (1.0 MB) 111 /
+  // 112, 11 sites complex64 (1.7 MB) 142 / 134 and complex128 (3.4 MB) 152 /
+  // 143, 12 sites 4 + 5 complex64 (3.1 MB) 192 / 149.
+  const double least = mode == kPlain ? 4.0 : 1.0;
+  return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) >= least * 1024 * 1024;
 }
 
 int apply_grid(const DevBasis& db, int prec, int nv) {
