@@ -451,18 +451,25 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   }
   int gmax = kMaxNV;
   while (gmax > 1 && hub::apply_lds_bytes(h->D, prec, gmax, 1) > 48 * 1024) gmax /= 2;
-  // single vectors run the two-pass kernels with fused updates, which beat
-  // interleaved one-pass blocks whenever they apply
-  // (complex128 below 4 MiB: pairs and fours on the one-pass kernels, 11 sites,
-  // 5 vectors 291 vs 371 us a step)
-  const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
-  const bool blocks = automatic && prec == 0 && nvec > 1 && h->D.dim * 16 < 4 * 1024 * 1024;
-  if (!blocks && hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) gmax = 1;
-  // except complex64 propagations of several vectors: there blocks of 4 on
-  // the two-pass block kernels beat single vectors on concurrent lanes (per
-  // vector-step, 8 vectors: 12 sites 139.5 vs 165.5 us, 14 sites 2,204 vs
-  // 2,382 us; complex128 singles stay ahead at 12 sites, 251 vs 259 us)
-  if (propagate && prec == 1 && nvec > 1 && gmax == 1 && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
+  // Single vectors run the two-pass kernels with fused updates, which beat
+  // interleaved one-pass blocks whenever they apply.  Propagations of more
+  // vectors take blocks of 4 on the two-pass block kernels, complex64 from 4 on
+  // and complex128 below 8 MiB from 5 on: us a step, singles on concurrent lanes
+  // / fours, 8 vectors: 11 sites c64 376 / 263, c128 450 / 345, 12 sites c64 886
+  // / 762, c128 of 4 + 5 electrons (6.3 MB) 643 / 560, 13 sites c64 3,671 /
+  // 3,130; complex128 singles stay ahead at 12 sites, 1,367 / 1,547.  Fewer
+  // vectors are faster each on a lane of its own than in pairs (2 and 3: 12
+  // sites c64 282 / 342 and 361 / 434, 13 sites c64 778 / 871, 11 sites c128 169
+  // / 187 and 198 / 210) and no slower than one block (4: 11 sites c128 231 /
+  // 244, c64 192 / 199; 13 sites c64 1,853 / 1,641).
+  if (hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) {
+    const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
+    const bool small = automatic && prec == 0 && h->D.dim * 16 < 8 * 1024 * 1024;
+    const bool fours = propagate && (prec == 1 ? nvec > 3 : small && nvec > 4) && hub::block_two_pass(h->D, prec, 4);
+    // where those blocks are not to be had, small tiles keep the one-pass groups
+    if (fours) gmax = 4;
+    else if (!(small && nvec > 4 && h->D.dim * 16 < 4 * 1024 * 1024)) gmax = 1;
+  }
   // plain applies of blocks on the two-pass block kernels: the largest group
   // whose staged row keeps two workgroups per CU (else one).  Propagations
   // keep the rules above unless a tuned plan says otherwise: at 12 sites
