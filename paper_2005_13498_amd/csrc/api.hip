@@ -2492,6 +2492,7 @@ hub_status hub_ground_state(hub_basis h, double A, const hub_krylov_opts* opts, 
   kmax = static_cast<int>(std::min({dim, std::max<int64_t>(kmax, vecs), static_cast<int64_t>(kmax) * kGsWider}));
   s = ensure_workspace(h, static_cast<size_t>(dim) * 16, kmax + 1, 0);
   if (s != HUB_OK && kmax > most) {  // no memory for the wider space
+    (void)hipGetLastError();
     kmax = most;
     s = ensure_workspace(h, static_cast<size_t>(dim) * 16, kmax + 1, 0);
   }
