@@ -320,9 +320,10 @@ hub_status hub_greens_diag(hub_basis basis, int32_t n_targets, const hub_basis *
  * opts.substeps = 1 and target sectors with at most 32 grouped hop slots per
  * string whose tables plus one tile row (and one tile column) fit 148 KiB,
  * else hub_greens_diag returns HUB_E_INVALID.  path -1 (default): 1 where it
- * applies, every target sector has at most 2^18 states and there are at
- * least as many members as compute units (one workgroup per member runs well
- * below a compute unit's share of the bandwidth), else 0.  Both give the same
+ * applies and the largest target sector has at most 8,192 states, 16,384 with
+ * 48 members or more, 32,768 with 96, or 2^18 with as many members as compute
+ * units (one workgroup per member runs well below a compute unit's share of
+ * the bandwidth), else 0.  Both give the same
  * overlaps up to rounding.  Errors: HUB_E_INVALID. */
 hub_status hub_set_greens_path(hub_basis basis, int32_t path);
 

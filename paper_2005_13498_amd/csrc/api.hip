@@ -1945,15 +1945,25 @@ hub_status hub_dot(hub_basis h, hub_prec prec, int32_t nvec, const void* x, cons
 
 namespace {
 
-// LDS staging of the persistent member stepper; the largest target sector and
-// the fewest members (per compute unit) for which it is the automatic choice:
-// one workgroup per member runs well below a compute unit's share of the
-// bandwidth, so it pays only once every unit has a member (10-site sectors:
-// 64 members 0.6x, 256 members 1.45x the per-sector batches), and larger
-// sectors fill the GPU one apply at a time.
-constexpr size_t kMembersLds = 148 << 10;  // tables + staging per member workgroup
-constexpr int64_t kMembersAutoDim = 1 << 18;
-constexpr int kMembersAutoPerCU = 1;
+constexpr size_t kMembersLds = 148 << 10;  // tables + staging per member workgroup of the persistent stepper
+
+// The fewest members for which the persistent stepper is the automatic choice,
+// by the largest target sector (0: never).  One workgroup per member runs well
+// below a compute unit's share of the bandwidth, but all members at once and
+// without launches: short sectors gain with any number, longer ones once
+// enough units have a member, and the largest fill the GPU one apply at a
+// time.  Whole calls of 12 relative steps, per sector / persistent, in ms: 8
+// sites (4,900 states) complex64 4 members 4.6 / 3.1, 64 members 8.1 / 4.1; 9
+// sites (15,876) 16 members 5.1 / 5.5, 32 5.7 / 6.4, 48 8.5 / 7.0, complex128
+// 48 8.2 / 8.3; 10 sites (25,200) 64 9.0 / 8.8, complex128 9.2 / 10.4, 96 12.3
+// / 10.9; 20 steps of 10 sites (52,920) 64 16.3 / 26.6, 128 28.6 / 29.7, 256
+// 52.9 / 38.1.
+int members_auto_least(int64_t dim, int n_cu) {
+  if (dim <= 8192) return 1;
+  if (dim <= 16384) return 48;
+  if (dim <= 32768) return 96;
+  return dim <= 1 << 18 ? n_cu : 0;
+}
 
 // Members of one target sector in hub_greens_diag.
 struct GreensSector {
@@ -2145,7 +2155,7 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
   // the three-term recurrence with one solve per step and the grouped hop
   // tables of every target sector, with a tile row and a tile column in LDS.
   bool members_fit = opts->reorth == 0 && opts->substeps == 1;
-  bool members_small = true;
+  int64_t members_dim = 0;
   for (int k = 0; k < n_members && members_fit; ++k) {
     const hub::Basis& TB = targets[tb[k]]->B;
     const DevBasis& TD = targets[tb[k]]->D;
@@ -2154,16 +2164,16 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
                                               TD.eps_up != nullptr || TD.eps_dn != nullptr, map_len);
     members_fit = (TD.dn_gslots > 0 || TB.dn.max_hops == 0) && (TD.up_gslots > 0 || TB.up.max_hops == 0) &&
                   tab + (TD.dim_dn + 1) * es <= kMembersLds && tab + (TD.dim_up + 1) * es <= kMembersLds;
-    members_small &= TD.dim <= kMembersAutoDim;
+    members_dim = std::max(members_dim, TD.dim);
   }
   if (h->greens_path == 1 && !members_fit)
     return fail(HUB_E_INVALID, "the persistent member stepper needs reorth 0, substeps 1 and grouped hop tables");
   int n_cu = 0;
   if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || n_cu < 1)
     n_cu = 256;
-  const bool members_many = n_members >= kMembersAutoPerCU * n_cu;
+  const int members_least = members_auto_least(members_dim, n_cu);
   const bool use_members =
-      h->greens_path == 1 || (h->greens_path == -1 && members_fit && members_small && members_many);
+      h->greens_path == 1 || (h->greens_path == -1 && members_fit && members_least > 0 && n_members >= members_least);
   // Device buffers: psi at every step (the trajectory), the members of every
   // target sector in the ABI layout (ordered by start step), their operator
   // maps packed per sector [member][map_len], overlap partials per sector

@@ -282,3 +282,28 @@ def test_greens_ring10_all_64_members(c3_reference, path):
         B.close()
         for t in T:
             t.close()
+
+
+@pytest.mark.parametrize("lat,nu,nd,members,persistent", [
+    (ring(8), 4, 4, 1, True), (ring(8), 4, 4, 5, True),       # sectors of at most 8,192 states
+    (ring(9), 4, 4, 47, False), (ring(9), 4, 4, 48, True),    # 16,384
+    (ring(10), 3, 3, 95, False), (ring(10), 3, 3, 96, True)])  # 32,768
+def test_automatic_member_stepper(lat, nu, nd, members, persistent):
+    """The automatic choice gives the chosen stepper's overlaps bit for bit and
+    the other's up to rounding (complex128, three steps)."""
+    B = hub.Basis(lat, 8.0, nu, nd)
+    T = [hub.Basis(lat, 8.0, nu + a, nd + b) for a, b in ((1, 0), (-1, 0), (0, 1), (0, -1))]
+    psi = _dev(random_state(B.dim, seed=8)[0], torch.complex128)
+    m = [(k // 4 % lat.n_sites, k % 2, k // 2 % 2, k // 16 % 3) for k in range(members)]
+    try:
+        out = {}
+        for path in (-1, 0, 1):
+            hub.hub_set_greens_path(B.handle, path)
+            out[path] = hub.hub_greens_diag(B.handle, [t.handle for t in T], PulseParams(0, 0.4, 8.0, 0.02, 0.05), 0.0,
+                                            0.01, 3, hub.make_opts(tol=1e-10, m_max=30), m, psi.clone())
+        assert np.array_equal(out[-1], out[1 if persistent else 0])
+        assert np.max(np.abs(out[0] - out[1])) <= 1e-12
+    finally:
+        B.close()
+        for t in T:
+            t.close()
