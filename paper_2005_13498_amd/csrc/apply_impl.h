@@ -898,6 +898,7 @@ hipError_t apply_mode(const ApplyLaunch& L, int grid, size_t lds, int* pgrid) {
     const bool two = apply_two_pass(*L.db, L.prec, 1, L.mode, L.obs);
     const bool gather = two && L.mode == kPlain && apply_gathers(*L.db, L.prec);
     if (apply_global_rows(*L.db, L.prec, 1)) {  // a row does not fit LDS
+      if (L.fuse) return hipErrorInvalidValue;  // these kernels leave the update to k_update
       if (gather) {
         const hipError_t e = rowgather<R>(L);
         return e != hipSuccess ? e : colgather<R>(L);

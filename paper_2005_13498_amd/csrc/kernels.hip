@@ -641,7 +641,9 @@ bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs) {
   if (nv != 1 || !(mode == kPlain || mode == kLanczos) || db.two_pass == 0 || !db.up_tab) return false;
   if (obs && mode != kLanczos) return false;
   const bool gather = mode == kPlain && apply_gathers(db, prec);
-  if (!gather && colpass_lds_bytes(db, prec) > 150 * 1024) return false;
+  // rows too long for LDS have a row pass of their own only where the column
+  // pass gathers (k_rowgather); their other kernels do it all in one pass
+  if (!gather && (apply_global_rows(db, prec, 1) || colpass_lds_bytes(db, prec) > 150 * 1024)) return false;
   if (db.two_pass == 1) return true;
   if (db.tuned_single[prec] >= 0) return db.tuned_single[prec] == 1;
   // automatic: when a vector is larger than one XCD's L2 the up-hop row
