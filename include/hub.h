@@ -458,8 +458,9 @@ hub_status hub_set_schedule(hub_basis basis, int32_t chunk, int32_t margin);
  *           applies of vectors larger than 32 MiB, whose column pass gathers
  *           from global memory in an order that the L2s hold;
  *   path -1 (default): two passes when they fit and the vector is larger
- *           than 4 MiB (Lanczos iterations of single vectors: 1 MiB), one
- *           pass otherwise.
+ *           than 4 MiB (Lanczos iterations of single vectors: 1 MiB where
+ *           there are 256 down strings and 64 up strings), one pass
+ *           otherwise.
  * Blocks of 2, 4 or 8 vectors (paths 1 and -1) run the two-pass block
  * kernels where a tile row and a tile column of the whole block fit LDS: a
  * row pass (diagonal and down hops) and a column pass (up hops, Lanczos

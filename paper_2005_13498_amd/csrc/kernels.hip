@@ -652,10 +652,15 @@ bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs) {
   // plain apply.
   if (mode == kPlain && !gather && colpass_width(db, prec) < kColW) return false;
   // Lanczos iterations, whose update the row pass then takes in, gain from 1
-  // MiB on: us per step, one pass / two, 10 sites complex128 (1.0 MB) 111 /
-  // 112, 11 sites complex64 (1.7 MB) 142 / 134 and complex128 (3.4 MB) 152 /
-  // 143, 12 sites 4 + 5 complex64 (3.1 MB) 192 / 149.
-  const double least = mode == kPlain ? 4.0 : 1.0;
+  // MiB on where the column pass has a workgroup for every fourth unit, 256
+  // columns, and the row pass 64 rows: us per step, one pass / two, 10 sites
+  // complex128 (1.0 MB) 111 / 112, 11 sites complex64 (1.7 MB) 142 / 134 and
+  // complex128 (3.4 MB) 152 / 143, 12 sites 4 + 5 complex64 (3.1 MB) 192 / 149;
+  // tall tiles, complex64, 3 steps: 3,432 x 91 (14 sites, 2.4 MB) 830 / 1,013,
+  // 3,003 x 105 764 / 906, 1,716 x 286 (13 sites, 3.7 MB) 810 / 705; 16 x 4,368
+  // (complex128, 1.1 MB), 8 vectors on concurrent lanes, 1,910 / 2,133.
+  const bool spread = mode != kPlain && db.dim_dn >= 256 && db.dim_up >= 64;
+  const double least = spread ? 1.0 : 4.0;
   return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) >= least * 1024 * 1024;
 }
 
