@@ -244,9 +244,10 @@ hub_status hub_propagate(hub_basis basis, const hub_pulse *pulses, double t_star
  * apply kernels are automatic (hub_set_apply_path -1) and nvec * 6144 is at
  * least the sector's dimension (one workgroup per vector runs at one compute
  * unit's LDS rate: a single large vector is better spread over the GPU; c64
- * sectors of more than 8,192 states from 33 vectors on, of more than 12,288
- * from 65), else 0.  Both paths give the same results up
- * to rounding.  Errors: HUB_E_INVALID. */
+ * sectors of more than 8,192 states from 9 vectors on where there are at most
+ * 9,600 states (from 5 with 512 down strings), or 768 down strings, or with at
+ * most 12,288 states 768 up strings, other ones from 33), else 0.  Both paths give the same
+ * results up to rounding.  Errors: HUB_E_INVALID. */
 hub_status hub_set_propagate_path(hub_basis basis, int32_t path);
 
 /* Ground state of H(A) (Sec. 3.4 "Ground state"): restarted Lanczos

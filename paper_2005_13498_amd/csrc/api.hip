@@ -1612,7 +1612,7 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     // and only for enough vectors per state
     const bool kernels_auto = h->D.two_pass == -1 && h->D.block_path == -1;
     const bool worth = static_cast<int64_t>(nvec) * kResidentAutoElems >= dim &&
-                       nvec >= hub::resident_min_vectors(pi, dim);
+                       nvec >= hub::resident_min_vectors(pi, h->D.dim_up, h->D.dim_dn);
     if (opts_ok && fits && (h->prop_path == 1 || (kernels_auto && worth)))
       return run_resident(h, prec, nvec, v_inout, n_steps, A_mid, A_sample, A_gauss, t_start, dt, o, obs, log, st);
   }

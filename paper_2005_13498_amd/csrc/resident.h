@@ -57,12 +57,22 @@ inline size_t resident_lds_bytes(int dim_up, int dim_dn, int gs_up, int gs_dn, b
 // Vectors from which the resident stepper is the faster one for its larger
 // instantiations (1: at any number).  With 12 or 16 complex64 elements per
 // thread it spills, and the launch path has four groups of eight vectors in
-// flight: us per step, resident / launches, at 1, 8, 32 and 48 vectors 10,584
-// states 164 / 104, 166 / 125, 177 / 160, 193 / 293; at 8, 64 and 96 15,876
-// states 288 / 127, 360 / 319, 393 / 472.
-inline int resident_min_vectors(int prec, int64_t dim) {
+// flight, of fewer where the tile is long.  us for three steps, resident /
+// launches, at 8, 12, 24, 32 and 48 vectors: 9,075 states (55 x 165) 501 / 456,
+// 510 / 561, 519 / 619, 529 / 662, 590 / -; 10,584 (84 x 126) 665 / 507, 674 /
+// 601, 690 / 693, 711 / 710, 808 / -; 15,876 (126 x 126) 1,057 / 507, 1,064 /
+// 593, 1,151 / 697, 1,195 / 726, 1,219 / 1,264; 12 x 924 692 / 689, 697 / 1,145,
+// 710 / 1,835, 726 / 2,387; 924 x 12 701 / 660, 707 / 775, 718 / 857, 737 / 929;
+// 14 x 1,001 784 / 669, 788 / 1,161, 814 / 1,822; 1,001 x 14 866 / 623, 871 /
+// 771, 891 / 857, 969 / 933, 1,006 / 1,613; at 4 and 8 13 x 715 481 / 466, 488 /
+// 565.
+inline int resident_min_vectors(int prec, int dim_up, int dim_dn) {
+  const int64_t dim = static_cast<int64_t>(dim_up) * dim_dn;
   if (prec == 0 || dim <= 8 * kResidentThreads) return 1;
-  return dim <= 12 * kResidentThreads ? 33 : 65;
+  constexpr int kLong = 768;
+  const bool longer = dim_dn >= kLong || (dim_up >= kLong && dim <= 12 * kResidentThreads);
+  if (dim <= 9600) return dim_dn >= 512 ? 5 : 9;
+  return longer ? 9 : 33;
 }
 
 // Dynamic LDS the resident kernel of `prec` may use on this device (0 if none).
