@@ -431,10 +431,15 @@ hub_status prof_harvest(hub_basis h, size_t from, size_t* end) {
   return HUB_OK;
 }
 
+// A propagation's groups share the event pool of the apply timing, or the
+// learned controller's buffers, and so run on one lane.
+bool one_lane_only(hub_basis h, bool pulsed) { return h->prof || (h->ctrl_on && pulsed); }
+
 // Group sizes for nvec vectors: powers of two up to 8 whose staged row keeps
 // at least three apply workgroups per CU (<= 48 KB of the 160 KB LDS), or one
 // vector per group; single vectors where the two-pass kernels apply.
-std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = true) {
+// one_lane: the groups of a propagation run one after another.
+std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = true, bool one_lane = false) {
   const int prop = nvec > kMaxNV && h->prop_group_large[prec] > 0 ? h->prop_group_large[prec] : h->prop_group[prec];
   const int tuned = h->force_group > 0 ? h->force_group : (propagate ? prop : h->apply_group[prec]);
   if (tuned > 0) {
@@ -461,14 +466,22 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   // vectors are faster each on a lane of its own than in pairs (2 and 3: 12
   // sites c64 282 / 342 and 361 / 434, 13 sites c64 778 / 871, 11 sites c128 169
   // / 187 and 198 / 210) and no slower than one block (4: 11 sites c128 231 /
-  // 244, c64 192 / 199; 13 sites c64 1,853 / 1,641).
-  if (hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) {
-    const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
-    const bool small = automatic && prec == 0 && h->D.dim * 16 < 8 * 1024 * 1024;
+  // 244, c64 192 / 199; 13 sites c64 1,853 / 1,641).  On one lane a group is
+  // never split: three steps timed, singles / pair or block, 12 sites c64, 2
+  // vectors, 1,768 / 1,497; 11 sites c128, 2 and 4, 1,727 / 1,233 and 3,407 /
+  // 2,440, c64, 2, 1,559 / 995; 12 sites of 6 + 3 c64, 8, fours 1,937, one
+  // block of 8 1,678.
+  const double mib = static_cast<double>(h->D.dim) * (prec == 0 ? 16 : 8) / (1024.0 * 1024.0);
+  const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
+  const bool mid = automatic && mib >= 1.0 && mib < 4.0;  // single vectors: two passes or, in tall tiles, one
+  if (mid || hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) {
+    const bool small = automatic && prec == 0 && mib < 8.0;
     const bool fours = propagate && (prec == 1 ? nvec > 3 : small && nvec > 4) && hub::block_two_pass(h->D, prec, 4);
     // where those blocks are not to be had, small tiles keep the one-pass groups
-    if (fours) gmax = 4;
-    else if (!(small && nvec > 4 && h->D.dim * 16 < 4 * 1024 * 1024)) gmax = 1;
+    if (one_lane) gmax = mid ? gmax : 1;
+    else if (fours || !(small && nvec > 4 && mid)) gmax = 1;
+    if (fours) gmax = std::max(gmax, 4);
+    else if (one_lane && prec == 1 && nvec > 1 && gmax == 1 && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
   }
   // plain applies of blocks on the two-pass block kernels: the largest group
   // whose staged row keeps two workgroups per CU (else one).  Propagations
@@ -1616,7 +1629,7 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     if (opts_ok && fits && (h->prop_path == 1 || (kernels_auto && worth)))
       return run_resident(h, prec, nvec, v_inout, n_steps, A_mid, A_sample, A_gauss, t_start, dt, o, obs, log, st);
   }
-  const std::vector<int> groups = groups_for(h, nvec, pi);
+  const std::vector<int> groups = groups_for(h, nvec, pi, true, one_lane_only(h, dA_mid != nullptr));
   const bool want_obs = obs != nullptr && A_sample != nullptr;
   const int E = scheme_exps(o);
 
@@ -1680,11 +1693,10 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     R.ran = true;
   };
 
-  // Lanes: groups run concurrently when there are several, unless the apply
-  // timing (shared event pool) or the learned controller (shared MLP buffers)
-  // is on, or the lanes' Krylov workspaces would exceed the budget.
+  // Lanes: groups run concurrently when there are several, unless one lane has
+  // to do or the lanes' Krylov workspaces would exceed the budget.
   int nlanes = 1;
-  if (groups.size() > 1 && !h->prof && !(h->ctrl_on && dA_mid)) {
+  if (groups.size() > 1 && !one_lane_only(h, dA_mid != nullptr)) {
     const int gmax = *std::max_element(groups.begin(), groups.end());
     const size_t per_lane = static_cast<size_t>(o.m_max + 2) * dim * gmax * es;  // slots and block buffer
     nlanes = static_cast<int>(std::min<size_t>(kMaxLanes, groups.size()));
@@ -2883,7 +2895,7 @@ hub_status hub_get_plan(hub_basis h, hub_prec prec, int32_t nvec, int32_t propag
   const int pi = prec == HUB_C128 ? 0 : 1;
   std::vector<ApplyGroup> g;
   if (propagate)
-    for (int nv : groups_for(h, nvec, pi)) g.push_back({nv, -1});
+    for (int nv : groups_for(h, nvec, pi, true, one_lane_only(h, true))) g.push_back({nv, -1});
   else
     g = apply_groups(h, nvec, pi);
   *n_groups = static_cast<int32_t>(g.size());

@@ -46,3 +46,14 @@ def test_resident_stepper_of_large_complex64_tiles(n, nu, nd, nvec, resident):
         assert (hub.hub_controller_read_stats(B.handle)["lanczos_launches"] == 0) == resident
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("n,nu,nd,prec,nvec,lanes,one", [
+    (12, 6, 6, C64, 2, [1, 1], [2]), (12, 6, 6, C64, 3, [1, 1, 1], [2, 1]), (12, 6, 6, C64, 8, [4, 4], [4, 4]),
+    (11, 5, 5, C128, 2, [1, 1], [2]), (11, 5, 5, C64, 2, [1, 1], [2]), (12, 6, 3, C64, 8, [4, 4], [8]),
+    (11, 5, 3, C128, 8, [4, 4], [8]), (12, 6, 6, C128, 3, [1, 1, 1], [1, 1, 1])])
+def test_groups_on_one_lane(n, nu, nd, prec, nvec, lanes, one):
+    """Apply timing leaves one lane, on which groups run one after another."""
+    got = [g for g, _ in _plan(ring(n), nu, nd, prec, nvec)]
+    assert got == lanes
+    assert [g for g, _ in _plan(ring(n), nu, nd, prec, nvec, setup=lambda h: hub.hub_profile_enable(h, 1))] == one
