@@ -482,6 +482,13 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
     else if (fours || !(small && nvec > 4 && mid)) gmax = 1;
     if (fours) gmax = std::max(gmax, 4);
     else if (one_lane && prec == 1 && nvec > 1 && gmax == 1 && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
+  } else if (propagate && prec == 1 && gmax == 1) {
+    // smaller tiles with long rows: fours where several would share a lane (us
+    // for three steps, singles on lanes / fours: 13 x 1,716 5 and 12 vectors
+    // 1,323 / 1,006 and 2,379 / 1,355; 16 x 4,368 4, 8 and 12 vectors 794 / 1,462,
+    // 1,517 / 1,732 and 2,213 / 1,991; one lane, 4 vectors 2,853 / 1,687)
+    const int least = one_lane ? 2 : (h->D.dim_dn < 2048 ? 5 : 9);
+    if (nvec >= least && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
   }
   // plain applies of blocks on the two-pass block kernels: the largest group
   // whose staged row keeps two workgroups per CU (else one).  Propagations

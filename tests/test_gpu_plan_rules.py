@@ -57,3 +57,11 @@ def test_groups_on_one_lane(n, nu, nd, prec, nvec, lanes, one):
     got = [g for g, _ in _plan(ring(n), nu, nd, prec, nvec)]
     assert got == lanes
     assert [g for g, _ in _plan(ring(n), nu, nd, prec, nvec, setup=lambda h: hub.hub_profile_enable(h, 1))] == one
+
+
+@pytest.mark.parametrize("n,nu,nd,nvec,lanes,one", [
+    (13, 1, 6, 4, [1] * 4, [4]), (13, 1, 6, 5, [4, 1], [4, 1]), (16, 1, 5, 8, [1] * 8, [4, 4]),
+    (16, 1, 5, 9, [4, 4, 1], [4, 4, 1]), (14, 1, 7, 2, [1, 1], [2])])
+def test_groups_of_small_tiles_with_long_rows(n, nu, nd, nvec, lanes, one):
+    assert [g for g, _ in _plan(ring(n), nu, nd, C64, nvec)] == lanes
+    assert [g for g, _ in _plan(ring(n), nu, nd, C64, nvec, setup=lambda h: hub.hub_profile_enable(h, 1))] == one
