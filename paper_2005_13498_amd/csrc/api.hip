@@ -465,9 +465,7 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   // 3,130; complex128 singles stay ahead at 12 sites, 1,367 / 1,547.  Fewer
   // vectors are faster each on a lane of its own than in pairs (2 and 3: 12
   // sites c64 282 / 342 and 361 / 434, 13 sites c64 778 / 871, 11 sites c128 169
-  // / 187 and 198 / 210) and no slower than one block (4: 11 sites c128 231 /
-  // 244, c64 192 / 199; 13 sites c64 1,853 / 1,641).  On one lane a group is
-  // never split: three steps timed, singles / pair or block, 12 sites c64, 2
+  // / 187 and 198 / 210).  On one lane a group is never split: three steps timed, singles / pair or block, 12 sites c64, 2
   // vectors, 1,768 / 1,497; 11 sites c128, 2 and 4, 1,727 / 1,233 and 3,407 /
   // 2,440, c64, 2, 1,559 / 995; 12 sites of 6 + 3 c64, 8, fours 1,937, one
   // block of 8 1,678.
@@ -477,9 +475,12 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   if (mid || hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) {
     const bool small = automatic && prec == 0 && mib < 8.0;
     const bool fours = propagate && (prec == 1 ? nvec > 3 : small && nvec > 4) && hub::block_two_pass(h->D, prec, 4);
-    // where those blocks are not to be had, small tiles keep the one-pass groups
+    // where those blocks are not to be had, and for four complex128 vectors,
+    // small tiles keep the groups of their rows (4 vectors, three steps, singles
+    // / groups: 11 sites of 4 + 4 1,223 / 753, 15 of 3 + 3 1,245 / 887, 16 of 5 +
+    // 1 2,336 / 1,414)
     if (one_lane) gmax = mid ? gmax : 1;
-    else if (fours || !(small && nvec > 4 && mid)) gmax = 1;
+    else if (fours || !mid || (propagate && nvec < 4)) gmax = 1;
     if (fours) gmax = std::max(gmax, 4);
     else if (one_lane && prec == 1 && nvec > 1 && gmax == 1 && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
   } else if (propagate && prec == 1 && gmax == 1) {

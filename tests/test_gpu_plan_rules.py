@@ -65,3 +65,9 @@ def test_groups_on_one_lane(n, nu, nd, prec, nvec, lanes, one):
 def test_groups_of_small_tiles_with_long_rows(n, nu, nd, nvec, lanes, one):
     assert [g for g, _ in _plan(ring(n), nu, nd, C64, nvec)] == lanes
     assert [g for g, _ in _plan(ring(n), nu, nd, C64, nvec, setup=lambda h: hub.hub_profile_enable(h, 1))] == one
+
+
+@pytest.mark.parametrize("n,nu,nd,groups", [(11, 4, 4, [4]), (11, 3, 5, [2, 2]), (16, 5, 1, [4]), (12, 3, 6, [1] * 4),
+                                            (12, 6, 6, [1] * 4)])
+def test_groups_of_four_complex128_vectors(n, nu, nd, groups):
+    assert [g for g, _ in _plan(ring(n), nu, nd, C128, 4)] == groups
