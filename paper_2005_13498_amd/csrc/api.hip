@@ -515,6 +515,20 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   return g;
 }
 
+// Tiles whose rows do not suit a workgroup of 256 threads per row and vector
+// (the batches' one pass): a great many short rows, where the interleaved
+// groups are one-pass ones with all vectors in a row (8 vectors, us, batch /
+// groups: 12,870 x 16 complex128 156 / 57, 8,008 x 16 86 / 40, 3,432 x 1 37 /
+// 16, 2 vectors of 12,870 x 1 complex64 33 / 23, 4 of 6,435 x 1 31 / 17), and two
+// vectors of a few long rows, for which the other kernels have larger
+// workgroups (15 x 6,435 complex64 36.7 / 32.5, 1 x 3,432 complex128 19.3 /
+// 15.5; 14 x 3,432 26.4 / 28.8).
+bool batch_misfit(hub_basis h, int nvec, int prec) {
+  const int64_t rows = static_cast<int64_t>(h->D.dim_up) * std::min(nvec, kMaxNV);
+  if (h->D.dim_dn < 64 && rows >= 8192 && !hub::block_two_pass(h->D, prec, 2)) return true;
+  return nvec == 2 && h->D.dim_up < 64 && h->D.dim_dn >= (h->D.dim_up < 8 ? 2048 : 4096);
+}
+
 // hub_apply_H's groups of the automatic rule: batches in the caller's layout
 // (columns: batch_columns) where the caller and no tuned plan chose kernels or
 // group sizes, else the interleaved groups (columns -1) of groups_for.
@@ -523,7 +537,8 @@ struct ApplyGroup {
 };
 std::vector<ApplyGroup> apply_groups(hub_basis h, int nvec, int prec) {
   std::vector<ApplyGroup> g;
-  if (nvec > 1 && h->force_group == 0 && h->apply_group[prec] <= 0 && h->D.two_pass == -1 && h->D.block_path == -1) {
+  if (nvec > 1 && h->force_group == 0 && h->apply_group[prec] <= 0 && h->D.two_pass == -1 && h->D.block_path == -1 &&
+      !batch_misfit(h, nvec, prec)) {
     // where a batch could stage only two columns, or none, vectors that gather
     // theirs go one by one: a vector of 14 sites takes 131 us instead of 213
     // (complex64) or 250 instead of 286 (complex128), of 15 sites 590 instead

@@ -71,3 +71,28 @@ def test_groups_of_small_tiles_with_long_rows(n, nu, nd, nvec, lanes, one):
                                             (12, 6, 6, [1] * 4)])
 def test_groups_of_four_complex128_vectors(n, nu, nd, groups):
     assert [g for g, _ in _plan(ring(n), nu, nd, C128, 4)] == groups
+
+
+@pytest.mark.parametrize("n,nu,nd,prec,nvec,groups", [
+    (16, 8, 1, C128, 8, [(8, 0)]), (16, 6, 1, C128, 8, [(8, 0)]), (14, 7, 0, C64, 8, [(8, 0)]), (16, 8, 0, C64, 2, [(2, 0)]),
+    (15, 1, 7, C64, 2, [(2, 2)]), (14, 0, 7, C128, 2, [(1, 0)] * 2), (14, 1, 7, C128, 2, [(2, 0)]),
+    (14, 7, 1, C128, 8, [(8, 0)])])
+def test_products_of_tiles_with_few_or_many_rows(n, nu, nd, prec, nvec, groups):
+    """The plan, and its products against single vectors: a component is a sum
+    of at most 32 hops and the diagonal, so within 64 eps |H|_inf max|x|."""
+    B = hub.Basis(ring(n), 8.0, nu, nd, device=0)
+    try:
+        assert hub.hub_get_plan(B.handle, prec, nvec, False) == groups
+        dtype = torch.complex128 if prec == C128 else torch.complex64
+        g = torch.Generator(device="cuda:0").manual_seed(4)
+        x = torch.randn(nvec, B.dim, dtype=dtype, device="cuda:0", generator=g)
+        y, z = torch.full_like(x, float("nan")), torch.empty_like(x)
+        A = [0.2 * k - 0.3 for k in range(nvec)]
+        hub.hub_apply_H(B.handle, A, x, y)
+        for k in range(nvec):
+            hub.hub_apply_H(B.handle, [A[k]], x[k], z[k])
+        eps = 2.0 ** (-52 if prec == C128 else -23)
+        bound = 64 * eps * hub.hub_basis_classes(B.handle)[2] * float(torch.max(torch.abs(torch.view_as_real(x))))
+        assert float(torch.max(torch.abs(torch.view_as_real(y - z)))) <= bound
+    finally:
+        B.close()
