@@ -192,10 +192,17 @@ hub_status work_init(Work& W, bool own_stream) {
       hipHostMalloc(reinterpret_cast<void**>(&W.h_ptrs), (kMMax + 2) * sizeof(void*), hipHostMallocDefault) !=
           hipSuccess)
     return fail(HUB_E_NOMEM, "workspace allocation failed");
-  if (hipMemset(W.ctl, 0, sizeof(StepCtl)) != hipSuccess || hipMemset(W.st, 0, kMaxNV * sizeof(VecState)) != hipSuccess)
-    return fail(HUB_E_DEVICE, "workspace initialisation failed");
   if (own_stream && hipStreamCreateWithFlags(&W.stream, hipStreamNonBlocking) != hipSuccess)
     return fail(HUB_E_DEVICE, "stream creation failed");
+  // Cleared before anything else on the lane's stream: a lane is created in
+  // the middle of a call, where the null stream may share a hardware queue
+  // with other lanes' work, hipMemset returns before it has run, and a lane's
+  // stream does not wait for the null stream.  Lane 0 runs on any stream, so
+  // its memory is clear on return.
+  if (hipMemsetAsync(W.ctl, 0, sizeof(StepCtl), W.stream) != hipSuccess ||
+      hipMemsetAsync(W.st, 0, kMaxNV * sizeof(VecState), W.stream) != hipSuccess ||
+      (!own_stream && hipStreamSynchronize(nullptr) != hipSuccess))
+    return fail(HUB_E_DEVICE, "workspace initialisation failed");
   return HUB_OK;
 }
 
