@@ -234,7 +234,8 @@ hub_status hub_propagate(hub_basis basis, const hub_pulse *pulses, double t_star
  * combine, and the observables of each step's input at its sample time; only
  * the Krylov vectors u_1 .. u_{m-1} of a step go to device memory.  It takes
  * sectors of at most 8,192 states (c128) or 16,384 (c64) whose tile and
- * tables fit a workgroup's LDS (8 sites at half filling: 4,900 states),
+ * tables fit a workgroup's LDS (8 sites at half filling: 4,900 states) and
+ * whose hops take at most 32 grouped slots per string,
  * opts.reorth = 0 (either scheme, any substeps: the step's Krylov solves run
  * one after another in the workgroup), and neither apply timing
  * (hub_profile_enable) nor the learned controller; else hub_propagate
@@ -246,8 +247,8 @@ hub_status hub_propagate(hub_basis basis, const hub_pulse *pulses, double t_star
  * unit's LDS rate: a single large vector is better spread over the GPU; c64
  * sectors of more than 8,192 states from 9 vectors on where there are at most
  * 9,600 states (from 5 with 512 down strings), or 768 down strings, or with at
- * most 12,288 states 768 up strings, other ones from 33), else 0.  Both paths give the same
- * results up to rounding.  Errors: HUB_E_INVALID. */
+ * most 12,288 states 768 up strings, other ones from 33), else 0.  Both paths
+ * give the same results up to rounding.  Errors: HUB_E_INVALID. */
 hub_status hub_set_propagate_path(hub_basis basis, int32_t path);
 
 /* Ground state of H(A) (Sec. 3.4 "Ground state"): restarted Lanczos

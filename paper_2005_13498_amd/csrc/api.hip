@@ -1467,8 +1467,8 @@ constexpr int64_t kResidentAutoElems = 6144;
 bool resident_fits(hub_basis h, int pi) {
   const DevBasis& D = h->D;
   if (D.dim < 1 || D.dim > static_cast<int64_t>(hub::kResidentThreads) * hub::kResidentEpt[pi]) return false;
-  if (D.dn_gslots > 32 || D.up_gslots > 32) return false;
-  if ((D.dn_gslots > 0 && !D.dn_tabg) || (D.up_gslots > 0 && !D.up_tabg)) return false;
+  // no grouped table (hops of more than 32 slots), though there are hops
+  if ((D.dn_gslots == 0 && h->B.dn.max_hops > 0) || (D.up_gslots == 0 && h->B.up.max_hops > 0)) return false;
   const size_t lds = hub::resident_lds_bytes(D.dim_up, D.dim_dn, D.up_gslots, D.dn_gslots,
                                              D.eps_up != nullptr || D.eps_dn != nullptr, pi);
   return lds <= static_cast<size_t>(hub::resident_lds_limit(pi));

@@ -76,3 +76,28 @@ def test_long_range_propagation(name, lat, U, nu, nd):
             assert np.max(np.abs(obs[:, k, 3] - r[:, 1])) < 1e-10
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("seed,n_bonds,nu,nd", [(3, 18, 3, 3), (3, 20, 3, 4)])
+def test_more_hops_than_the_resident_tables_hold(seed, n_bonds, nu, nd):
+    """Graphs of 7 sites whose hops need 36 table slots, more than the 32 of
+    the resident stepper's tables: it refuses them, and a propagation takes
+    the launch path, within 1e-10 of the exact stepper."""
+    lat = random_graph(7, n_bonds, seed=seed)
+    ham = HubbardOracle(lat, 4.0, nu, nd)
+    B = hub.Basis(lat, 4.0, nu, nd)
+    try:
+        pulse, steps, dt = PulseParams(0, 0.9, 6.0, 0.1, 0.2), 20, 0.01
+        v = random_state(ham.dim, seed=31)[0]
+        x = torch.from_numpy(to_canonical(v, ham.states, 7)).to(DEV)
+        opts = hub.make_opts(tol=1e-13, m_max=30)
+        hub.hub_set_propagate_path(B.handle, 1)
+        with pytest.raises(hub.HubError, match="does not fit"):
+            hub.hub_propagate(B.handle, [pulse], 0.0, dt, steps, opts, x.clone())
+        hub.hub_set_propagate_path(B.handle, -1)
+        hub.hub_propagate(B.handle, [pulse], 0.0, dt, steps, opts, x)
+        for s in range(steps):
+            v = midpoint_step_exact(ham, v, s * dt, dt, pulse)
+        assert _rel(from_canonical(x.cpu().numpy(), ham.states, 7), v) < 1e-10
+    finally:
+        B.close()
