@@ -438,6 +438,11 @@ hub_status prof_harvest(hub_basis h, size_t from, size_t* end) {
   return HUB_OK;
 }
 
+// An installed plan's vectors per group of a propagation (none: -1).
+int tuned_prop_group(hub_basis h, int nvec, int prec) {
+  return nvec > kMaxNV && h->prop_group_large[prec] > 0 ? h->prop_group_large[prec] : h->prop_group[prec];
+}
+
 // A propagation's groups share the event pool of the apply timing, or the
 // learned controller's buffers, and so run on one lane.
 bool one_lane_only(hub_basis h, bool pulsed) { return h->prof || (h->ctrl_on && pulsed); }
@@ -447,8 +452,8 @@ bool one_lane_only(hub_basis h, bool pulsed) { return h->prof || (h->ctrl_on && 
 // vector per group; single vectors where the two-pass kernels apply.
 // one_lane: the groups of a propagation run one after another.
 std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = true, bool one_lane = false) {
-  const int prop = nvec > kMaxNV && h->prop_group_large[prec] > 0 ? h->prop_group_large[prec] : h->prop_group[prec];
-  const int tuned = h->force_group > 0 ? h->force_group : (propagate ? prop : h->apply_group[prec]);
+  const int tuned =
+      h->force_group > 0 ? h->force_group : (propagate ? tuned_prop_group(h, nvec, prec) : h->apply_group[prec]);
   if (tuned > 0) {
     std::vector<int> g;
     // a tuned size smaller where neither the block kernels nor the one-pass
@@ -1654,8 +1659,12 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     // automatic: not where the caller chose the apply kernels (hub_set_apply_path),
     // and only for enough vectors per state
     const bool kernels_auto = h->D.two_pass == -1 && h->D.block_path == -1;
-    const bool worth = static_cast<int64_t>(nvec) * kResidentAutoElems >= dim &&
-                       nvec >= hub::resident_min_vectors(pi, h->D.dim_up, h->D.dim_dn);
+    // (a plan of singles or pairs leaves the launch path without the groups that
+    // resident_min_vectors was measured against: 8 vectors of 84 x 126 states,
+    // complex64, three steps, 1,610 us as singles, 678 resident)
+    const int tuned = tuned_prop_group(h, nvec, pi);
+    const int least = tuned == 1 || tuned == 2 ? 1 : hub::resident_min_vectors(pi, h->D.dim_up, h->D.dim_dn);
+    const bool worth = static_cast<int64_t>(nvec) * kResidentAutoElems >= dim && nvec >= least;
     if (opts_ok && fits && (h->prop_path == 1 || (kernels_auto && worth)))
       return run_resident(h, prec, nvec, v_inout, n_steps, A_mid, A_sample, A_gauss, t_start, dt, o, obs, log, st);
   }

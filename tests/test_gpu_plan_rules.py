@@ -29,23 +29,35 @@ def test_two_pass_iterations(n, nu, nd, prec, kernels):
     assert _plan(ring(n), nu, nd, prec, 1) == [(1, kernels)]
 
 
-@pytest.mark.parametrize("n,nu,nd,nvec,resident", [
-    (12, 1, 6, 8, False), (12, 1, 6, 9, True), (12, 6, 1, 12, True), (14, 1, 4, 12, True),  # long tiles
-    (11, 2, 3, 8, False), (11, 2, 3, 12, True), (13, 1, 4, 5, True),  # at most 9,600 states
-    (10, 2, 5, 32, False), (14, 4, 1, 32, False), (14, 4, 1, 33, True), (10, 3, 3, 48, True)])
-def test_resident_stepper_of_large_complex64_tiles(n, nu, nd, nvec, resident):
+def _resident(n, nu, nd, nvec, group=0):
     from synth import PulseParams
     B = hub.Basis(ring(n), 8.0, nu, nd, device=0)
     try:
+        if group:
+            hub.hub_set_tuning(B.handle, C64, {"single_two_pass": 0, "block_two_pass": [0, 1, 1, 1],
+                                               "apply_group": 8, "prop_group": group})
         g = torch.Generator(device="cuda:0").manual_seed(2)
         x = torch.randn(nvec, B.dim, dtype=torch.complex64, device="cuda:0", generator=g)
         x /= torch.linalg.vector_norm(x, dim=1, keepdim=True)
         hub.hub_controller_read_stats(B.handle)
         hub.hub_propagate(B.handle, [PulseParams(0, 0.4, 8.0, 0.1, 0.1)] * nvec, 0.0, 0.01, 2,
                           hub.make_opts(tol=1e-6, m_max=30), x)
-        assert (hub.hub_controller_read_stats(B.handle)["lanczos_launches"] == 0) == resident
+        return hub.hub_controller_read_stats(B.handle)["lanczos_launches"] == 0
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("group,resident", [(1, True), (2, True), (4, False), (8, False)])
+def test_resident_stepper_beside_a_plan(group, resident):
+    assert _resident(9, 3, 4, 8, group) == resident
+
+
+@pytest.mark.parametrize("n,nu,nd,nvec,resident", [
+    (12, 1, 6, 8, False), (12, 1, 6, 9, True), (12, 6, 1, 12, True), (14, 1, 4, 12, True),  # long tiles
+    (11, 2, 3, 8, False), (11, 2, 3, 12, True), (13, 1, 4, 5, True),  # at most 9,600 states
+    (10, 2, 5, 32, False), (14, 4, 1, 32, False), (14, 4, 1, 33, True), (10, 3, 3, 48, True)])
+def test_resident_stepper_of_large_complex64_tiles(n, nu, nd, nvec, resident):
+    assert _resident(n, nu, nd, nvec) == resident
 
 
 @pytest.mark.parametrize("n,nu,nd,prec,nvec,lanes,one", [
