@@ -323,10 +323,12 @@ hub_status hub_greens_diag(hub_basis basis, int32_t n_targets, const hub_basis *
  * string whose tables plus one tile row (and one tile column) fit 148 KiB,
  * else hub_greens_diag returns HUB_E_INVALID.  path -1 (default): 1 where it
  * applies and the largest target sector has at most 8,192 states, 16,384 with
- * 48 members or more, 32,768 with 96, or 2^18 with as many members as compute
+ * 48 members or more, 32,768 with 96, or 2^17 with as many members as compute
  * units (one workgroup per member runs well below a compute unit's share of
- * the bandwidth), else 0.  Both give the same
- * overlaps up to rounding.  Errors: HUB_E_INVALID. */
+ * the bandwidth), else 0; with fewer members than compute units also 0 where a
+ * target's handle has a path set (hub_set_apply_path, hub_set_propagate_path)
+ * or apply timing on.  Both give the same overlaps up to rounding.  Errors:
+ * HUB_E_INVALID. */
 hub_status hub_set_greens_path(hub_basis basis, int32_t path);
 
 /* Broadened spectral functions, Eq. (A_noneq_broad), from the overlaps of

@@ -2007,13 +2007,15 @@ constexpr size_t kMembersLds = 148 << 10;  // tables + staging per member workgr
 // sites (4,900 states) complex64 4 members 4.6 / 3.1, 64 members 8.1 / 4.1; 9
 // sites (15,876) 16 members 5.1 / 5.5, 32 5.7 / 6.4, 48 8.5 / 7.0, complex128
 // 48 8.2 / 8.3; 10 sites (25,200) 64 9.0 / 8.8, complex128 9.2 / 10.4, 96 12.3
-// / 10.9; 20 steps of 10 sites (52,920) 64 16.3 / 26.6, 128 28.6 / 29.7, 256
-// 52.9 / 38.1.
+// / 10.9; 10 sites (52,920) 96 12.7 / 15.7, 128 15.8 / 16.6, 256 30.2 / 21.6, 320
+// 36.5 / 32.6; 12 sites (108,900) 256 33.1 / 31.0; beyond, a second round of
+// workgroups costs what the first gained: 11 sites (152,460) 256 48.3 / 48.8,
+// 384 70.9 / 85.7, 512 92.3 / 90.7, 12 sites (245,025) 256 52.5 / 234.
 int members_auto_least(int64_t dim, int n_cu) {
   if (dim <= 8192) return 1;
   if (dim <= 16384) return 48;
   if (dim <= 32768) return 96;
-  return dim <= 1 << 18 ? n_cu : 0;
+  return dim <= 1 << 17 ? n_cu : 0;
 }
 
 // Members of one target sector in hub_greens_diag.
@@ -2223,8 +2225,16 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
   if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || n_cu < 1)
     n_cu = 256;
   const int members_least = members_auto_least(members_dim, n_cu);
+  // with fewer members than compute units only where no target's kernels were
+  // chosen (hub_set_apply_path, hub_set_propagate_path) nor are to be timed
+  bool chosen = false;
+  for (int g : tb) {
+    const hub_basis T = targets[g];
+    chosen |= T->D.two_pass != -1 || T->D.block_path != -1 || T->prop_path != -1 || T->prof;
+  }
   const bool use_members =
-      h->greens_path == 1 || (h->greens_path == -1 && members_fit && members_least > 0 && n_members >= members_least);
+      h->greens_path == 1 || (h->greens_path == -1 && members_fit && members_least > 0 &&
+                              n_members >= (chosen ? std::max(members_least, n_cu) : members_least));
   // Device buffers: psi at every step (the trajectory), the members of every
   // target sector in the ABI layout (ordered by start step), their operator
   // maps packed per sector [member][map_len], overlap partials per sector

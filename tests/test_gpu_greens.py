@@ -307,3 +307,52 @@ def test_automatic_member_stepper(lat, nu, nd, members, persistent):
         B.close()
         for t in T:
             t.close()
+
+
+@pytest.mark.parametrize("setup,persistent,timed", [
+    (None, True, False), (lambda t: hub.hub_set_apply_path(t, 0), False, False),
+    (lambda t: hub.hub_set_apply_path(t, 1), False, False), (lambda t: hub.hub_set_propagate_path(t, 0), False, False),
+    (lambda t: hub.hub_profile_enable(t, 1), False, True)])
+def test_targets_with_chosen_kernels_keep_them(setup, persistent, timed):
+    """A path set on a target's handle, or apply timing, keeps a call with few
+    members off the persistent stepper, whose overlaps differ from the
+    launches' in the last bits; timing then has samples to show."""
+    B = hub.Basis(ring(8), 8.0, 4, 4)
+    T = [hub.Basis(ring(8), 8.0, 4 + a, 4 + b) for a, b in ((1, 0), (-1, 0), (0, 1), (0, -1))]
+    psi = _dev(random_state(B.dim, seed=8)[0], torch.complex128)
+    m = [(k, k % 2, k // 2 % 2, k % 3) for k in range(8)]
+
+    def run():
+        return hub.hub_greens_diag(B.handle, [t.handle for t in T], PulseParams(0, 0.4, 8.0, 0.02, 0.05), 0.0, 0.01, 3,
+                                   hub.make_opts(tol=1e-10, m_max=30), m, psi.clone())
+
+    try:
+        if setup:
+            setup(T[2].handle)
+        out = run()
+        launches, _, _ = hub.hub_profile_read(T[2].handle)
+        hub.hub_set_greens_path(B.handle, 0)
+        per_sector = run()
+        assert np.array_equal(out, per_sector) != persistent
+        assert (launches > 0) == timed
+    finally:
+        B.close()
+        for t in T:
+            t.close()
+
+
+def test_a_refused_target_path_stays_refused():
+    """hub_set_propagate_path 1 on a target asks for the resident stepper, which
+    takes no step hooks: refused with few members, as it was."""
+    B = hub.Basis(ring(8), 8.0, 4, 4)
+    T = hub.Basis(ring(8), 8.0, 5, 4)
+    psi = _dev(random_state(B.dim, seed=8)[0], torch.complex128)
+    try:
+        hub.hub_set_propagate_path(T.handle, 1)
+        with pytest.raises(hub.HubError) as e:
+            hub.hub_greens_diag(B.handle, [T.handle], PulseParams(0, 0.4, 8.0, 0.02, 0.05), 0.0, 0.01, 3,
+                                hub.make_opts(tol=1e-10, m_max=30), [(0, 0, 1, 0)], psi)
+        assert e.value.status == hub.HUB_E_INVALID
+    finally:
+        B.close()
+        T.close()
