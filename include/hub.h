@@ -482,14 +482,17 @@ hub_status hub_set_apply_path(hub_basis basis, int32_t path);
  * (c) the vectors per group when a call carries many vectors, separately for
  * hub_apply_H and hub_propagate.  Without tuning these follow built-in rules
  * (LDS fit and vector size); hub_tune measures them on this basis's sector:
- * plain H*v of 8 vectors in groups of 1, 2, 4, 8 on each feasible path
- * (`reps` timed calls each, HIP events), then two midpoint steps (after one
- * untimed) per group size on the chosen paths (dt |H|_inf = 1/2, tol 1e-10,
- * host clock), of 8 vectors and of 32, and installs the fastest choices in
- * the handle.  Groups run on up to 4 concurrent lanes, so the best group
+ * plain H*v of 8 vectors in groups of 1, 2, 4, 8 on each feasible path and
+ * as a batch in the caller's layout (`reps` timed calls each, HIP events),
+ * then two midpoint steps (after one untimed, dt |H|_inf = 1/2, tol 1e-10,
+ * host clock) of a single vector, and where products go in batches of a
+ * block, on either path, and per group size on the chosen paths, of 8 vectors
+ * and of 32, and installs the fastest choices in the handle.  Groups run on up to 4 concurrent lanes, so the best group
  * size depends on how many groups a call has: 8 vectors in groups of 8 run
  * on one lane, 32 fill every lane at every group size.  A hub_propagate call
- * of at most 8 vectors takes prop_group, a larger one prop_group_large.
+ * of at most 8 vectors takes prop_group (two or three vectors of at least 1
+ * MiB that are fewer than a group: the built-in rule), a larger one
+ * prop_group_large.
  * The 32-vector measurement skips a group size whose vectors and Krylov
  * workspace would not fit the device's free memory (step_us_large 0 there;
  * prop_group_large = prop_group when none fits).  Results never
@@ -501,7 +504,11 @@ hub_status hub_set_apply_path(hub_basis basis, int32_t path);
 typedef struct {
   int32_t single_two_pass;    /* single vectors: 1 = two-pass kernels, 0 = one pass       */
   int32_t block_two_pass[4];  /* [1], [2], [3]: groups of 2, 4, 8 on the two-pass block
-                                 kernels (1) or the one-pass kernel (0); [0] unused         */
+                                 kernels (1) or the one-pass kernel (0); [0], a sum: 1 =
+                                 hub_apply_H in batches of the caller's layout where they are
+                                 available (else groups of apply_group), 2 = Lanczos iterations
+                                 of single vectors on the kernels that single_two_pass does not
+                                 name (tables from before: 0, neither)                      */
   int32_t apply_group;        /* vectors per group of hub_apply_H (1, 2, 4, 8)             */
   int32_t prop_group;         /* vectors per group of hub_propagate (1, 2, 4, 8)           */
   double apply_us[4][2];      /* measured H*v time per vector (us), groups of 1, 2, 4, 8 x

@@ -140,6 +140,7 @@ struct hub_basis_s {
   // and hub_propagate with several vectors; force_group (> 0) overrides both
   // while hub_tune measures
   int apply_group[2] = {-1, -1};
+  bool apply_batch[2] = {false, false};  // .. hub_apply_H in batches of the caller's layout where there are
   int prop_group[2] = {-1, -1};
   int prop_group_large[2] = {-1, -1};  // hub_propagate with more than kMaxNV vectors
   int force_group = 0;
@@ -438,9 +439,13 @@ hub_status prof_harvest(hub_basis h, size_t from, size_t* end) {
   return HUB_OK;
 }
 
-// An installed plan's vectors per group of a propagation (none: -1).
+// An installed plan's vectors per group of a propagation (none: -1).  Two or
+// three vectors of at least 1 MiB that do not fill its groups take the built-in
+// rule, which was measured for them (12 sites complex64, plan of fours, singles
+// on lanes / pairs: 2 vectors, four steps, 1,288 / 1,391 us).
 int tuned_prop_group(hub_basis h, int nvec, int prec) {
-  return nvec > kMaxNV && h->prop_group_large[prec] > 0 ? h->prop_group_large[prec] : h->prop_group[prec];
+  const int g = nvec > kMaxNV && h->prop_group_large[prec] > 0 ? h->prop_group_large[prec] : h->prop_group[prec];
+  return g > nvec && nvec < 4 && h->D.dim * (prec == 0 ? 16 : 8) >= 1024 * 1024 ? -1 : g;
 }
 
 // A propagation's groups share the event pool of the apply timing, or the
@@ -541,16 +546,16 @@ bool batch_misfit(hub_basis h, int nvec, int prec) {
   return nvec == 2 && h->D.dim_up < 64 && h->D.dim_dn >= (h->D.dim_up < 8 ? 2048 : 4096);
 }
 
-// hub_apply_H's groups of the automatic rule: batches in the caller's layout
-// (columns: batch_columns) where the caller and no tuned plan chose kernels or
-// group sizes, else the interleaved groups (columns -1) of groups_for.
+// hub_apply_H's groups: batches in the caller's layout (columns:
+// batch_columns) where neither the caller nor a tuned plan chose other kernels
+// or group sizes, else the interleaved groups (columns -1) of groups_for.
 struct ApplyGroup {
   int nv, columns;
 };
 std::vector<ApplyGroup> apply_groups(hub_basis h, int nvec, int prec) {
   std::vector<ApplyGroup> g;
-  if (nvec > 1 && h->force_group == 0 && h->apply_group[prec] <= 0 && h->D.two_pass == -1 && h->D.block_path == -1 &&
-      !batch_misfit(h, nvec, prec)) {
+  const bool automatic = h->force_group == 0 && (h->apply_group[prec] <= 0 || h->apply_batch[prec]);
+  if (nvec > 1 && automatic && h->D.two_pass == -1 && h->D.block_path == -1 && !batch_misfit(h, nvec, prec)) {
     // where a batch could stage only two columns, or none, vectors that gather
     // theirs go one by one: a vector of 14 sites takes 131 us instead of 213
     // (complex64) or 250 instead of 286 (complex128), of 15 sites 590 instead
@@ -2732,16 +2737,19 @@ hub_status hub_spectral(int32_t device, int32_t n_members, int32_t n_s, const do
 // Kernel plan tuning.
 namespace {
 
+// hub_tuning.block_two_pass[0]
+constexpr int kPlanBatches = 1, kPlanOtherLanczos = 2;
+
 int gidx(int g) { return g == 1 ? 0 : (g == 2 ? 1 : (g == 4 ? 2 : 3)); }
 
 // Can group size g run on path (0 one pass, 1 two pass) for precision pi?
-bool path_feasible(const DevBasis& D, int pi, int g, int path) {
+bool path_feasible(const DevBasis& D, int pi, int g, int path, int mode = hub::kPlain) {
   DevBasis T = D;
   T.two_pass = path;
   T.block_path = path ? -1 : 0;
-  T.tuned_single[pi] = -1;
+  T.tuned_single[pi] = T.tuned_lanczos[pi] = -1;
   for (int k = 0; k < 4; ++k) T.tuned_block[pi][k] = -1;
-  if (g == 1) return path ? hub::apply_two_pass(T, pi, 1, hub::kPlain, false) : true;
+  if (g == 1) return path ? hub::apply_two_pass(T, pi, 1, mode, false) : true;
   if (path) return hub::block_two_pass(T, pi, g);
   return hub::apply_lds_bytes(T, pi, g, 1) <= 150 * 1024;
 }
@@ -2763,6 +2771,7 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
   hipEvent_t e0 = nullptr, e1 = nullptr;
   const DevBasis saved = h->D;
   const int saved_ag = h->apply_group[pi], saved_pg = h->prop_group[pi], saved_pgl = h->prop_group_large[pi];
+  const bool saved_ab = h->apply_batch[pi];
   // the plans are the launch path's: its propagations are timed, not the resident stepper's
   const int saved_path = h->prop_path;
   h->prop_path = 0;
@@ -2772,6 +2781,7 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
     h->prop_path = saved_path;
     if (r != HUB_OK) {
       h->apply_group[pi] = saved_ag;
+      h->apply_batch[pi] = saved_ab;
       h->prop_group[pi] = saved_pg;
       h->prop_group_large[pi] = saved_pgl;
     }
@@ -2795,7 +2805,21 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
   if (hub::launch_fill_probe(pi, dim * kN, x, st) != hipSuccess) return done(fail(HUB_E_DEVICE, "fill kernel"));
   hub_tuning T{};
   const double A[kN] = {0.5, 0.5, 0.5, 0.5, 0.5, 0.5, 0.5, 0.5};
-  // 1. plain H*v of kN vectors in groups of g on either path
+  auto time_applies = [&](double* us_per_vector) -> hub_status {
+    for (int r = 0; r < 2; ++r)
+      if ((s = hub_apply_H(h, A, prec, kN, x, y, stream)) != HUB_OK) return s;
+    float ms = 0.0f;
+    HUB_HIP(hipEventRecord(e0, st));
+    for (int r = 0; r < reps; ++r)
+      if ((s = hub_apply_H(h, A, prec, kN, x, y, stream)) != HUB_OK) return s;
+    HUB_HIP(hipEventRecord(e1, st));
+    HUB_HIP(hipEventSynchronize(e1));
+    HUB_HIP(hipEventElapsedTime(&ms, e0, e1));
+    *us_per_vector = 1e3 * ms / (static_cast<double>(reps) * kN);
+    return HUB_OK;
+  };
+  // 1. plain H*v of kN vectors in groups of g on either path, and as a batch
+  // in the caller's layout
   for (int g : {1, 2, 4, 8})
     for (int path = 0; path < 2; ++path) {
       if (!path_feasible(saved, pi, g, path)) continue;
@@ -2803,17 +2827,16 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
       h->D.two_pass = path;
       h->D.block_path = path ? -1 : 0;
       h->force_group = g;
-      for (int r = 0; r < 2; ++r)
-        if ((s = hub_apply_H(h, A, prec, kN, x, y, stream)) != HUB_OK) return done(s);
-      TUNE_HIP(hipEventRecord(e0, st));
-      for (int r = 0; r < reps; ++r)
-        if ((s = hub_apply_H(h, A, prec, kN, x, y, stream)) != HUB_OK) return done(s);
-      TUNE_HIP(hipEventRecord(e1, st));
-      TUNE_HIP(hipEventSynchronize(e1));
-      float ms = 0.0f;
-      TUNE_HIP(hipEventElapsedTime(&ms, e0, e1));
-      T.apply_us[gidx(g)][path] = 1e3 * ms / (static_cast<double>(reps) * kN);
+      if ((s = time_applies(&T.apply_us[gidx(g)][path])) != HUB_OK) return done(s);
     }
+  h->D = saved;
+  h->D.two_pass = h->D.block_path = -1;
+  h->D.tuned_single[pi] = h->D.tuned_lanczos[pi] = -1;
+  h->force_group = 0;
+  h->apply_group[pi] = -1;
+  double batch_us = 0.0;
+  const std::vector<ApplyGroup> batch = apply_groups(h, kN, pi);
+  if (batch.size() == 1 && batch[0].columns >= 0 && (s = time_applies(&batch_us)) != HUB_OK) return done(s);
   auto best_path = [&](int g) {
     const double* u = T.apply_us[gidx(g)];
     if (u[0] > 0.0 && u[1] > 0.0) return u[1] < u[0] ? 1 : 0;
@@ -2823,9 +2846,9 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
   for (int g : {2, 4, 8}) T.block_two_pass[gidx(g)] = best_path(g);
   // install the path choices
   h->D = saved;
-  h->D.tuned_single[pi] = T.single_two_pass;
+  h->D.tuned_single[pi] = h->D.tuned_lanczos[pi] = T.single_two_pass;
   for (int g : {2, 4, 8}) h->D.tuned_block[pi][gidx(g)] = T.block_two_pass[gidx(g)];
-  const DevBasis chosen = h->D;
+  DevBasis chosen = h->D;
   double best = 0.0;
   for (int g : {1, 2, 4, 8}) {
     const int path = g == 1 ? T.single_two_pass : T.block_two_pass[gidx(g)];
@@ -2834,6 +2857,11 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
       best = u;
       T.apply_group = g;
     }
+  }
+  const bool batches = batch_us > 0.0 && batch_us < best;
+  if (batches) {
+    T.apply_group = kN;
+    T.block_two_pass[0] |= kPlanBatches;
   }
   // 2. midpoint steps of nv vectors in groups of g (the chosen paths), dt
   // such that dt |H|_inf = 1/2, tol 1e-10: time per vector-step, for nv =
@@ -2863,10 +2891,40 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
   auto group_ok = [&](int g) {
     return g == 1 || hub::block_two_pass(chosen, pi, g) || hub::apply_lds_bytes(chosen, pi, g, 1) <= 150 * 1024;
   };
+  // Lanczos iterations of a single vector, whose two-pass row pass takes the
+  // update in, on either kernels; of blocks too, where products need none
+  if (path_feasible(saved, pi, 1, 1, hub::kLanczos)) {
+    double us[2] = {INFINITY, INFINITY};  // best of five in turn: a step is a few launches
+    for (int k = 0; k < 10; ++k) {
+      double t = 0.0;
+      chosen.tuned_lanczos[pi] = k % 2;
+      if ((s = time_steps(1, x, 1, &t)) != HUB_OK) return done(s);
+      us[k % 2] = std::min(us[k % 2], t);
+    }
+    const int other = 1 - T.single_two_pass;
+    const bool faster = us[other] < 0.95 * us[T.single_two_pass];
+    chosen.tuned_lanczos[pi] = faster ? other : T.single_two_pass;
+    if (faster) T.block_two_pass[0] |= kPlanOtherLanczos;
+  }
+  for (int g : {2, 4, 8}) {
+    if (!batches || !path_feasible(saved, pi, g, 0) || !path_feasible(saved, pi, g, 1)) continue;
+    double us[2] = {INFINITY, INFINITY};
+    for (int k = 0; k < 6; ++k) {
+      double t = 0.0;
+      chosen.tuned_block[pi][gidx(g)] = k % 2;
+      if ((s = time_steps(g, x, g, &t)) != HUB_OK) return done(s);
+      us[k % 2] = std::min(us[k % 2], t);
+    }
+    T.block_two_pass[gidx(g)] = chosen.tuned_block[pi][gidx(g)] = us[1] < us[0] ? 1 : 0;
+  }
   best = 0.0;
   for (int g : {1, 2, 4, 8}) {
     if (!group_ok(g)) continue;
-    if ((s = time_steps(kN, x, g, &T.step_us[gidx(g)])) != HUB_OK) return done(s);
+    for (int k = 0; k < 3; ++k) {  // best of three: sizes can be a few per cent apart
+      double t = 0.0, &us = T.step_us[gidx(g)];
+      if ((s = time_steps(kN, x, g, &t)) != HUB_OK) return done(s);
+      us = k == 0 ? t : std::min(us, t);
+    }
     if (best == 0.0 || T.step_us[gidx(g)] < best) {
       best = T.step_us[gidx(g)];
       T.prop_group = g;
@@ -2901,6 +2959,7 @@ hub_status hub_tune(hub_basis h, hub_prec prec, int32_t reps, hub_tuning* out, v
   h->force_group = 0;
   h->prop_path = saved_path;
   h->apply_group[pi] = T.apply_group;
+  h->apply_batch[pi] = batches;
   h->prop_group[pi] = T.prop_group;
   h->prop_group_large[pi] = T.prop_group_large;
   *out = T;
@@ -2917,9 +2976,10 @@ hub_status hub_set_tuning(hub_basis h, hub_prec prec, const hub_tuning* t) {
   if (prec != HUB_C128 && prec != HUB_C64) return fail(HUB_E_INVALID, "unknown precision");
   const int pi = prec == HUB_C128 ? 0 : 1;
   if (!t) {  // back to the built-in rules
-    h->D.tuned_single[pi] = -1;
+    h->D.tuned_single[pi] = h->D.tuned_lanczos[pi] = -1;
     for (int k = 0; k < 4; ++k) h->D.tuned_block[pi][k] = -1;
     h->apply_group[pi] = h->prop_group[pi] = h->prop_group_large[pi] = -1;
+    h->apply_batch[pi] = false;
     return HUB_OK;
   }
   auto pow2 = [](int g) { return g == 1 || g == 2 || g == 4 || g == 8; };
@@ -2928,7 +2988,10 @@ hub_status hub_set_tuning(hub_basis h, hub_prec prec, const hub_tuning* t) {
     return fail(HUB_E_INVALID, "tuning: groups must be 1, 2, 4 or 8 and paths 0 or 1");
   for (int k = 1; k < 4; ++k)
     if (t->block_two_pass[k] != 0 && t->block_two_pass[k] != 1) return fail(HUB_E_INVALID, "tuning: block path");
+  const bool other = (t->block_two_pass[0] & kPlanOtherLanczos) != 0;
   h->D.tuned_single[pi] = t->single_two_pass;
+  h->D.tuned_lanczos[pi] = other ? 1 - t->single_two_pass : t->single_two_pass;
+  h->apply_batch[pi] = (t->block_two_pass[0] & kPlanBatches) != 0;
   for (int k = 1; k < 4; ++k) h->D.tuned_block[pi][k] = t->block_two_pass[k];
   h->apply_group[pi] = t->apply_group;
   h->prop_group[pi] = t->prop_group;

@@ -71,9 +71,10 @@ struct DevBasis {
   int block_path = -1;           // blocks of vectors: -1 two-pass block kernels where they fit, 0 one pass
   // tuned choices per precision [c128, c64] (-1 = the built-in rule), used
   // while two_pass / block_path are automatic: single vectors two-pass (1) or
-  // one pass (0); blocks of 2, 4, 8 ([1], [2], [3]) on the two-pass block
-  // kernels (1) or the one-pass kernel (0)
+  // one pass (0), in plain products and in Lanczos iterations; blocks of 2, 4,
+  // 8 ([1], [2], [3]) on the two-pass block kernels (1) or the one-pass kernel (0)
   int tuned_single[2] = {-1, -1};
+  int tuned_lanczos[2] = {-1, -1};
   int tuned_block[2][4] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
   int up_max_hops = 0, dn_max_hops = 0;
 };

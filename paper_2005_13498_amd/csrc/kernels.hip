@@ -645,7 +645,8 @@ bool apply_two_pass(const DevBasis& db, int prec, int nv, int mode, bool obs) {
   // pass gathers (k_rowgather); their other kernels do it all in one pass
   if (!gather && (apply_global_rows(db, prec, 1) || colpass_lds_bytes(db, prec) > 150 * 1024)) return false;
   if (db.two_pass == 1) return true;
-  if (db.tuned_single[prec] >= 0) return db.tuned_single[prec] == 1;
+  const int tuned = mode == kPlain ? db.tuned_single[prec] : db.tuned_lanczos[prec];
+  if (tuned >= 0) return tuned == 1;
   // automatic: when a vector is larger than one XCD's L2 the up-hop row
   // gathers of the one-pass kernel stream from the Infinity Cache.  With 2
   // staged columns only the Lanczos iterations gain (fused updates), not a

@@ -127,3 +127,49 @@ def test_tuned_group_shrinks_where_no_kernel_fits():
     finally:
         B.close()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("prec", [hub.HUB_C128, hub.HUB_C64])
+def test_tuned_products_are_no_slower_than_the_built_in_rule(prec):
+    """12 sites, 8 vectors: batches in the caller's layout take 83 and 139 us,
+    interleaved groups 117 and 182, so the tuner finds them; its table
+    installs them again, and one without the mark keeps interleaved groups."""
+    w = workloads()["cluster3x4"]
+    B = hub.Basis(w.lattice, w.U, 6, 6)
+    try:
+        built_in = hub.hub_get_plan(B.handle, prec, 8, False)
+        t = hub.hub_tune(B.handle, prec, 10)
+        assert t["block_two_pass"][0] & 1 and t["apply_group"] == 8
+        assert hub.hub_get_plan(B.handle, prec, 8, False) == built_in == [(8, 2)]
+        x = torch.randn(8, B.dim, dtype=torch.complex128 if prec == hub.HUB_C128 else torch.complex64, device=DEV)
+        y, z, w = torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+        A = [0.1 * k for k in range(8)]
+        hub.hub_apply_H(B.handle, A, x, y)
+        hub.hub_set_tuning(B.handle, prec, None)
+        hub.hub_apply_H(B.handle, A, x, z)
+        hub.hub_set_tuning(B.handle, prec, t)
+        hub.hub_apply_H(B.handle, A, x, w)
+        assert torch.equal(y, z) and torch.equal(w, z)
+        old = dict(t, block_two_pass=[0] + t["block_two_pass"][1:], apply_group=4)
+        hub.hub_set_tuning(B.handle, prec, old)
+        assert hub.hub_get_plan(B.handle, prec, 8, False) == [(4, 2), (4, 2)]
+    finally:
+        B.close()
+
+
+def test_plans_name_the_iterations_kernels_apart():
+    """single_two_pass names the kernels of plain products, and of the Lanczos
+    iterations unless the plan says that those take the other ones."""
+    B = hub.Basis(ring(11), 8.0, 5, 5)
+    try:
+        for single in (0, 1):
+            for flag, lanczos in ((0, single), (2, 1 - single)):
+                hub.hub_set_tuning(B.handle, hub.HUB_C128, {"single_two_pass": single, "block_two_pass": [flag, 1, 1, 1],
+                                                            "apply_group": 1, "prop_group": 1})
+                assert hub.hub_get_plan(B.handle, hub.HUB_C128, 1, False) == [(1, single)]
+                assert hub.hub_get_plan(B.handle, hub.HUB_C128, 1, True) == [(1, lanczos)]
+        t = hub.hub_tune(B.handle, hub.HUB_C128, 3)  # two-pass iterations are the faster ones here
+        plan = hub.hub_get_plan(B.handle, hub.HUB_C128, 1, True)[0][1]
+        assert plan == (t["single_two_pass"] ^ (t["block_two_pass"][0] >> 1 & 1))
+    finally:
+        B.close()
