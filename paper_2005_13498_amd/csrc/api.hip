@@ -2023,6 +2023,10 @@ int members_auto_least(int64_t dim, int n_cu) {
   return dim <= 1 << 17 ? n_cu : 0;
 }
 
+// Overlap partials a target sector keeps at once (64 members of 14 sites: 1 MB
+// a sample).
+constexpr size_t kOverlapBytes = size_t(256) << 20;
+
 // Members of one target sector in hub_greens_diag.
 struct GreensSector {
   hub_basis T = nullptr;
@@ -2032,8 +2036,9 @@ struct GreensSector {
   int8_t* sgns = nullptr;
   int map_len = 0, ogrid = 0;
   bool down = false;
-  double* part = nullptr;
-  double* tot = nullptr;
+  int window = 0;          // samples whose overlap partials are kept at once
+  double* part = nullptr;  // [window][members][ogrid][2]
+  double* tot = nullptr;   // [n_rel + 1][members][2]
   hipStream_t stream = nullptr;
   hub_status s = HUB_OK;
   std::string err;
@@ -2242,8 +2247,8 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
                               n_members >= (chosen ? std::max(members_least, n_cu) : members_least));
   // Device buffers: psi at every step (the trajectory), the members of every
   // target sector in the ABI layout (ordered by start step), their operator
-  // maps packed per sector [member][map_len], overlap partials per sector
-  // [n_rel + 1][members][grid][2] and their totals [n_rel + 1][members][2].
+  // maps packed per sector [member][map_len], and on the per-sector path the
+  // overlap partials of a window of samples and the totals of all.
   using Sector = GreensSector;
   std::vector<Sector> secs;
   void* traj = nullptr;
@@ -2288,13 +2293,15 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
       maps.insert(maps.end(), M.map.begin(), M.map.end());
       sg.insert(sg.end(), M.sgn.begin(), M.sgn.end());
     }
-    if ((!use_members && hipMalloc(&S.buf, static_cast<size_t>(nm) * dt_ * es) != hipSuccess) ||
-        hipMalloc(reinterpret_cast<void**>(&S.maps), maps.size() * sizeof(int32_t)) != hipSuccess ||
+    const size_t sample = static_cast<size_t>(nm) * S.ogrid * 2 * sizeof(double);
+    S.window = static_cast<int>(std::min<size_t>(n_rel + 1, std::max<size_t>(1, kOverlapBytes / sample)));
+    if (hipMalloc(reinterpret_cast<void**>(&S.maps), maps.size() * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&S.sgns), sg.size()) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&S.part),
-                  static_cast<size_t>(n_rel + 1) * nm * S.ogrid * 2 * sizeof(double)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&S.tot), static_cast<size_t>(n_rel + 1) * nm * 2 * sizeof(double)) !=
-            hipSuccess)
+        (!use_members &&
+         (hipMalloc(&S.buf, static_cast<size_t>(nm) * dt_ * es) != hipSuccess ||
+          hipMalloc(reinterpret_cast<void**>(&S.part), S.window * sample) != hipSuccess ||
+          hipMalloc(reinterpret_cast<void**>(&S.tot), static_cast<size_t>(n_rel + 1) * nm * 2 * sizeof(double)) !=
+              hipSuccess)))
       return cleanup(fail(HUB_E_NOMEM, "member buffers"));
     HUB_HIP(hipMemcpy(S.maps, maps.data(), maps.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     HUB_HIP(hipMemcpy(S.sgns, sg.data(), sg.size(), hipMemcpyHostToDevice));
@@ -2320,7 +2327,7 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
     return cleanup(s);
   }
   // 2. every member from c_k psi(t'_k); overlaps after s = 0..n_rel steps,
-  // gathered from the trajectory, partials at [s][member][grid][2]
+  // gathered from the trajectory
   auto overlap_launch = [&](Sector& S, int k0, int nv, int n_done, const void* phi, bool interleaved,
                             const StepCtl* ctl, hipStream_t s_) -> hipError_t {
     const int nm = static_cast<int>(S.mem.size());
@@ -2337,8 +2344,18 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
     a.traj = traj;
     a.phi = phi;
     a.ctl = ctl;
-    a.partials = S.part + (static_cast<size_t>(n_done) * nm + k0) * S.ogrid * 2;
-    return hub::launch_overlaps(pi, nv, a, s_);
+    a.partials = S.part + (static_cast<size_t>(n_done % S.window) * nm + k0) * S.ogrid * 2;
+    const hipError_t e = hub::launch_overlaps(pi, nv, a, s_);
+    if (e != hipSuccess || S.window > n_rel || (n_done % S.window < S.window - 1 && n_done < n_rel)) return e;
+    // the window's last sample: its totals, before the next one takes its
+    // place (after an abandoned step this runs again with the step's re-run)
+    for (int n = n_done - n_done % S.window; n <= n_done; ++n) {
+      const hipError_t r = hub::launch_reduce_sets(S.part + (static_cast<size_t>(n % S.window) * nm + k0) * S.ogrid * 2,
+                                                   static_cast<int64_t>(S.ogrid) * 2, nv, S.ogrid, 2,
+                                                   S.tot + (static_cast<size_t>(n) * nm + k0) * 2, 2, s_);
+      if (r != hipSuccess) return r;
+    }
+    return hipSuccess;
   };
   for (Sector& S : secs) {
     const int nm = static_cast<int>(S.mem.size());
@@ -2396,8 +2413,9 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
   std::vector<double> host;
   for (Sector& S : secs) {
     const int nm = static_cast<int>(S.mem.size());
-    HUB_HIP(hub::launch_reduce_sets(S.part, static_cast<int64_t>(S.ogrid) * 2, (n_rel + 1) * nm, S.ogrid, 2, S.tot, 2,
-                                    S.stream));
+    if (S.window > n_rel)
+      HUB_HIP(hub::launch_reduce_sets(S.part, static_cast<int64_t>(S.ogrid) * 2, (n_rel + 1) * nm, S.ogrid, 2, S.tot, 2,
+                                      S.stream));
     host.assign(static_cast<size_t>(n_rel + 1) * nm * 2, 0.0);
     HUB_HIP(hipMemcpyAsync(host.data(), S.tot, host.size() * sizeof(double), hipMemcpyDeviceToHost, S.stream));
     HUB_HIP(hipStreamSynchronize(S.stream));

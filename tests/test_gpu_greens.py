@@ -356,3 +356,71 @@ def test_a_refused_target_path_stays_refused():
     finally:
         B.close()
         T.close()
+
+
+def _peak_bytes(call):
+    """Device memory that call() takes at most beyond what is in use before
+    (it allocates in the library, with the interpreter lock released)."""
+    import threading
+    free, stop, low = torch.cuda.mem_get_info()[0], threading.Event(), []
+
+    def watch():
+        while not stop.is_set():
+            low.append(torch.cuda.mem_get_info()[0])
+
+    t = threading.Thread(target=watch)
+    t.start()
+    try:
+        out = call()
+    finally:
+        stop.set()
+        t.join()
+    return free - min(low), out
+
+
+def test_overlap_memory_does_not_grow_with_the_samples():
+    """11 sites, 64 members: a sample's partial sums are 0.85 MB, and at most
+    256 MiB of them are kept, so 400 more samples take 400 more states of psi
+    and no more.  The samples that both runs have are the same bits; all of
+    them agree with the persistent stepper's to a few hundred steps' rounding."""
+    B, T = hub.Basis(ring(11), 8.0, 5, 5), hub.Basis(ring(11), 8.0, 6, 5)
+    psi = _dev(random_state(B.dim, seed=8)[0], torch.complex64)
+    m = [(k % 11, 0, 1, 0) for k in range(64)]
+
+    def run(n_rel, path):
+        hub.hub_set_greens_path(B.handle, path)
+        return hub.hub_greens_diag(B.handle, [T.handle], PulseParams(0, 0.4, 8.0, 0.2, 0.3), 0.0, 0.002, n_rel,
+                                   hub.make_opts(tol=1e-7, m_max=20), m, psi.clone())
+
+    try:
+        run(2, 0)  # the handles' workspaces
+        short, a = _peak_bytes(lambda: run(300, 0))
+        long, b = _peak_bytes(lambda: run(700, 0))
+        assert long - short <= 400 * B.dim * 8 + (64 << 20)
+        assert np.array_equal(a, b[:, :301])
+        assert np.max(np.abs(b - run(700, 1))) <= 700 * 20 * 2.0 ** -23
+    finally:
+        B.close()
+        T.close()
+
+
+def test_member_stepper_keeps_no_overlap_partials():
+    """8 sites, 512 members, 1,000 samples: the persistent stepper adds its
+    overlaps itself and keeps its Krylov slots, psi and its results alone."""
+    B, T = hub.Basis(ring(8), 8.0, 4, 4), hub.Basis(ring(8), 8.0, 5, 4)
+    psi = _dev(random_state(B.dim, seed=8)[0], torch.complex64)
+    m = [(k % 8, 0, 1, 0) for k in range(512)]
+    try:
+        hub.hub_set_greens_path(B.handle, 1)
+
+        def run(n_rel):
+            return hub.hub_greens_diag(B.handle, [T.handle], PulseParams(0, 0.4, 8.0, 0.2, 0.3), 0.0, 0.002, n_rel,
+                                       hub.make_opts(tol=1e-5, m_max=8), m, psi.clone())
+
+        run(2)
+        peak, _ = _peak_bytes(lambda: run(1000))
+        kept = 512 * 10 * T.dim * 8 + 1001 * B.dim * 8 + 512 * 1001 * (16 + 8)
+        assert peak <= kept + (48 << 20)
+    finally:
+        B.close()
+        T.close()
