@@ -252,10 +252,11 @@ hub_status hub_propagate(hub_basis basis, const hub_pulse *pulses, double t_star
 hub_status hub_set_propagate_path(hub_basis basis, int32_t path);
 
 /* Ground state of H(A) (Sec. 3.4 "Ground state"): restarted Lanczos
- * with its vectors orthogonal to rounding, in FP64, until the residual
- * |H x - E0 x| falls below opts->tol * |H|_inf (opts NULL: tol 1e-12, m_max
- * 60).  It restarts after m_max vectors, or later where more of them fit a
- * workspace of 256 MiB (at most 4 m_max).  v_out:
+ * in FP64, until the residual |H x - E0 x|, with what its vectors have lost of
+ * their orthogonality (at most a quarter of the smaller of opts->tol and 1e-9,
+ * times |H|_inf) counted in, falls below opts->tol * |H|_inf (opts NULL: tol
+ * 1e-12, m_max 60).  It restarts after m_max vectors, or later where more of
+ * them fit 256 MiB (at most 4 m_max), which the handle then keeps.  v_out:
  * device, dim complex doubles, normalised, phase fixed so that the component
  * of largest modulus is real positive (lowest index among ties within 1e-12).
  * E0, gap (E1 - E0 of the Ritz values): host, gap may be NULL.  Returns

@@ -2429,12 +2429,13 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
 }
 
 // ---------------------------------------------------------------------------
-// Ground state: restarted Lanczos with orthogonal vectors, complex double; the
-// lowest Ritz pair of the tridiagonal on the host.
+// Ground state: restarted Lanczos, complex double, its vectors orthogonal
+// within a checked bound (gs_lanczos); the lowest Ritz pair of the tridiagonal on the host.
 namespace {
 
 // Iterations enqueued between two looks at the residual (the host waits once
-// per batch; iterations past the one that converges are dropped).  10 sites:
+// per batch; those past the one that converges go into T and the Ritz vector
+// as well).  10 sites:
 // 6.8 ms at 8 iterations, 5.5 at 16; what a batch loses of the orthogonality
 // doubles with its length at first (1e-13 of |H| = 60 at 8, 2e-13 at 16).
 constexpr int kGsBatch = 16;

@@ -1,5 +1,4 @@
-// Ground-state Lanczos kernels: complex double, one vector, orthogonal to
-// rounding.  An iteration is the H v kernels and two launches, with no host
+// Ground-state Lanczos kernels: complex double, one vector.  An iteration is the H v kernels and two launches, with no host
 // wait in between: inner products and subtraction of the two vectors that H v
 // overlaps with (and of the deflated one).  The last two iterations of a batch
 // have the same two launches once more against every vector, which takes out
@@ -209,8 +208,9 @@ __global__ __launch_bounds__(kBlock) void k_gs_scale(int64_t dim, const double2*
   }
 }
 
-// Counter-based: element i mixes (seed, i) to 64 random bits twice and takes
-// the pair of normal numbers of Box and Muller.
+// Counter-based: element i mixes (seed, i) to 64 random bits twice (the
+// finaliser of Steele, Lea and Flood's SplitMix64) and takes the pair of normal
+// numbers of Box and Muller.
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ULL;
   z = (z ^ (z >> 27)) * 0x94d049bb133111ebULL;

@@ -41,3 +41,24 @@ def test_ground_state_residual(lat, nu, nd, tol, m_max):
     ham = HubbardOracle(lat, U, nu, nd)
     E0 = ground_state(ham, 0.3)[0] if ham.dim > 2 else float(np.real(y[0] / x[0]))
     assert abs(e0 - E0) <= bound + 1e-10 * abs(E0)
+
+
+@pytest.mark.parametrize("lat,nu,nd", [(chain(3), 1, 1), (chain(4), 2, 1), (ring(6), 3, 3), (chain(6), 3, 2), (ring(5), 2, 1),
+                                       (chain(5), 2, 2)])
+@pytest.mark.parametrize("tol,m_max", [(1e-6, 60), (1e-8, 16), (1e-12, 60), (1e-12, 10), (1e-15, 60)])
+def test_energy_and_gap_against_dense_eigenvalues(lat, nu, nd, tol, m_max):
+    """E0 within (tol + 256 eps) |H|_inf of the lowest eigenvalue, and the gap,
+    whose vector has a residual of 1e-6 |H|, second order in that but for the
+    quarter of 1e-9 |H| that its vectors may have lost of their orthogonality:
+    runs that close, that restart, and that converge within one batch."""
+    U = 8.0
+    ham = HubbardOracle(lat, U, nu, nd)
+    H = np.column_stack([ham.apply(0.3, e) for e in np.eye(ham.dim, dtype=complex)])
+    ev = np.linalg.eigvalsh(H)
+    B = hub.Basis(lat, U, nu, nd, device=0)
+    norm = hub.hub_basis_classes(B.handle)[2]
+    v = torch.empty(1, B.dim, dtype=torch.complex128, device=DEV)
+    st, e0, gap = hub.hub_ground_state(B.handle, 0.3, v, hub.make_opts(tol=tol, m_max=m_max))
+    B.close()
+    assert abs(e0 - ev[0]) <= (tol + 256 * 2.0 ** -52) * norm
+    assert abs(gap - (ev[1] - ev[0])) <= (1e-6 * norm) ** 2 / (ev[2] - ev[1]) + (tol + 1e-9) * norm
