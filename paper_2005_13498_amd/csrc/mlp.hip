@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdint>
 
+#include "gelu.h"
 #include "hub.h"
 #include "mlp.h"
 
@@ -25,35 +26,10 @@ constexpr int kMlpBlock = 256, kMlpWaves = kMlpBlock / 64;
 constexpr int kGradStride = kP + 1;  // partial row: gradient, then the loss
 
 __device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-// GELU (x) and its derivative (y): h = z Phi(z), h' = Phi(z) + z phi(z).
-// Branch-free, so that the 32 evaluations of a lane per tile interleave with
-// each other and the matrix instructions (the library's erff branches on its
-// argument).  Phi(z) = 1/2 + z p(z^2) for z^2 < 2, else from its tail
-// phi-weighted, e^{-z^2/2} q r(q) with q = 1 / (1 + |z| / sqrt 8); p and r are
-// least-maximum fits of those functions (to 3e-10 and 2e-9).  Against 64 bits
-// over [-8, 8]: Phi 8.4e-8 at most, 1.3e-8 rms (from a correctly rounded erff:
-// 6.0e-8, 1.5e-8), h 3.8e-7, 6.1e-8 rms (4.5e-7, 6.8e-8).
-__device__ __forceinline__ float2 gelu_both(float z) {
-  const float u = z * z;
-  float p = 4.20559104e-07f;
-  p = fmaf(p, u, -8.76378544e-06f);
-  p = fmaf(p, u, 0.000114431277f);
-  p = fmaf(p, u, -0.00118652277f);
-  p = fmaf(p, u, 0.00997322239f);
-  p = fmaf(p, u, -0.0664903149f);
-  p = fmaf(p, u, 0.398942292f);
-  const float q = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.35355338f, 1.0f));
-  float r = -0.101734042f;
-  r = fmaf(r, q, 0.278311163f);
-  r = fmaf(r, q, 0.0145136295f);
-  r = fmaf(r, q, 0.171200514f);
-  r = fmaf(r, q, 0.137736544f);
-  const float e = __builtin_amdgcn_exp2f(u * -0.72134752f);
-  const float tail = r * q * e;
-  const float far = z > 0.0f ? 1.0f - tail : tail;
-  const float phi = u < 2.0f ? fmaf(z, p, 0.5f) : far;
-  return make_float2(z * phi, fmaf(z * 0.39894228040143268f, e, phi));
-}
+struct GeluOps {
+  static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+  static __device__ __forceinline__ float exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+};
 __device__ __forceinline__ float lane_bcast(float v, int src) { return __shfl(v, src, 64); }
 __device__ __forceinline__ float wave_sum_f(float v) {
 #pragma unroll
@@ -247,9 +223,9 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
       for (int s = 0; s < 2; ++s) z = mfma4(w1[t][s], x[s], z);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float2 q = gelu_both(z[r]);
-        h1[t][r] = q.x;
-        g1[t][r] = q.y;
+        const Gelu q = gelu_both<GeluOps>(z[r]);
+        h1[t][r] = q.h;
+        g1[t][r] = q.d;
       }
       *reinterpret_cast<f32x4*>(H + c * kTStride + 16 * t + 4 * g) = h1[t];
     }
@@ -267,9 +243,9 @@ __global__ __launch_bounds__(kGradBlock) void k_mlp_grad(const float* __restrict
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float2 q = gelu_both(z[r]);
-        h2[t][r] = q.x;
-        dz[t][r] = q.y;
+        const Gelu q = gelu_both<GeluOps>(z[r]);
+        h2[t][r] = q.h;
+        dz[t][r] = q.d;
         o = fmaf(w3[r], h2[t][r], o);
       }
     }
