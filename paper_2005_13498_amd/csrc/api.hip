@@ -1265,6 +1265,8 @@ hub_status hub_basis_create(const hub_lattice* lat, int32_t n_up, int32_t n_dn, 
   D.nc = static_cast<int>(B.classes.size());
   D.n_sites = B.lat.n_sites;
   D.U = B.lat.U;
+  int n_cu = 0;
+  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && n_cu > 0) D.n_cu = n_cu;
   hub_status s = HUB_OK;
   if ((s = upload(h, &D.up_bits, B.up.states)) != HUB_OK) return cleanup(s);
   if ((s = upload(h, &D.dn_bits, B.dn.states)) != HUB_OK) return cleanup(s);
@@ -2231,9 +2233,7 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
   }
   if (h->greens_path == 1 && !members_fit)
     return fail(HUB_E_INVALID, "the persistent member stepper needs reorth 0, substeps 1 and grouped hop tables");
-  int n_cu = 0;
-  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || n_cu < 1)
-    n_cu = 256;
+  const int n_cu = h->D.n_cu;
   const int members_least = members_auto_least(members_dim, n_cu);
   // with fewer members than compute units only where no target's kernels were
   // chosen (hub_set_apply_path, hub_set_propagate_path) nor are to be timed

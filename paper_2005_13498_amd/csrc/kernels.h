@@ -61,7 +61,8 @@ struct DevBasis {
   uint8_t up_slot_class[64] = {0};
   int up_nslots = 0, up_maxs_pad = 8;
   // grouped tables of the block apply (class ranges rounded up to a multiple
-  // of four slots): [dim][gslots] entries as above, class of every group
+  // of four slots): [dim][gslots] entries src, bit 15 set for a negative hop,
+  // pad dim; class of every group
   uint16_t* dn_tabg = nullptr;
   uint16_t* up_tabg = nullptr;
   uint8_t dn_gclass[8] = {0};
@@ -76,7 +77,7 @@ struct DevBasis {
   int tuned_single[2] = {-1, -1};
   int tuned_lanczos[2] = {-1, -1};
   int tuned_block[2][4] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
-  int up_max_hops = 0, dn_max_hops = 0;
+  int n_cu = 256;                // compute units of the device
 };
 
 enum ApplyMode : int {

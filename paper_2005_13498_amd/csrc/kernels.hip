@@ -731,11 +731,11 @@ int batch_columns(const DevBasis& db, int prec, int nvec) {
   const size_t col = (static_cast<size_t>(db.dim_up) + 1) * 16;
   const int groups = prec == 0 ? nvec : (nvec + 1) / 2;
   // 8 columns per workgroup, one workgroup per compute unit, where that makes
-  // nearly whole rounds of the 256 (12 sites, 8 complex64 vectors, 464
+  // nearly whole rounds of them (of 256: 12 sites, 8 complex64 vectors, 464
   // workgroups: 82.6 us vs 90.9 with 4 columns; 3 complex128 vectors, 348:
   // 60.7 vs 54.5), else 4, or 2 where 4 do not fit (14 sites)
-  const int w8 = groups * ((db.dim_dn + 7) / 8), rounds = (w8 + 255) / 256;
-  if (8 * col <= kLds && 20 * w8 >= 17 * 256 * rounds) return 8;
+  const int w8 = groups * ((db.dim_dn + 7) / 8), rounds = (w8 + db.n_cu - 1) / db.n_cu;
+  if (8 * col <= kLds && 20 * w8 >= 17 * db.n_cu * rounds) return 8;
   return 4 * col <= kLds ? 4 : (2 * col <= kLds ? 2 : -1);
 }
 
