@@ -482,7 +482,8 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   // 3,130; complex128 singles stay ahead at 12 sites, 1,367 / 1,547.  Fewer
   // vectors are faster each on a lane of its own than in pairs (2 and 3: 12
   // sites c64 282 / 342 and 361 / 434, 13 sites c64 778 / 871, 11 sites c128 169
-  // / 187 and 198 / 210).  On one lane a group is never split: three steps timed, singles / pair or block, 12 sites c64, 2
+  // / 187 and 198 / 210), but for large tiles (below).  On one lane a group is
+  // never split: three steps timed, singles / pair or block, 12 sites c64, 2
   // vectors, 1,768 / 1,497; 11 sites c128, 2 and 4, 1,727 / 1,233 and 3,407 /
   // 2,440, c64, 2, 1,559 / 995; 12 sites of 6 + 3 c64, 8, fours 1,937, one
   // block of 8 1,678.
@@ -498,7 +499,17 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
     // 1 2,336 / 1,414)
     if (one_lane) gmax = mid ? gmax : 1;
     else if (fours || !mid || (propagate && nvec < 4)) gmax = 1;
+    // (two or three large ones in a pair where the single-vector kernels are at
+    // their worst, a column pass of two columns or a row pass of 16 and more
+    // slots: three steps, singles / pair, 2 vectors: 14 sites of 7 + 7 13,119 /
+    // 11,980, 5 + 7 (52 MiB) 7,233 / 6,809, 4 + 7 (26 MiB) 3,083 / 3,040, 7 + 6, 12
+    // slots, 10,799 / 11,317; two columns: 15 of 6 + 6 34,043 / 28,163, 6 + 5
+    // 19,447 / 17,207, 6 + 3 (17 MiB) 2,482 / 2,394, 16 of 6 + 2 (7 MiB) 2,097 / 2,235)
+    const bool worst =
+        (h->D.maxs_pad >= 16 && mib >= 48.0) || (hub::colpass_width(h->D, prec) < hub::kColW && mib >= 16.0);
+    const bool pairs = propagate && prec == 1 && nvec < 4 && worst && hub::block_two_pass(h->D, prec, 2);
     if (fours) gmax = std::max(gmax, 4);
+    else if (pairs) gmax = std::max(gmax, 2);
     else if (one_lane && prec == 1 && nvec > 1 && gmax == 1 && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
   } else if (propagate && prec == 1 && gmax == 1) {
     // smaller tiles with long rows: fours where several would share a lane (us

@@ -85,6 +85,13 @@ def test_groups_of_four_complex128_vectors(n, nu, nd, groups):
     assert [g for g, _ in _plan(ring(n), nu, nd, C128, 4)] == groups
 
 
+@pytest.mark.parametrize("n,nu,nd,nvec,groups", [
+    (14, 7, 7, 2, [2]), (14, 7, 7, 3, [2, 1]), (14, 5, 7, 2, [2]), (14, 4, 7, 2, [1, 1]), (14, 7, 6, 2, [1, 1]),
+    (13, 7, 6, 2, [1, 1]), (15, 6, 5, 3, [2, 1]), (15, 6, 3, 2, [2]), (16, 6, 2, 2, [1, 1]), (16, 5, 5, 3, [1] * 3)])
+def test_pairs_of_large_complex64_tiles(n, nu, nd, nvec, groups):
+    assert [g for g, _ in _plan(ring(n), nu, nd, C64, nvec)] == groups
+
+
 @pytest.mark.parametrize("n,nu,nd,prec,nvec,groups", [
     (16, 8, 1, C128, 8, [(8, 0)]), (16, 6, 1, C128, 8, [(8, 0)]), (14, 7, 0, C64, 8, [(8, 0)]), (16, 8, 0, C64, 2, [(2, 0)]),
     (15, 1, 7, C64, 2, [(2, 2)]), (14, 0, 7, C128, 2, [(1, 0)] * 2), (14, 1, 7, C128, 2, [(2, 0)]),
