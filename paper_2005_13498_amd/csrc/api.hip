@@ -568,8 +568,8 @@ std::vector<ApplyGroup> apply_groups(hub_basis h, int nvec, int prec) {
   const bool automatic = h->force_group == 0 && (h->apply_group[prec] <= 0 || h->apply_batch[prec]);
   if (nvec > 1 && automatic && h->D.two_pass == -1 && h->D.block_path == -1 && !batch_misfit(h, nvec, prec)) {
     // where a batch could stage only two columns, or none, vectors that gather
-    // theirs go one by one: a vector of 14 sites takes 131 us instead of 213
-    // (complex64) or 250 instead of 286 (complex128), of 15 sites 590 instead
+    // theirs go one by one: a vector of 14 sites takes 139 us instead of 211
+    // (complex64) or 240 instead of 283 (complex128), of 15 sites 590 instead
     // of 1,150; 4 columns are as fast (13 sites, complex128: 58 against 60)
     if (hub::apply_gathers(h->D, prec) && hub::apply_two_pass(h->D, prec, 1, hub::kPlain, false) &&
         hub::batch_columns(h->D, prec, std::min(nvec, kMaxNV)) < 4) {
@@ -2441,14 +2441,15 @@ hub_status hub_greens_diag(hub_basis h, int32_t n_targets, const hub_basis* targ
 
 // ---------------------------------------------------------------------------
 // Ground state: restarted Lanczos, complex double, its vectors orthogonal
-// within a checked bound (gs_lanczos); the lowest Ritz pair of the tridiagonal on the host.
+// within a checked bound (gs_lanczos); the lowest Ritz pair of the tridiagonal
+// on the host.
 namespace {
 
 // Iterations enqueued between two looks at the residual (the host waits once
 // per batch; those past the one that converges go into T and the Ritz vector
-// as well).  10 sites:
-// 6.8 ms at 8 iterations, 5.5 at 16; what a batch loses of the orthogonality
-// doubles with its length at first (1e-13 of |H| = 60 at 8, 2e-13 at 16).
+// as well).  10 sites: 6.8 ms at 8 iterations, 5.5 at 16; what a batch loses of
+// the orthogonality doubles with its length at first (1e-13 of |H| = 60 at 8,
+// 2e-13 at 16).
 constexpr int kGsBatch = 16;
 // Lanczos vectors kept: up to kGsWider times m_max within kGsWideBytes.
 constexpr int kGsWider = 4;

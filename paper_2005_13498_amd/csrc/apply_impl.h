@@ -670,9 +670,10 @@ hipError_t colpass_s(const ApplyLaunch& L, int* pgrid) {
 // that the source rows' segments stay in the L2 of the XCD that works on those
 // columns.  A wavefront owns one row's segment: its hops, source addresses and
 // coefficients are the same on every lane and live in scalar registers.  What
-// is left is bound by fabric traffic: 16 sites, complex128, 2.38 ms for x 2.3
-// times, y in and out at 5.6 TB/s; 64 lanes over 8 rows of 8 columns read x
-// once by count but twice by lines (a row is no whole number of them), 3.6 ms.
+// is left is bound by fabric traffic: 16 sites, complex128, 2.38 ms for x 3.2
+// times, y in and out by the counters, 13.9 GB at 5.8 TB/s (14 sites 136 us, x
+// 1.2 times, 4.5 TB/s); 64 lanes over 8 rows of 8 columns read x once by count
+// but twice by lines (a row is no whole number of them), 3.6 ms.
 // The terms are added in the one-pass kernel's order: bit-identical.
 struct GatherArgs {
   int dim_up, dim_dn, row_groups;
@@ -782,7 +783,7 @@ hipError_t colgather(const ApplyLaunch& L) {
 // once for all of them, and the workgroups of the same rows run side by side
 // on one XCD, whose L2 then holds those rows (one workgroup per row had 64
 // rows in flight on an L2 of 20).  The L1's rate bounds it, 34 64-byte
-// accesses per gather of a wavefront: 16 sites, complex128, 2.01 ms, 2.55 with
+// accesses per gather of a wavefront: 16 sites, complex128, 2.05 ms, 2.55 with
 // a workgroup per row; with half the loads in flight and twice the wavefronts
 // 2.32.
 struct RowArgs {

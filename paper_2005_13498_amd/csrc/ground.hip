@@ -1,6 +1,7 @@
-// Ground-state Lanczos kernels: complex double, one vector.  An iteration is the H v kernels and two launches, with no host
-// wait in between: inner products and subtraction of the two vectors that H v
-// overlaps with (and of the deflated one).  The last two iterations of a batch
+// Ground-state Lanczos kernels: complex double, one vector.  An iteration is
+// the H v kernels and two launches, with no host wait in between: inner
+// products and subtraction of the two vectors that H v overlaps with (and of
+// the deflated one).  The last two iterations of a batch
 // have the same two launches once more against every vector, which takes out
 // what the three-term recurrence let grow back; gs_lanczos checks how much
 // that was.  Vectors are stored as subtracted, with their norms beside them.
@@ -12,7 +13,7 @@
 // the caches).  A whole ground state with its gap took 192 ms with a dense
 // eigenproblem, three waits on the host per iteration and start vectors from
 // the host, 12.6 ms with every product against every vector of up to 60, and
-// 5.5 ms now (240 iterations, whose three launches of 4 to 6 us bound it).
+// 5.5 ms now (240 iterations, whose three launches of 5 to 7 us bound it).
 #include "ground.h"
 
 #include <algorithm>

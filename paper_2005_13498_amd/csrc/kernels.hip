@@ -627,11 +627,12 @@ bool apply_global_rows(const DevBasis& db, int prec, int nv) {
   return nv == 1 && apply_lds_bytes(db, prec, 1, 1) > 150 * 1024;
 }
 
-// Larger than the eight XCDs' L2s together: one vector, one pass / staged
-// columns / gathered columns, in us: 24 MB (13 sites, complex64) - / 40 / 40;
-// 47 MB (13 sites, complex128) - / 67 / 60; 94 MB (14 sites, complex64) 200 /
-// 200 / 140; 188 MB (14 sites, complex128) 300 / 306 / 249; 2.6 GB (16 sites,
-// complex128, nothing fits LDS) 5040 / - / 4390.
+// Larger than the eight XCDs' L2s together: one vector, changing buffers, one
+// pass / gathered columns, in us: 47 MB (13 sites, complex128) 104 / 72, 94 MB
+// (14 sites, complex64) 228 / 142, 188 MB (14 sites, complex128) 287 / 243, 331
+// MB (15 sites, complex64) 894 / 590, 2.6 GB (16 sites, complex128) 5,033 /
+// 4,423.  Staged columns: 24 MB (13 sites, complex64) as fast as gathered ones,
+// 14 sites, complex64, 200 where those then took 140, 15 and 16 sites do not fit.
 bool apply_gathers(const DevBasis& db, int prec) {
   if (apply_global_rows(db, prec, 1) && db.dn_gslots == 0) return false;  // no grouped table for the row pass
   return static_cast<double>(db.dim) * (prec == 0 ? 16 : 8) > 32.0 * 1024 * 1024;

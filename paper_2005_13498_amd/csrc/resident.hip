@@ -21,7 +21,7 @@
 // summed in FP64 from the first iteration's group sums with the coefficients
 // of the sample time.
 //
-// The one workgroup's VALU issue bounds it (71 % busy: about 200 instructions
+// The one workgroup's VALU issue bounds it (67 % busy: about 200 instructions
 // an element and iteration, most of them addresses, signs and products of the
 // hops).  50 steps of 70 x 70 complex128 elements (450 iterations) took 5.64
 // ms; with sums across lanes by DPP and up sources kept as LDS offsets 5.19,
