@@ -22,9 +22,9 @@ namespace dev {
 //     complex64 or one complex128, interleaved in LDS only, so that a hop is
 //     one 16-byte read and its table entry is decoded once for both.  Eight
 //     complex64 vectors of 12 sites 126 -> 83 us (1.3 TB/s of x and y; the
-//     row pass keeps the VALU busy 58 % and the LDS 54 % of its 40 us, three
+//     row pass keeps the VALU busy 59 % and the LDS 55 % of its 40 us, three
 //     fifths of that bank conflicts of the random 16-byte gathers, the column
-//     pass 51 % and 35 % of 43 us), eight
+//     pass 51 % and 34 % of 43 us), eight
 //     complex128 ones 209 -> 139 us; 14 sites 2,045 -> 1,689 and 3,770 ->
 //     2,265 us.  More words per element in the row pass (2 or 4, as the block
 //     kernels) conflict less but leave too few wavefronts: 100-112 us.
