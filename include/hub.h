@@ -524,9 +524,9 @@ typedef struct {
 hub_status hub_tune(hub_basis basis, hub_prec prec, int32_t reps, hub_tuning *out, void *stream);
 hub_status hub_set_tuning(hub_basis basis, hub_prec prec, const hub_tuning *t);
 
-/* The plan for nvec vectors (propagate = 1: hub_propagate, 0: hub_apply_H):
- * n_groups, and per group (host arrays of >= nvec entries, either may be
- * NULL) its size and kernels: 0 one pass, 1 two-pass single vector, 2
+/* The plan for nvec vectors (propagate = 1: hub_propagate with opts.reorth 0,
+ * 0: hub_apply_H): n_groups, and per group (host arrays of >= nvec entries,
+ * either may be NULL) its size and kernels: 0 one pass, 1 two-pass single vector, 2
  * two-pass kernels over several vectors (blocks, or the batches hub_apply_H
  * takes in the caller's layout). */
 hub_status hub_get_plan(hub_basis basis, hub_prec prec, int32_t nvec, int32_t propagate, int32_t *n_groups,

@@ -455,8 +455,10 @@ bool one_lane_only(hub_basis h, bool pulsed) { return h->prof || (h->ctrl_on && 
 // Group sizes for nvec vectors: powers of two up to 8 whose staged row keeps
 // at least three apply workgroups per CU (<= 48 KB of the 160 KB LDS), or one
 // vector per group; single vectors where the two-pass kernels apply.
-// one_lane: the groups of a propagation run one after another.
-std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = true, bool one_lane = false) {
+// one_lane: the groups of a propagation run one after another.  reorth: its
+// iterations are re-orthogonalised, so none is fused.
+std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = true, bool one_lane = false,
+                            bool reorth = false) {
   const int tuned =
       h->force_group > 0 ? h->force_group : (propagate ? tuned_prop_group(h, nvec, prec) : h->apply_group[prec]);
   if (tuned > 0) {
@@ -491,8 +493,15 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
   const bool automatic = h->D.two_pass == -1 && h->D.tuned_single[prec] < 0;
   const bool mid = automatic && mib >= 1.0 && mib < 4.0;  // single vectors: two passes or, in tall tiles, one
   if (mid || hub::apply_two_pass(h->D, prec, 1, hub::kLanczos, false)) {
+    // Re-orthogonalised, up to eight vectors keep the pairs of their rows (four
+    // steps, fours / pairs: 11 sites c128, 5 and 8 vectors, 5,372 / 4,179 and 6,438
+    // / 5,168, 12: 8,368 / 8,986; 12 sites of 4 + 5 c64, 4 and 8, 4,567 / 3,553 and
+    // 5,772 / 4,955), complex128 from 4 MiB on singles (12 sites of 4 + 5, 8 and 12
+    // vectors, fours / singles 10,016 / 8,864 and 14,052 / 13,232).
+    const bool keep = reorth && ((prec == 0 && mib >= 4.0) || (mid && gmax == 2 && nvec <= kMaxNV));
     const bool small = automatic && prec == 0 && mib < 8.0;
-    const bool fours = propagate && (prec == 1 ? nvec > 3 : small && nvec > 4) && hub::block_two_pass(h->D, prec, 4);
+    const bool fours =
+        propagate && !keep && (prec == 1 ? nvec > 3 : small && nvec > 4) && hub::block_two_pass(h->D, prec, 4);
     // where those blocks are not to be had, and for four complex128 vectors,
     // small tiles keep the groups of their rows (4 vectors, three steps, singles
     // / groups: 11 sites of 4 + 4 1,223 / 753, 15 of 3 + 3 1,245 / 887, 16 of 5 +
@@ -515,8 +524,10 @@ std::vector<int> groups_for(hub_basis h, int nvec, int prec, bool propagate = tr
     // smaller tiles with long rows: fours where several would share a lane (us
     // for three steps, singles on lanes / fours: 13 x 1,716 5 and 12 vectors
     // 1,323 / 1,006 and 2,379 / 1,355; 16 x 4,368 4, 8 and 12 vectors 794 / 1,462,
-    // 1,517 / 1,732 and 2,213 / 1,991; one lane, 4 vectors 2,853 / 1,687)
-    const int least = one_lane ? 2 : (h->D.dim_dn < 2048 ? 5 : 9);
+    // 1,517 / 1,732 and 2,213 / 1,991; one lane, 4 vectors 2,853 / 1,687;
+    // re-orthogonalised, four steps, 15 x 3,003 4, 5 and 8 vectors 1,772 / 2,263,
+    // 3,228 / 2,488 and 3,470 / 2,592)
+    const int least = one_lane ? 2 : (h->D.dim_dn < 2048 || reorth ? 5 : 9);
     if (nvec >= least && hub::block_two_pass(h->D, prec, 4)) gmax = 4;
   }
   // plain applies of blocks on the two-pass block kernels: the largest group
@@ -1686,7 +1697,7 @@ static hub_status run_all(hub_basis h, hub_prec prec, int32_t nvec, void* v_inou
     if (opts_ok && fits && (h->prop_path == 1 || (kernels_auto && worth)))
       return run_resident(h, prec, nvec, v_inout, n_steps, A_mid, A_sample, A_gauss, t_start, dt, o, obs, log, st);
   }
-  const std::vector<int> groups = groups_for(h, nvec, pi, true, one_lane_only(h, dA_mid != nullptr));
+  const std::vector<int> groups = groups_for(h, nvec, pi, true, one_lane_only(h, dA_mid != nullptr), o.reorth != 0);
   const bool want_obs = obs != nullptr && A_sample != nullptr;
   const int E = scheme_exps(o);
 

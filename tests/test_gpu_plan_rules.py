@@ -85,6 +85,35 @@ def test_groups_of_four_complex128_vectors(n, nu, nd, groups):
     assert [g for g, _ in _plan(ring(n), nu, nd, C128, 4)] == groups
 
 
+def _launches(n, nu, nd, prec, nvec, group=0):
+    """Lanczos launches of a re-orthogonalised propagation, in groups of
+    `group` where that is set: every group enqueues its own."""
+    from synth import PulseParams
+    B = hub.Basis(ring(n), 8.0, nu, nd, device=0)
+    try:
+        if group:
+            hub.hub_set_tuning(B.handle, prec, {"single_two_pass": 0, "block_two_pass": [0, 1, 1, 1],
+                                                "apply_group": 1, "prop_group": group})
+        dtype = torch.complex128 if prec == C128 else torch.complex64
+        g = torch.Generator(device="cuda:0").manual_seed(2)
+        x = torch.randn(1, B.dim, dtype=dtype, device="cuda:0", generator=g)
+        x = (x / torch.linalg.vector_norm(x)).repeat(nvec, 1)
+        hub.hub_controller_read_stats(B.handle)
+        hub.hub_propagate(B.handle, [PulseParams(0, 0.4, 8.0, 0.1, 0.1)] * nvec, 0.0, 0.01, 2,
+                          hub.make_opts(tol=1e-6, m_max=30, reorth=1), x)
+        return hub.hub_controller_read_stats(B.handle)["lanczos_launches"]
+    finally:
+        B.close()
+
+
+@pytest.mark.parametrize("n,nu,nd,prec,nvec,group", [
+    (11, 5, 5, C128, 8, 2), (12, 4, 5, C64, 4, 2), (12, 4, 5, C64, 8, 2), (11, 4, 4, C128, 8, 4),  # 1 to 4 MiB
+    (12, 4, 5, C128, 8, 1), (15, 14, 5, C64, 8, 4), (15, 14, 5, C64, 4, 1)])
+def test_groups_of_reorthogonalised_propagations(n, nu, nd, prec, nvec, group):
+    """Equal vectors, so that every group takes the same iterations."""
+    assert _launches(n, nu, nd, prec, nvec) == _launches(n, nu, nd, prec, nvec, group)
+
+
 @pytest.mark.parametrize("n,nu,nd,nvec,groups", [
     (14, 7, 7, 2, [2]), (14, 7, 7, 3, [2, 1]), (14, 5, 7, 2, [2]), (14, 4, 7, 2, [1, 1]), (14, 7, 6, 2, [1, 1]),
     (13, 7, 6, 2, [1, 1]), (15, 6, 5, 3, [2, 1]), (15, 6, 3, 2, [2]), (16, 6, 2, 2, [1, 1]), (16, 5, 5, 3, [1] * 3)])
